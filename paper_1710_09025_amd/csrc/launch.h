@@ -6,21 +6,23 @@
 
 namespace pamc {
 
-// CM: colour-major, +-1 couplings (CM2T, CM3T: two or three colours with the
-// neighbour offsets in an LDS table); CQ: colour-major, real couplings; SQ: CQ on the
-// square lattice (four neighbours)
+// RB: +-1 couplings, replicas as bits of an LDS word; CQ: real couplings,
+// replica quads (two or three colours); SQ: CQ on the square lattice (four
+// neighbours)
 enum SweepVariant {
-    kSweepLex = 0,
-    kSweepEO8 = 1,
-    kSweepEO16 = 2,
-    kSweepCM2 = 3,
-    kSweepCM3 = 4,
     kSweepCQ2 = 5,
     kSweepCQ3 = 6,
     kSweepSQ2 = 7,
     kSweepSQ3 = 8,
-    kSweepCM2T = 9,
-    kSweepCM3T = 10
+    kSweepRB = 16
+};
+
+// What a sweep launch needs to know of its instances' lattice and shape.
+struct SweepShape {
+    int variant = 0, tile_rows = 0, row_bytes = 0;
+    int tpr = 0, rp = 0;  // CQ, SQ: threads per replica quad, quads per workgroup
+    int G = 0, plane = 0; // RB: Philox blocks of the largest colour, words per site plane
+    int M = 0, sets = 0;  // RB: replicas per word, sets (of M replicas) per pass of a workgroup
 };
 
 // Dynamic LDS a sweep workgroup may take: gfx950 gives one workgroup up to
@@ -43,14 +45,6 @@ inline int cm_plane_bytes(int row_bytes) { return row_bytes <= 64 ? row_bytes : 
 // idle (tpr * rp is a multiple of 64 below).
 inline int cm_launch_threads(int tpr, int rp) { return (tpr * rp + 63) / 64 * 64; }
 
-// LDS of the neighbour table of the table forms: per colour and Philox
-// block (tpr records a colour) 24 slot offsets of 16 bits, 48 bytes; 16
-// more for its alignment.
-inline int cm_table_bytes(int variant, int tpr)
-{
-    return variant == kSweepCM2T ? 16 + 96 * tpr : variant == kSweepCM3T ? 16 + 144 * tpr : 0;
-}
-
 // LDS stride of one replica-quad slot of `planes` byte planes.  Below 64
 // threads per quad one wave sweeps 64 / tpr quads side by side; unpadded,
 // their slots (a multiple of 64 words for rows longer than 64 bytes, 128
@@ -68,6 +62,15 @@ inline int cm_slot_bytes(int row_bytes, int tpr, int planes)
     return base + (((want - base) % 256) + 256) % 256;
 }
 
+// The replica-word sweep: LDS words of a set's site plane (plane i holds
+// site i of every four-site block of a row; a multiple of 64 words for rows
+// of more than 128 bytes, so that every plane starts at bank 0), whether a
+// workgroup sweeps one set, its threads and dynamic LDS for `sets` sets.
+inline int rb_plane(int row_bytes) { return row_bytes <= 128 ? row_bytes / 4 : (row_bytes / 4 + 63) & ~63; }
+bool rb_uniform(int G);
+int rb_threads(int G, int sets);
+size_t rb_lds(int plane, int sets);
+
 // LDS of one cluster-move pair (the island search of one lane group): the
 // sector flags of every lexicographic site (a byte: bit 0 where the replicas
 // differ, bit 1 where they agree), the visited bits, the
@@ -84,22 +87,18 @@ static_assert(icm_pair_bytes(32 * 32 * 32) <= kMaxSweepLds, "cluster-move pair e
 // default number of replica quads a colour-major workgroup sweeps at once
 // (tpr threads per quad)
 int cm_replicas_per_block(int tpr);
-// replicas swept at once by an even/odd-x workgroup (L = 8 or 16); its tile
-// holds a multiple of this many rows
-int eo_replicas_per_pass(int L);
-
 // lds_bytes: staging for packed rows (max(16384, row_bytes) when any instance
 // of the launch is packed, else 0)
 void launch_init(const Inst *insts, const Work *work, int nwork, size_t lds_bytes, hipStream_t st);
 void launch_energy(const Inst *insts, const Work *work, int nwork, const int8_t *const *Jraw, hipStream_t st);
 // sweeps of one temperature step; the last workgroup of each instance also
 // measures the step and prepares its resampling table
-// (tpr, rp: threads per replica quad and replica quads per workgroup of the
-// colour-major kernel; unused by the others).  phase 0: all N_S sweeps;
-// with cluster moves, phase 1: the first floor(N_S/2) sweeps (no energies,
-// no measurement), phase 2: the rest with energies and the measurement.
-void launch_sweep(int variant, const Inst *insts, const Work *work, int nwork, int tile_rows, int row_bytes, int tpr,
-                  int rp, int phase, hipStream_t st);
+// (phase 0: all N_S sweeps; with cluster moves, phase 1: the first
+// floor(N_S/2) sweeps without energies and measurement, phase 2: the rest
+// with both).
+void launch_sweep(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
+void launch_sweep_rb(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
+hipError_t sweep_rb_init();
 // resampling weights and their normaliser (instances with real couplings;
 // work items are 1024-row blocks)
 void launch_weights(const Inst *insts, const Work *work, int nwork, hipStream_t st);

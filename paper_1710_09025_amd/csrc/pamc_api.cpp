@@ -32,7 +32,8 @@ struct pamc_batch {
 namespace pamc {
 int make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const double *beta, int nT, int NS,
               uint64_t seed, const pamc_options &opt, HostInst &h);
-bool shape_valid(const HostInst &h, int tile_rows, int rp, const char **why);
+bool shape_valid(const HostInst &h, const char **why);
+bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why);
 void default_shape(HostInst &h, int gmax);
 int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt);
 }
@@ -104,12 +105,11 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
     // the normaliser's tree folds at most 2^19 roots of 1024-row blocks
     if (real && cap > ((int64_t)1 << 29)) return invalid("real couplings: capacity must stay at or below 2^29");
     const pamc::LayoutInfo li = pamc::layout_for(L, real, dim);
-    if (li.layout < 0) return invalid("real couplings need even L <= 20 or odd L <= 21");
+    if (!li.valid) return invalid("real couplings need even L <= 20 or odd L <= 21");
     h.dim = dim;
     h.L = L;
     h.N = N;
     h.ncol = li.ncol;
-    h.layout = li.layout;
     h.variant = li.variant;
     h.row_bytes = li.row_bytes;
     h.packed = opt.spin_format == PAMC_SPINS_PACKED ? 1 : 0;
@@ -146,25 +146,12 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
     pamc::default_shape(h, li.gmax);
     if (opt.tile_rows < 0 || opt.tile_rows > 4096) return invalid("tile_rows out of range");
     if (opt.group_replicas < 0 || opt.group_replicas > 1024) return invalid("group_replicas out of range");
-    const bool cm = h.variant == pamc::kSweepCM2 || h.variant == pamc::kSweepCM2T || h.variant == pamc::kSweepCM3 ||
-                    h.variant == pamc::kSweepCM3T ||
-                    h.variant == pamc::kSweepCQ2 || h.variant == pamc::kSweepCQ3 || h.variant == pamc::kSweepSQ2 ||
-                    h.variant == pamc::kSweepSQ3;
-    if (opt.tile_rows > 0 || (cm && opt.group_replicas > 0)) {
-        // the colour-major kernel sweeps replicas in fours
-        if (cm && opt.group_replicas % 4) return invalid("group_replicas must be a multiple of four for this lattice");
-        const int rp = cm && opt.group_replicas > 0 ? opt.group_replicas / 4 : h.rp;
-        // without an explicit tile: the default number of passes per workgroup
-        int tr = opt.tile_rows > 0 ? opt.tile_rows : (cm ? h.tile_rows / h.rp * rp : h.tile_rows);
-        // the even/odd-x kernel sweeps a fixed number of replicas per pass
-        if (h.variant == pamc::kSweepEO8 || h.variant == pamc::kSweepEO16) {
-            const int p = pamc::eo_replicas_per_pass(L);
-            tr = (tr + p - 1) / p * p;
-        }
+    // lattices whose sweep takes replicas in fours honour group_replicas
+    const bool quads = real || !(L == 8 || L == 16 || L > 21 || (L > 20 && L % 2 == 0));
+    if (opt.tile_rows > 0 || (quads && opt.group_replicas > 0)) {
+        if (quads && opt.group_replicas % 4) return invalid("group_replicas must be a multiple of four for this lattice");
         const char *why = nullptr;
-        if (!pamc::shape_valid(h, tr, rp, &why)) return invalid(why);
-        h.tile_rows = tr;
-        h.rp = rp;
+        if (!pamc::explicit_shape(h, li.gmax, opt.tile_rows, opt.group_replicas, &why)) return invalid(why);
     } else if (opt.autotune) {
         const int st = pamc::tune_shape(h, opt, nullptr);
         if (st != PAMC_OK) return st;
@@ -219,7 +206,7 @@ int64_t pamc_footprint(int L, int64_t R, int n_temps, const pamc_options *opt)
     const pamc_options o = resolve(opt);
     const int dim = o.dim == 0 ? 3 : o.dim;
     if ((dim != 2 && dim != 3) || L < 2 || L > (dim == 3 ? 32 : 64) || R < 1 || n_temps < 1) return -1;
-    if ((o.real_couplings || dim == 2) && pamc::layout_for(L, true, dim).layout < 0) return -1;
+    if ((o.real_couplings || dim == 2) && !pamc::layout_for(L, true, dim).valid) return -1;
     const bool real = o.real_couplings != 0 || dim == 2;
     const int64_t cap = o.capacity > 0 ? o.capacity : pamc::default_capacity(R);
     const int nov = (o.overlap_steps && o.n_overlap_steps > 0) ? o.n_overlap_steps : 1;
@@ -444,7 +431,7 @@ int pamc_batch_create(int n, const pamc_instance *inst, const pamc_options *opt,
         auto gkey = [](const HostInst &h) { return GKey(h.variant, h.dim, h.L, h.NS, h.packed); };
         std::map<GKey, int64_t> rows;
         for (const HostInst &h : v) rows[gkey(h)] += h.R;
-        std::map<GKey, std::pair<int, int>> shape;
+        std::map<GKey, HostInst> shape;
         for (auto &kv : rows) {
             HostInst t;
             for (const HostInst &h : v)
@@ -456,14 +443,11 @@ int pamc_batch_create(int n, const pamc_instance *inst, const pamc_options *opt,
             t.Rcap = pamc::default_capacity(t.R);
             const int st = pamc::tune_shape(t, o, nullptr);
             if (st != PAMC_OK) return st;
-            shape[kv.first] = {t.tile_rows, t.rp};
+            shape[kv.first] = std::move(t);
         }
         for (HostInst &h : v) {
-            const auto s = shape[gkey(h)];
-            if (pamc::shape_valid(h, s.first, s.second, nullptr)) {
-                h.tile_rows = s.first;
-                h.rp = s.second;
-            }
+            const HostInst &s = shape[gkey(h)];
+            if (pamc::shape_valid(s, nullptr)) pamc::take_shape(h, s);
         }
     }
     std::unique_ptr<pamc_batch> b(new (std::nothrow) pamc_batch());

@@ -21,27 +21,14 @@ constexpr uint32_t kTagSweep = 0x20000000u;
 constexpr uint32_t kTagResample = 0x30000000u;
 constexpr uint32_t kTagIcm = 0x40000000u;
 
-// Spin storage layouts inside one replica row.
-enum Layout : int32_t {
-    // byte per site (0: S = -1, 1: S = +1), lexicographic s = x + L(y + Lz)
-    kLayoutLex = 0,
-    // byte per site, the sites of colour 0 then those of colour 1, each in
-    // lexicographic order: pos = c N/2 + (zL + y)(L/2) + (x >> 1) for the
-    // site of colour c = (x + y + z) & 1.  Used for L = 8 and 16 (L/2 a
-    // multiple of four): the four sites of one Philox block are one aligned
-    // 32-bit word inside one row (y, z), their y and z neighbours and one x
-    // neighbour are the word at the same place of the other colour's rows,
-    // and the other x neighbour is that word shifted by one byte.  Lanes
-    // sweeping consecutive blocks read consecutive words.
-    kLayoutEO = 1,
-    // byte per site, colour-major: the sites of colour 0 in lexicographic
-    // order, then colour 1 (and 2 for odd L), each colour padded to a
-    // multiple of four, so the four sites of one Philox block are one
-    // aligned 32-bit word for every L.
-    kLayoutCM = 2,
-};
+// Spin storage inside one replica row: colour-major, one position per site
+// (0: S = -1, 1: S = +1).  The sites of colour 0 in lexicographic order, then
+// colour 1 (and 2 for odd L), each colour padded to a multiple of four, so
+// that the four sites of one Philox block are positions 4 b ... 4 b + 3 for
+// every L.
 
 constexpr int kRowsPerBlock = 1024;  // rows handled per block by row kernels
+constexpr int kDirectRows = 32768;    // +-1 populations up to this size are measured row by row
 constexpr int kOvlPairs = 2048;      // replica pairs per overlap workgroup (few workgroups: most steps measure no overlap)
 constexpr int kOvlLdsBins = 8194;    // overlap histograms up to this many bins (L <= 16) are built in LDS
 
@@ -70,7 +57,7 @@ struct EMoments {
 
 struct Inst {
     // problem
-    int32_t L, N, ncol, layout;
+    int32_t L, N, ncol;
     int32_t dim;        // lattice dimension: 3 (cubic, N = L^3) or 2 (square, N = L^2; real couplings only)
     int32_t row_bytes;  // bytes per replica row in LDS, one byte per storage position (>= N, multiple of 16)
     int32_t packed;     // 1: the spin buffers hold one bit per storage position
@@ -92,7 +79,8 @@ struct Inst {
     uint32_t *fam[2];
     // resampling scratch
     uint32_t *map;      // [Rcap] destination row -> source row
-    uint32_t *loff;     // [Rcap] first destination of each row inside its row block
+    uint32_t *loff;     // [Rcap] real couplings: first destination of each row inside its row block (+-1 couplings
+                        //    keep those in the idle energy buffer); +-1 couplings: parts of the energy histogram
     uint32_t *bsum;     // [nblk]
     uint32_t *boff;     // [nblk]
     uint32_t *sync;     // [4] workgroups finished in the current sweep / post / weights launch
@@ -100,7 +88,8 @@ struct Inst {
     int32_t post_blocks;  // workgroups of this instance in a post launch
     int32_t tile_rows;    // replica rows per sweep workgroup
     uint32_t *hist;     // [nlev] energy histogram, (E + 3N)/2
-    uint2 *BF;          // [nlev] (floor(tau), frac(tau) 2^32) per level above E_min
+    int32_t hist_copies;  // parts the sweep's workgroups count into: hist, and more in loff (cleared by k_expand);
+                          //    0: at most kDirectRows rows, measured from their energies
     uint32_t *cnt;      // [R] descendants per family
     double *fpart;      // [max(1, fam_pow2 / 2048)] family tree partial sums
     // tables
@@ -109,24 +98,26 @@ struct Inst {
     const double *rho;  // [nT] exp(-2 (beta_{k+1} - beta_k)), host libm
     const double *Rt;   // [nT] nominal population R(beta_k) the resampling targets
     const double *nlnn; // [>= Rcap + 1] n ln n, host libm (shared)
-    const uint4 *site;  // lex layout: [N] {nb+x|nb-x<<16, nb+y|nb-y<<16, nb+z|nb-z<<16, jmask}
-    const uint16_t *grp;// lex layout: [ncol][gmax][4] sites of each Philox block (0xFFFF: none)
-    const uint32_t *jeo;// EO layout: [2][N/8][6] coupling words per block
+    // +-1 couplings: per colour and Philox block 64 bytes, the LDS word
+    // indices (16 bits) within a set of the six neighbours of its four sites
+    // ([direction][site]), the sign bits (J = -1: bit 4 d + i) and the mask
+    // of real sites
+    const uint4 *rbtab; // [ncol][gmax][4]
+    int32_t rb_plane;   // LDS words per site plane (rb_plane())
     const uint16_t *pos;// [N] storage position of each lexicographic site
     const uint16_t *lexof; // [row_bytes] lexicographic site at each storage position (0xFFFF: padding)
-    // CM layout: per colour and Philox block, the 24 LDS byte offsets (within
-    // a replica slot) of the 6 neighbours of its 4 sites, in the spin copy or,
-    // for a -1 coupling, in the complemented copy at +row_bytes; word 24 is
-    // the mask of real (non-padding) sites, one 0x01 per byte.
+    // real couplings: per colour and Philox block, the 24 storage positions
+    // of the 6 neighbours of its 4 sites; word 24 is the mask of real
+    // (non-padding) sites, one 0x01 per byte.
     const uint16_t *cmdesc;  // [ncol][gmax][32]
-    int32_t cbase[3];   // CM layout: first byte of each colour
-    int32_t tpr;        // CM layout: threads per replica
-    int32_t plane_bytes;// CM layout: LDS stride of a replica quad's byte planes (>= row_bytes)
-    int32_t slot_bytes; // CM layout: LDS stride of the replica quads' slots (bank-skewed)
+    int32_t cbase[3];   // first storage position of each colour
+    int32_t tpr;        // real couplings: threads per replica quad
+    int32_t plane_bytes;// real couplings: LDS stride of a replica quad's byte planes (>= row_bytes)
+    int32_t slot_bytes; // real couplings: LDS stride of the replica quads' slots (bank-skewed)
     int32_t ncs[3];     // sites per colour
     int32_t gcs[3];     // Philox blocks per colour, ceil(ncs / 4)
     int32_t gmax;
-    // real couplings (CM layout)
+    // real couplings
     int64_t *Eq[2];     // energies, units of 2^-20
     double *wrep;       // [Rcap] resampling weight of each row
     double *wpart;      // [nblk] pairwise-tree roots of the 1024-row blocks

@@ -1,19 +1,19 @@
 // resample.hip -- resampling and the per-step statistics (paper Sec. II.B,
 // Eq. (2), Sec. V.A) for gfx950.
 //
-// After the sweep kernel (which also measured the step and prepared the
-// (floor(tau), frac(tau) 2^32) table), one post launch runs three kinds of
-// workgroups per instance:
-//   copies    n_r = floor(tau) + [u_r < frac(tau) 2^32] for 1024 rows, with
-//             their exclusive scan inside the workgroup; each also clears
-//             a slice of the step's energy histogram;
+// After the sweeps, one post launch runs three kinds of workgroups per
+// instance:
+//   copies    measures the step (energy sums, normaliser) and takes
+//             n_r = floor(tau) + [u_r < frac(tau) 2^32] for 1024 rows, with
+//             their exclusive scan inside the workgroup;
 //   families  n ln n of 2048 family ids, summed by the pairwise tree;
 //   overlap   spin overlaps of 2048 replica pairs (at overlap steps).
 // The last workgroup of an instance to finish scans the per-workgroup
 // totals into offsets, sets R_{k+1} and the capacity / extinction status,
 // folds the family partial sums, and advances the step.  An expand launch
 // then writes the copy map (destination row -> source row, stable order),
-// which the next sweep reads its tile through.
+// which the next sweep reads its tile through, and clears the step's energy
+// histogram.
 #include "launch.h"
 #include "pamc_dev.h"
 #include "step_common.h"
@@ -96,28 +96,245 @@ __device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t *sh, uint3
     return r;
 }
 
-// Copy counts of rows [row0, row0 + 1024) and their offsets in the block.
-__device__ void copies_role(const Inst &I, int k, uint32_t row0, uint32_t *sh)
+// Measurement of step k after its sweeps with +-1 couplings, by a workgroup of
+// 1024 threads: E_min, E_max, sum E, sum E^2 (exact integers; written to the
+// step's record by `writer`), and for k < nT-1 the level weights
+// w[m] = exp(-2 dbeta m) as a fixed product of rho^(2^b) and their normaliser
+// S by the pairwise tree over 2^ceil(log2(M+1)) levels.  Every copies
+// workgroup measures for itself: its pass over the energies or the histogram
+// comes out of the L2 (12 loads a thread at L = 8), where one workgroup at the
+// end of the sweep launch kept the whole chip waiting (64 threads at L = 8:
+// about 25 us a step) and every other one had to count itself in.
+//   Up to kDirectRows rows: the energies themselves, 32 a thread, with the
+// histogram built in LDS (a sweep launch then counts nothing: its atomics on
+// the few energies of a cold population follow each other about 0.1 us apart
+// on each address, 15-50 us a launch at 10^4 rows).
+//   Beyond: the histogram that the sweep's workgroups have counted.
+// pw: 40 doubles, a: 4096 doubles, of LDS.
+struct Levels {
+    int lmin;
+    double S;
+};
+
+struct LevelSums {
+    int64_t s1, s2;
+    int32_t lmin, lmax;
+    __device__ __forceinline__ void add(int m, int64_t c, int N3)
+    {
+        const int64_t e = 2 * m - N3;
+        s1 += c * e;
+        s2 += c * e * e;
+        lmin = min(lmin, m);
+        lmax = max(lmax, m);
+    }
+    // over the workgroup (two barriers inside)
+    __device__ __forceinline__ void reduce()
+    {
+        __shared__ int64_t sh64[2][16];
+        __shared__ int32_t sh32[2][16];
+        for (int off = 32; off > 0; off >>= 1) {
+            s1 += __shfl_xor(s1, off);
+            s2 += __shfl_xor(s2, off);
+            lmin = min(lmin, __shfl_xor(lmin, off));
+            lmax = max(lmax, __shfl_xor(lmax, off));
+        }
+        const int wave = threadIdx.x >> 6, nw = ((int)blockDim.x + 63) >> 6;
+        if ((threadIdx.x & 63) == 0) {
+            sh64[0][wave] = s1;
+            sh64[1][wave] = s2;
+            sh32[0][wave] = lmin;
+            sh32[1][wave] = lmax;
+        }
+        __syncthreads();
+        s1 = sh64[0][0];
+        s2 = sh64[1][0];
+        lmin = sh32[0][0];
+        lmax = sh32[1][0];
+        for (int i = 1; i < nw; ++i) {
+            s1 += sh64[0][i];
+            s2 += sh64[1][i];
+            lmin = min(lmin, sh32[0][i]);
+            lmax = max(lmax, sh32[1][i]);
+        }
+        __syncthreads();
+    }
+};
+
+// S from the levels of up to 32 rows a thread (lev[i] of row 1024 i + t, -1:
+// none), 2048 levels at a time (an aligned subtree of the tree).
+__device__ double normaliser_direct(const int (&lev)[32], int groups, int lmin, int nl, const double *pw, double *a)
 {
+    uint32_t *h = reinterpret_cast<uint32_t *>(a + 3072);
+    double *roots = a + 2048;
+    int P = 1;
+    while (P < nl) P <<= 1;
+    const int nchunks = P > 2048 ? P / 2048 : 1;
+    const int lane = threadIdx.x & 63;
+    double S = 0.0;
+    for (int c = 0; c < nchunks; ++c) {
+        for (int i = threadIdx.x; i < 2048; i += 1024) h[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if (g >= groups) break;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t i = (uint32_t)(lev[8 * g + u] - lmin - 2048 * c);
+                bool on = lev[8 * g + u] >= 0 && i < 2048u;
+                // the first lane's level in one count: a cold population has
+                // hardly another
+                const uint64_t m = __ballot(on);
+                if (m == 0ull) continue;
+                const int lead = __builtin_ctzll(m);
+                const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)i, lead);
+                const uint64_t same = __ballot(on && i == li);
+                if (lane == lead)
+                    atomicAdd(&h[li], (uint32_t)__builtin_popcountll(same));
+                else if (on && i != li)
+                    atomicAdd(&h[i], 1u);
+            }
+        }
+        __syncthreads();
+        S = tree_sum<1024>(
+            nchunks > 1 ? 2048 : P,
+            [&](int m) {
+                const int l = 2048 * c + m;
+                return l < nl ? (double)h[m] * level_weight(pw, (uint32_t)l) : 0.0;
+            },
+            a, a + 1024);
+        if (nchunks > 1) {
+            if (threadIdx.x == 0) roots[c] = S;
+            __syncthreads();
+        }
+    }
+    return nchunks > 1 ? lds_pairwise(roots, nchunks) : S;
+}
+
+__device__ Levels measure_levels(const Inst &I, int k, int buf, bool writer, double *pw, double *a)
+{
+    const bool resample = k < I.nT - 1;
+    // loaded before the pass over the energies so that its latency overlaps it
+    const double rho_k = resample ? I.rho[k] : 1.0;
+    const int N3 = 3 * I.N, nlev = I.nlev, copies = I.hist_copies, Rk = (int)I.Rk[k];
+    const bool direct = copies == 0;
+    LevelSums s{0, 0, 0x7FFFFFFF, -1};
+    int lev[32];
+    const int groups = (Rk + 8191) / 8192;
+    if (threadIdx.x == 0) {
+        pw[0] = rho_k;
+        for (int b = 1; b < 40; ++b) pw[b] = pw[b - 1] * pw[b - 1];
+    }
+    // loads eight at a time before any is used: the pass waits for about one
+    // memory latency per eight of a thread
+    if (direct) {
+        const int32_t *E = I.E[buf];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if (g < groups) {
+                int e[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int r = (8 * g + u) * 1024 + (int)threadIdx.x;
+                    e[u] = r < Rk ? E[r] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int r = (8 * g + u) * 1024 + (int)threadIdx.x;
+                    lev[8 * g + u] = r < Rk ? (e[u] + N3) >> 1 : -1;
+                    if (r < Rk) s.add(lev[8 * g + u], 1, N3);
+                }
+            }
+        }
+    } else {
+        for (int base = threadIdx.x; base < nlev; base += 8 * 1024) {
+            uint32_t c[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+            for (int p = 0; p < copies; ++p) {
+                const uint32_t *hp = hist_copy(I, p);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int m = base + u * 1024;
+                    c[u] += m < nlev ? hp[m] : 0u;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c[u]) s.add(base + u * 1024, (int64_t)c[u], N3);
+        }
+    }
+    s.reduce();
+    double S = __builtin_nan("");
+    if (resample) {
+        const int lmin = s.lmin, nl = s.lmax - s.lmin + 1;
+        if (direct) {
+            S = normaliser_direct(lev, groups, lmin, nl, pw, a);
+        } else {
+            int P = 1;
+            while (P < nl) P <<= 1;
+            S = tree_sum<1024>(
+                P,
+                [&](int m) {
+                    if (m >= nl) return 0.0;
+                    uint32_t h = 0;
+                    for (int p = 0; p < copies; ++p) h += hist_copy(I, p)[lmin + m];
+                    return (double)h * level_weight(pw, (uint32_t)m);
+                },
+                a, a + 1024);
+        }
+    }
+    if (writer && threadIdx.x == 0) {
+        StepRec *rec = I.rec + k;
+        rec->R = Rk;
+        rec->sumE = s.s1;
+        rec->sumE2 = (uint64_t)s.s2;
+        rec->sumE2_hi = 0;
+        rec->Emin = 2 * s.lmin - N3;
+        rec->Emax = 2 * s.lmax - N3;
+        rec->S = S;
+    }
+    __syncthreads();
+    return Levels{s.lmin, S};
+}
+
+// Where the offsets of the resampled rows go: the energy buffer that the next
+// sweep will fill (real couplings: memory of their own).
+__device__ __forceinline__ uint32_t *row_offsets(const Inst &I, int idle)
+{
+    return I.real ? I.loff : reinterpret_cast<uint32_t *>(I.E[idle]);
+}
+
+// Copy counts of rows [row0, row0 + 1024) and their offsets in the block:
+// tau = R' w / S, floor(tau) copies and one more when the row's draw is below
+// floor(frac(tau) 2^32).
+__device__ void copies_role(const Inst &I, int k, uint32_t row0, uint32_t *sh, double *pw, double *a)
+{
+    const int buf = swept_buffer(I);
     const int Rk = (int)I.Rk[k];
     const int r = (int)row0 + (int)threadIdx.x;
+    const bool resample = k < I.nT - 1;
+    Levels lv{0, 0.0};
+    // (issued before the measurement, whose latency covers it)
+    const int E = !I.real && resample && r < Rk ? I.E[buf][r] : 0;
+    if (!I.real && (resample || row0 == 0)) lv = measure_levels(I, k, buf, row0 == 0, pw, a);
+    if (!resample) return;
     uint32_t n = 0;
     if (r < Rk) {
         const uint32_t u = philox10(make_uint4(0u, (uint32_t)r, (uint32_t)k, kTagResample), I.key0, I.key1).x;
+        double w, S;
         if (I.real) {
             // per-replica weight from the weights launch
-            const double tau = (I.Rt[k + 1] * I.wrep[r]) / I.rec[k].S;
-            const double fl = __builtin_floor(tau);
-            n = (uint32_t)fl + (u < (uint32_t)__builtin_floor((tau - fl) * 4294967296.0) ? 1u : 0u);
+            w = I.wrep[r];
+            S = I.rec[k].S;
         } else {
-            const int m = (int)((I.E[*I.cur][r] - I.rec[k].Emin) >> 1);
-            const uint2 bf = I.BF[m];
-            n = bf.x + (u < bf.y ? 1u : 0u);
+            w = level_weight(pw, (uint32_t)(((E + 3 * I.N) >> 1) - lv.lmin));
+            S = lv.S;
         }
+        const double tau = (I.Rt[k + 1] * w) / S;
+        const double fl = __builtin_floor(tau);
+        n = (uint32_t)fl + (u < (uint32_t)__builtin_floor((tau - fl) * 4294967296.0) ? 1u : 0u);
     }
     uint32_t total;
     const uint32_t off = block_exscan(n, sh, &total);
-    if (r < I.Rcap) I.loff[r] = off;
+    if (r < I.Rcap) row_offsets(I, buf ^ 1)[r] = off;
     if (threadIdx.x == 0) I.bsum[row0 / kRowsPerBlock] = total;
 }
 
@@ -174,7 +391,7 @@ __device__ void overlap_role(const Inst &I, int k, uint32_t p0, uint32_t *qh)
         for (int i = threadIdx.x; i < nb; i += blockDim.x) qh[i] = 0u;
         __syncthreads();
     }
-    const uint8_t *sp = I.spins[*I.cur];
+    const uint8_t *sp = I.spins[swept_buffer(I)];
     // 16-byte words of a stored row: bytes 0/1, or bits (both count the
     // differing sites as the popcount of the XOR)
     const int words = I.srow_bytes >> 4;
@@ -239,17 +456,22 @@ __device__ void post_finish(const Inst &I, int k, uint32_t *sh, double *a)
             if (!ok) {
                 I.status[1] = (uint32_t)k;
                 I.status[0] |= carry == 0 ? 2u : 1u;
-            } else {
-                *I.mapped = 1;
             }
         }
     }
-    if (threadIdx.x == 0 && ok) *I.k = k + 1;
+    if (threadIdx.x == 0) {
+        // the population of step k lies where its sweeps left it; rows of the
+        // next step live there through the copy map
+        *I.cur = swept_buffer(I);
+        *I.mapped = ok && k < I.nT - 1 ? 1 : 0;
+        if (ok) *I.k = k + 1;
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_post(const Inst *insts, const Work *work)
 {
     __shared__ uint32_t sh[17];
+    __shared__ double pw[40];
     // pairwise-tree scratch, or the LDS overlap histogram
     __shared__ double a[kOvlLdsBins / 2 + 1];
     const Work w = work[blockIdx.x];
@@ -257,15 +479,7 @@ __global__ __launch_bounds__(1024) void k_post(const Inst *insts, const Work *wo
     const int k = *I.k;
     if (!inst_live(I, k)) return;
     if (w.role == kRoleCopies) {
-        // the step's energy histogram (+-1 couplings) has been measured:
-        // the nblk copies workgroups clear it for the next sweep, a slice
-        // each, off the measurement's serial path
-        if (!I.real) {
-            const int per = (I.nlev + I.nblk - 1) / I.nblk;
-            const int m0 = (int)(w.row0 / kRowsPerBlock) * per, m1 = min(I.nlev, m0 + per);
-            for (int m = m0 + (int)threadIdx.x; m < m1; m += blockDim.x) I.hist[m] = 0u;
-        }
-        if (k < I.nT - 1) copies_role(I, k, w.row0, sh);
+        copies_role(I, k, w.row0, sh, pw, a);
     } else if (w.role == kRoleFamilies) {
         families_role(I, k, w.row0, a);
     } else {
@@ -288,12 +502,26 @@ __global__ __launch_bounds__(1024) void k_expand(const Inst *insts, const Work *
     if (!inst_live(I, k) || k == 0 || !*I.mapped) return;
     const int Rold = (int)I.Rk[k - 1];
     const int row0 = (int)w.row0;
+    if (!I.real && I.hist_copies > 0) {
+        // every copies workgroup has measured the step: the nblk workgroups
+        // clear its energy histogram for the next sweep, a slice each
+        const int slice = (int)((int64_t)I.hist_copies * I.nlev + I.nblk - 1) / I.nblk;
+        const int first = (row0 / kRowsPerBlock) * slice, last = min(I.hist_copies * I.nlev, first + slice);
+        for (int i = first + (int)threadIdx.x; i < last; i += blockDim.x) {
+            if (i < I.nlev)
+                I.hist[i] = 0u;
+            else
+                I.loff[i - I.nlev] = 0u;
+        }
+    }
     if (row0 >= Rold) return;
     const int nrow = min(kRowsPerBlock, Rold - row0);
     const uint32_t total = I.bsum[row0 / kRowsPerBlock];
     const uint32_t base = I.boff[row0 / kRowsPerBlock];
     if (total == 0u) return;
-    for (int t = threadIdx.x; t < nrow; t += blockDim.x) off[t] = I.loff[row0 + t];
+    // (the step has moved on: cur is the buffer of the rows being copied)
+    const uint32_t *loff = row_offsets(I, *I.cur ^ 1);
+    for (int t = threadIdx.x; t < nrow; t += blockDim.x) off[t] = loff[row0 + t];
     __syncthreads();
     const uint32_t lim = (uint32_t)I.Rcap - min(base, (uint32_t)I.Rcap);
     const uint32_t end = min(total, lim);

@@ -48,13 +48,10 @@ static int colour_of(int L, int x, int y, int z)
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// L = 8, 16: even/odd-x rows (SWAR words aligned to rows).  Otherwise the
-// colour-major layout when its largest colour fits a workgroup of 1024
-// threads, the slot offsets fit 16 bits and a replica quad's slot fits the
-// workgroup's LDS (even L up to 20, odd L up to 21); else lexicographic.
-// Real couplings: the colour-major layout wherever it fits (a quad slot of
-// four planes), L = 8 and 16 included; no kernel beyond it.  The square
-// lattice (dim = 2) runs only with real couplings, in the same layout.
+// Colour-major rows for every lattice.  Real couplings need a replica quad's
+// slot of four byte planes in the workgroup's LDS and its largest colour in
+// 1024 threads (even L up to 20, odd L up to 21); no kernel beyond it.  The
+// square lattice (dim = 2) runs only with real couplings.
 LayoutInfo layout_for(int L, bool real, int dim)
 {
     LayoutInfo li{};
@@ -66,70 +63,31 @@ LayoutInfo layout_for(int L, bool real, int dim)
             for (int x = 0; x < L; ++x) li.ncs[colour_of(L, x, y, z)]++;
     li.gmax = 1;
     for (int c = 0; c < 3; ++c) li.gmax = std::max(li.gmax, (li.ncs[c] + 3) / 4);
-    li.row_bytes = (N + 15) & ~15;
-    if (!real && dim != 3) {
-        li.layout = -1;
-        li.variant = -1;
-        return li;
-    }
-    if (!real && (L == 8 || L == 16)) {
-        li.layout = kLayoutEO;
-        li.variant = L == 8 ? kSweepEO8 : kSweepEO16;
-        return li;
-    }
     int cb = 0;
     for (int c = 0; c < li.ncol; ++c) {
         li.cbase[c] = cb;
         cb += (li.ncs[c] + 3) & ~3;
     }
-    const int rb = (cb + 15) & ~15;
+    li.row_bytes = (cb + 15) & ~15;
     // threads per replica quad: one per Philox block of the largest colour;
     // up to 64 blocks rounded up to a power of two, so that whole quads fit
     // in a wave and sync with wave barriers
-    int tpr = 1;
+    li.tpr = 1;
     if (li.gmax <= 64) {
-        while (tpr < li.gmax) tpr <<= 1;
+        while (li.tpr < li.gmax) li.tpr <<= 1;
     } else {
-        tpr = li.gmax;
+        li.tpr = li.gmax;
     }
-    if (real) {
-        if (tpr <= 1024 && 2 * rb <= 65535 &&
-            (size_t)cm_slot_bytes(rb, tpr, 4) * cm_replicas_per_block(tpr) + 32 + 8 * 64 <= kMaxSweepLds) {
-            li.layout = kLayoutCM;
-            li.variant = dim == 2 ? (li.ncol == 2 ? kSweepSQ2 : kSweepSQ3) : (li.ncol == 2 ? kSweepCQ2 : kSweepCQ3);
-            li.row_bytes = rb;
-            li.tpr = tpr;
-        } else {
-            li.layout = -1;
-            li.variant = -1;
-        }
-        return li;
+    li.valid = true;
+    if (!real) {
+        li.valid = dim == 3;
+        li.variant = kSweepRB;
+    } else if (li.tpr <= 1024 && 2 * li.row_bytes <= 65535 &&
+               (size_t)cm_slot_bytes(li.row_bytes, li.tpr, 4) * cm_replicas_per_block(li.tpr) + 32 + 8 * 64 <= kMaxSweepLds) {
+        li.variant = dim == 2 ? (li.ncol == 2 ? kSweepSQ2 : kSweepSQ3) : (li.ncol == 2 ? kSweepCQ2 : kSweepCQ3);
+    } else {
+        li.valid = false;
     }
-    // The neighbour table in LDS instead of registers: three colours always
-    // (136 VGPRs without spills against 168 with 38 spilled: 10-20% faster
-    // at L = 5 ... 13), two colours with quads of at most 128 threads
-    // (L <= 10: four waves per SIMD instead of three, 7-12% faster; above,
-    // the extra table reads and adds cost what the occupancy gains).  The
-    // table holds 16-bit slot offsets, so the slot must stay within 64 KB,
-    // and slot and table must fit the workgroup's LDS; otherwise the
-    // register form.
-    auto fits = [&](int v) {
-        const size_t tab = (size_t)cm_table_bytes(v, tpr);
-        return (size_t)cm_slot_bytes(rb, tpr, 8) * cm_replicas_per_block(tpr) + 32 + 4 * 64 + tab <= kMaxSweepLds &&
-               (tab == 0 || 8 * (size_t)cm_plane_bytes(rb) <= 65536);
-    };
-    const int tab_form = li.ncol == 2 ? (tpr <= 128 ? kSweepCM2T : -1) : kSweepCM3T;
-    const int reg_form = li.ncol == 2 ? kSweepCM2 : kSweepCM3;
-    const int cmv = tab_form >= 0 && fits(tab_form) ? tab_form : fits(reg_form) ? reg_form : -1;
-    if (tpr <= 1024 && 2 * rb <= 65535 && cmv >= 0) {
-        li.layout = kLayoutCM;
-        li.variant = cmv;
-        li.row_bytes = rb;
-        li.tpr = tpr;
-        return li;
-    }
-    li.layout = kLayoutLex;
-    li.variant = kSweepLex;
     return li;
 }
 
@@ -145,8 +103,8 @@ struct Carve {
 };
 
 struct InstLayout {
-    size_t ctl, status, sync, spins0, spins1, E0, E1, f0, f1, map, loff, bsum, boff, hist, BF, cnt, fpart, thr,
-        beta, rho, Rt, site, grp, jeo, J, pos, lexof, cmdesc, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emom, cmj,
+    size_t ctl, status, sync, spins0, spins1, E0, E1, f0, f1, map, loff, bsum, boff, hist, cnt, fpart, thr,
+        beta, rho, Rt, rbtab, J, pos, lexof, cmdesc, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emom, cmj,
         bq, gpw, total;
 };
 
@@ -177,20 +135,17 @@ InstLayout layout_of(int L, int64_t R, int64_t Rcap, int nT, int n_ovl, bool pac
     l.bsum = c.take((size_t)nblk * 4);
     l.boff = c.take((size_t)nblk * 4);
     l.hist = c.take((size_t)nlev * 4);
-    l.BF = c.take((size_t)nlev * 8);
     l.cnt = c.take((size_t)R * 4);
     l.fpart = c.take((size_t)std::max<int64_t>(1, fp2 / 2048) * 8);
     l.thr = c.take((size_t)nT * 16);
     l.beta = c.take((size_t)nT * 8);
     l.rho = c.take((size_t)nT * 8);
     l.Rt = c.take((size_t)nT * 8);
-    l.site = c.take((size_t)N * 16);
-    l.grp = c.take((size_t)ncol * gmax * 4 * 2);
-    l.jeo = c.take((size_t)2 * (N / 8 + 1) * 6 * 4);
+    l.rbtab = c.take(real ? 16 : (size_t)ncol * gmax * 64);
     l.J = c.take((size_t)dim * N * (real ? 4 : 1));
     l.pos = c.take((size_t)N * 2);
     l.lexof = c.take((size_t)li.row_bytes * 2);
-    l.cmdesc = li.layout == kLayoutCM ? c.take((size_t)ncol * gmax * 32 * 2) : c.take(16);
+    l.cmdesc = c.take(real ? (size_t)ncol * gmax * 32 * 2 : 16);
     l.Rk = c.take((size_t)(nT + 1) * 4);
     l.rec = c.take((size_t)nT * sizeof(StepRec));
     l.ovl_slot = c.take((size_t)nT * 4);
@@ -481,7 +436,6 @@ int Runner::upload_inst(int i)
     d.N = N;
     d.dim = h.dim;
     d.ncol = h.ncol;
-    d.layout = h.layout;
     d.row_bytes = h.row_bytes;
     d.packed = h.packed;
     d.srow_bytes = h.srow_bytes;
@@ -508,7 +462,11 @@ int Runner::upload_inst(int i)
     d.bsum = (uint32_t *)(b + lay.bsum);
     d.boff = (uint32_t *)(b + lay.boff);
     d.hist = (uint32_t *)(b + lay.hist);
-    d.BF = (uint2 *)(b + lay.BF);
+    // more histogram parts where the rows make hundreds of updates, as far as
+    // loff holds them and the measurement (1024 threads) reads them in a few
+    // microseconds
+    d.hist_copies =
+        h.real || h.Rcap <= kDirectRows ? 0 : (int32_t)(1 + std::min({(int64_t)63, h.Rcap / d.nlev, (int64_t)32768 / d.nlev, h.Rcap / 512}));
     d.cnt = (uint32_t *)(b + lay.cnt);
     d.fpart = (double *)(b + lay.fpart);
     d.thr = (const uint4 *)(b + lay.thr);
@@ -516,9 +474,8 @@ int Runner::upload_inst(int i)
     d.rho = (const double *)(b + lay.rho);
     d.Rt = (const double *)(b + lay.Rt);
     d.nlnn = d_nlnn_;
-    d.site = (const uint4 *)(b + lay.site);
-    d.grp = (const uint16_t *)(b + lay.grp);
-    d.jeo = (const uint32_t *)(b + lay.jeo);
+    d.rbtab = (const uint4 *)(b + lay.rbtab);
+    d.rb_plane = rb_plane(h.row_bytes);
     d.pos = (const uint16_t *)(b + lay.pos);
     d.lexof = (const uint16_t *)(b + lay.lexof);
     d.cmdesc = (const uint16_t *)(b + lay.cmdesc);
@@ -602,110 +559,72 @@ int Runner::upload_inst(int i)
     h.lex_pos.resize(N);
     std::vector<uint16_t> pos16((size_t)N);
     for (int s = 0; s < N; ++s) {
-        const int x = s % L, yz = s / L;
-        if (h.layout == kLayoutLex)
-            h.lex_pos[s] = s;
-        else if (h.layout == kLayoutEO)
-            h.lex_pos[s] = col[s] * (N / 2) + yz * (L / 2) + (x >> 1);
-        else
-            h.lex_pos[s] = li.cbase[col[s]] + rank[s];
+        h.lex_pos[s] = li.cbase[col[s]] + rank[s];
         pos16[s] = (uint16_t)h.lex_pos[s];
     }
     // its inverse over the storage positions of a row (cluster moves read
     // rows in storage order)
     std::vector<uint16_t> lexof16((size_t)h.row_bytes, (uint16_t)0xFFFF);
     for (int s = 0; s < N; ++s) lexof16[(size_t)h.lex_pos[s]] = (uint16_t)s;
+    // per colour, Philox block and site: its six neighbours and couplings.
+    // On the square lattice the two z entries of a site point at the site
+    // itself with coupling 0: they add nothing to its field or to the
+    // energy, so the sweep kernel runs unchanged.  Padding sites point at
+    // themselves.
     std::vector<uint16_t> cmdesc;
     std::vector<int32_t> cmj;
-    std::vector<uint32_t> site((size_t)N * 4, 0u);
-    std::vector<uint16_t> grp((size_t)h.ncol * d.gmax * 4, (uint16_t)0xFFFF);
-    std::vector<uint32_t> jeo((size_t)2 * (N / 8 + 1) * 6, 0u);
-    if (h.layout == kLayoutLex) {
-        for (int z = 0; z < L; ++z)
-            for (int y = 0; y < L; ++y)
-                for (int x = 0; x < L; ++x) {
-                    const int s = site_of(x, y, z);
-                    const int nb[6] = {site_of(x + 1, y, z), site_of(x - 1, y, z), site_of(x, y + 1, z),
-                                       site_of(x, y - 1, z), site_of(x, y, z + 1), site_of(x, y, z - 1)};
-                    // couplings of the six bonds; the bond to s - e_d is
-                    // stored at the lower site
-                    const int jv[6] = {J(0, s), J(0, nb[1]), J(1, s), J(1, nb[3]), J(2, s), J(2, nb[5])};
-                    uint32_t jm = 0;
-                    for (int q = 0; q < 6; ++q)
-                        if (jv[q] < 0) jm |= 1u << q;
-                    site[4 * s + 0] = (uint32_t)nb[0] | ((uint32_t)nb[1] << 16);
-                    site[4 * s + 1] = (uint32_t)nb[2] | ((uint32_t)nb[3] << 16);
-                    site[4 * s + 2] = (uint32_t)nb[4] | ((uint32_t)nb[5] << 16);
-                    site[4 * s + 3] = jm;
-                    const int c = col[s], r = rank[s];
-                    grp[((size_t)c * d.gmax + (r >> 2)) * 4 + (r & 3)] = (uint16_t)s;
-                }
-    } else if (h.layout == kLayoutCM) {
-        // per colour, Philox block and site: the LDS offsets of its six
-        // neighbours, in the complemented copy (+row_bytes) for a -1 bond;
-        // for real couplings the plain copy, with the couplings alongside.
-        // On the square lattice the two z entries of a site point at the
-        // site itself with coupling 0: they add nothing to its field or to
-        // the energy, so the sweep kernel runs unchanged.
-        std::vector<int> site_at((size_t)3 * N, -1);
-        for (int s = 0; s < N; ++s) site_at[(size_t)col[s] * N + rank[s]] = s;
+    std::vector<uint32_t> rbtab;
+    std::vector<int> site_at((size_t)3 * N, -1);
+    for (int s = 0; s < N; ++s) site_at[(size_t)col[s] * N + rank[s]] = s;
+    if (h.real) {
         cmdesc.assign((size_t)h.ncol * d.gmax * 32, 0);
-        if (h.real) cmj.assign((size_t)h.ncol * d.gmax * 24, 0);
-        for (int c = 0; c < h.ncol; ++c)
-            for (int g = 0; g < d.gcs[c]; ++g) {
-                uint16_t *e = cmdesc.data() + ((size_t)c * d.gmax + g) * 32;
-                uint32_t vmask = 0;
-                for (int bb = 0; bb < 4; ++bb) {
-                    const int i = 4 * g + bb;
-                    if (i >= ncs[c]) {
-                        // padding byte: no site; point at itself (value 0)
-                        for (int dd = 0; dd < 6; ++dd) e[4 * dd + bb] = (uint16_t)(li.cbase[c] + i);
-                        continue;
-                    }
+        cmj.assign((size_t)h.ncol * d.gmax * 24, 0);
+    } else {
+        rbtab.assign((size_t)h.ncol * d.gmax * 16, 0u);
+    }
+    const bool sq = h.dim == 2;
+    for (int c = 0; c < h.ncol; ++c)
+        for (int g = 0; g < d.gcs[c]; ++g) {
+            const size_t blk = (size_t)c * d.gmax + g;
+            uint32_t vmask = 0;
+            for (int bb = 0; bb < 4; ++bb) {
+                const int i = 4 * g + bb;
+                int nbp[6], jv[6] = {0, 0, 0, 0, 0, 0};
+                if (i >= ncs[c]) {
+                    for (int dd = 0; dd < 6; ++dd) nbp[dd] = li.cbase[c] + i;
+                } else {
                     vmask |= 1u << (8 * bb);
                     const int s = site_at[(size_t)c * N + i];
                     const int x = s % L, y = (s / L) % L, z = s / (L * L);
-                    const bool sq = h.dim == 2;
+                    // the bond to s - e_d is stored at the lower site
                     const int nb[6] = {site_of(x + 1, y, z), site_of(x - 1, y, z), site_of(x, y + 1, z),
                                        site_of(x, y - 1, z), sq ? s : site_of(x, y, z + 1),
                                        sq ? s : site_of(x, y, z - 1)};
-                    const int jv[6] = {J(0, s), J(0, nb[1]), J(1, s), J(1, nb[3]), sq ? 0 : J(2, s),
-                                       sq ? 0 : J(2, nb[5])};
                     for (int dd = 0; dd < 6; ++dd) {
-                        if (h.real) {
-                            e[4 * dd + bb] = (uint16_t)h.lex_pos[nb[dd]];
-                            cmj[((size_t)c * d.gmax + g) * 24 + 4 * dd + bb] = jv[dd];
-                        } else {
-                            e[4 * dd + bb] = (uint16_t)(h.lex_pos[nb[dd]] + (jv[dd] < 0 ? h.row_bytes : 0));
-                        }
+                        nbp[dd] = h.lex_pos[nb[dd]];
+                        jv[dd] = sq && dd >= 4 ? 0 : J(dd >> 1, dd & 1 ? nb[dd] : s);
                     }
                 }
-                e[24] = (uint16_t)(vmask & 0xFFFFu);
-                e[25] = (uint16_t)(vmask >> 16);
-            }
-    } else {
-        const int H = L / 2, GPR = L / 8, G = N / 8;
-        for (int c = 0; c < 2; ++c)
-            for (int g = 0; g < G; ++g) {
-                const int row = g / GPR, jb = g % GPR;
-                const int y = row % L, z = row / L;
-                const int p = (c + y + z) & 1;
-                uint32_t w[6] = {0, 0, 0, 0, 0, 0};
-                for (int bb = 0; bb < 4; ++bb) {
-                    const int x = 2 * (4 * jb + bb) + p;
-                    const int s = site_of(x, y, z);
-                    const int xm = site_of(x - 1, y, z), ym = site_of(x, y - 1, z), zm = site_of(x, y, z - 1);
-                    // aligned x neighbour: x+1 for p = 0, x-1 for p = 1
-                    const int ja = p == 0 ? J(0, s) : J(0, xm);
-                    const int js = p == 0 ? J(0, xm) : J(0, s);
-                    const int jv[6] = {ja, js, J(1, s), J(1, ym), J(2, s), J(2, zm)};
-                    for (int q = 0; q < 6; ++q)
-                        if (jv[q] < 0) w[q] |= 1u << (8 * bb);
+                for (int dd = 0; dd < 6; ++dd) {
+                    const int e = 4 * dd + bb;
+                    if (h.real) {
+                        cmdesc[blk * 32 + e] = (uint16_t)nbp[dd];
+                        cmj[blk * 24 + e] = jv[dd];
+                    } else {
+                        const uint32_t word = (uint32_t)((nbp[dd] & 3) * d.rb_plane + (nbp[dd] >> 2));
+                        rbtab[blk * 16 + (e >> 1)] |= word << (16 * (e & 1));
+                        if (jv[dd] < 0) rbtab[blk * 16 + 12] |= 1u << e;
+                    }
                 }
-                for (int q = 0; q < 6; ++q) jeo[((size_t)c * G + g) * 6 + q] = w[q];
-                (void)H;
             }
-    }
+            if (h.real) {
+                cmdesc[blk * 32 + 24] = (uint16_t)(vmask & 0xFFFFu);
+                cmdesc[blk * 32 + 25] = (uint16_t)(vmask >> 16);
+            } else {
+                for (int bb = 0; bb < 4; ++bb)
+                    if ((vmask >> (8 * bb)) & 1u) rbtab[blk * 16 + 13] |= 1u << bb;
+            }
+        }
     // real couplings: beta_k 2^-20 in binary32 and the weight factors
     // exp(-(beta_{k+1} - beta_k) 2^(b-20)), b < 40, host libm
     std::vector<float> bq((size_t)h.nT);
@@ -733,9 +652,7 @@ int Runner::upload_inst(int i)
     put(lay.beta, h.beta.data(), h.beta.size() * 8);
     put(lay.rho, rho.data(), rho.size() * 8);
     put(lay.Rt, h.pop.data(), h.pop.size() * 8);
-    put(lay.site, site.data(), site.size() * 4);
-    put(lay.grp, grp.data(), grp.size() * 2);
-    put(lay.jeo, jeo.data(), jeo.size() * 4);
+    if (!rbtab.empty()) put(lay.rbtab, rbtab.data(), rbtab.size() * 4);
     if (h.real)
         put(lay.J, h.Jq.data(), h.Jq.size() * 4);
     else
@@ -766,14 +683,13 @@ std::vector<Work> gather_items(uint32_t slot, int64_t Rcap, int row_bytes)
     return v;
 }
 
-int Runner::set_shape(int i, int tile_rows, int rp)
+int Runner::set_shape(int i, const HostInst &shape)
 {
     if (i < 0 || i >= max_slots_ || !used_[i]) return PAMC_ERR_STATE;
     HostInst &h = inst_[i];
-    h.tile_rows = tile_rows;
-    h.rp = rp;
-    h.dev.tile_rows = tile_rows;
-    h.dev.sweep_tiles = (int32_t)((h.Rcap + tile_rows - 1) / tile_rows);
+    take_shape(h, shape);
+    h.dev.tile_rows = h.tile_rows;
+    h.dev.sweep_tiles = (int32_t)((h.Rcap + h.tile_rows - 1) / h.tile_rows);
     HIPCHK(hipStreamSynchronize(stream_), "set_shape sync");
     HIPCHK(hipMemcpy(d_insts_ + i, &h.dev, sizeof(Inst), hipMemcpyHostToDevice), "update instance shape");
     return build_work(active_);
@@ -802,7 +718,10 @@ int Runner::build_work(const std::vector<int> &active)
         if (h2d(p, src, bytes) != PAMC_OK) return nullptr;
         return p;
     };
-    std::map<std::tuple<int, int, int, int, int, int, int>, std::vector<Work>> groups;
+    // by what a launch's instances share: the lattice, the shape, and
+    // whether the launch is split around cluster moves
+    std::map<std::tuple<int, int, int, int, int, int, int, int, int>, std::vector<Work>> groups;
+    std::map<std::tuple<int, int, int, int, int, int, int, int, int>, SweepShape> shapes;
     std::vector<Work> rows, post, gath, wblk, icm;
     icm_rounds_ = 0;
     icm_N_ = 0;
@@ -810,7 +729,19 @@ int Runner::build_work(const std::vector<int> &active)
     for (int i : active) {
         const HostInst &h = inst_[i];
         const uint32_t ii = (uint32_t)i;
-        auto &g = groups[std::make_tuple(h.variant, h.L, h.tile_rows, h.row_bytes, h.tpr, h.rp, h.icm > 0 ? 1 : 0)];
+        const auto key = std::make_tuple(h.icm > 0 ? 1 : 0, h.variant, h.L, h.tile_rows, h.row_bytes, h.tpr, h.rp, h.mrep,
+                                         h.sets);
+        auto &g = groups[key];
+        SweepShape &sh = shapes[key];
+        sh.variant = h.variant;
+        sh.tile_rows = h.tile_rows;
+        sh.row_bytes = h.row_bytes;
+        sh.tpr = h.tpr;
+        sh.rp = h.rp;
+        sh.G = h.dev.gmax;
+        sh.plane = h.dev.rb_plane;
+        sh.M = h.mrep;
+        sh.sets = h.sets;
         if (h.icm > 0) {
             for (int64_t j = 0; j < h.Rcap / 2; ++j) icm.push_back(Work{ii, (uint32_t)j, 0u, 0u});
             icm_rounds_ = std::max(icm_rounds_, h.icm);
@@ -831,12 +762,8 @@ int Runner::build_work(const std::vector<int> &active)
     }
     for (auto &kv : groups) {
         SweepGroup sg;
-        sg.variant = std::get<0>(kv.first);
-        sg.tile_rows = std::get<2>(kv.first);
-        sg.row_bytes = std::get<3>(kv.first);
-        sg.tpr = std::get<4>(kv.first);
-        sg.rp = std::get<5>(kv.first);
-        sg.icm = std::get<6>(kv.first);
+        sg.shape = shapes[kv.first];
+        sg.icm = std::get<0>(kv.first);
         sg.nwork = (int)kv.second.size();
         sg.work = (Work *)upload(kv.second.data(), kv.second.size() * sizeof(Work));
         if (!sg.work) return dev_fail(hipErrorOutOfMemory, "upload sweep work");
@@ -917,18 +844,18 @@ int Runner::launch_step_kernels()
     const int ns = std::min((int)aux_.size(), (int)plain.size() - 1);
     if (ns <= 0) {
         for (const SweepGroup *g : plain)
-            launch_sweep(g->variant, d_insts_, g->work, g->nwork, g->tile_rows, g->row_bytes, g->tpr, g->rp, 0, stream_);
+            launch_sweep(g->shape, d_insts_, g->work, g->nwork, 0, stream_);
     } else {
         std::stable_sort(plain.begin(), plain.end(), [](const SweepGroup *a, const SweepGroup *b) {
-            return (double)a->nwork * a->tile_rows * a->row_bytes > (double)b->nwork * b->tile_rows * b->row_bytes;
+            return (double)a->nwork * a->shape.tile_rows * a->shape.row_bytes >
+                   (double)b->nwork * b->shape.tile_rows * b->shape.row_bytes;
         });
         HIPCHK(hipEventRecord(ev_fork_, stream_), "hipEventRecord (fork)");
         for (int a = 0; a < ns; ++a) HIPCHK(hipStreamWaitEvent(aux_[a], ev_fork_, 0), "hipStreamWaitEvent (fork)");
         for (size_t j = 0; j < plain.size(); ++j) {
             const int lane = (int)(j % (size_t)(ns + 1));
             const SweepGroup *g = plain[j];
-            launch_sweep(g->variant, d_insts_, g->work, g->nwork, g->tile_rows, g->row_bytes, g->tpr, g->rp, 0,
-                         lane == 0 ? stream_ : aux_[lane - 1]);
+            launch_sweep(g->shape, d_insts_, g->work, g->nwork, 0, lane == 0 ? stream_ : aux_[lane - 1]);
         }
         for (int a = 0; a < ns; ++a) {
             HIPCHK(hipEventRecord(ev_join_[a], aux_[a]), "hipEventRecord (join)");
@@ -939,11 +866,11 @@ int Runner::launch_step_kernels()
     if (nicm_) {
         for (auto &g : sweep_groups_)
             if (g.icm)
-                launch_sweep(g.variant, d_insts_, g.work, g.nwork, g.tile_rows, g.row_bytes, g.tpr, g.rp, 1, stream_);
+                launch_sweep(g.shape, d_insts_, g.work, g.nwork, 1, stream_);
         for (int rd = 0; rd < icm_rounds_; ++rd) launch_icm(d_insts_, d_icm_, nicm_, icm_N_, rd, stream_);
         for (auto &g : sweep_groups_)
             if (g.icm)
-                launch_sweep(g.variant, d_insts_, g.work, g.nwork, g.tile_rows, g.row_bytes, g.tpr, g.rp, 2, stream_);
+                launch_sweep(g.shape, d_insts_, g.work, g.nwork, 2, stream_);
     }
     if (timing_) HIPCHK(hipEventRecord(ev_pool_[ev_used_ - 3], stream_), "hipEventRecord");
     launch_weights(d_insts_, d_wblk_, nwblk_, stream_);
@@ -1344,6 +1271,10 @@ int Runner::set_state(int i, const pamc_state *st)
     HIPCHK(hipMemcpy(h.ctl, ctl, 12, hipMemcpyHostToDevice), "write ctl");
     HIPCHK(hipMemcpy(h.dev.status, status, 8, hipMemcpyHostToDevice), "write status");
     HIPCHK(hipMemcpy(h.dev.Rk + st->step, &Rk, 4, hipMemcpyHostToDevice), "write Rk");
+    // parts of the energy histogram, which a step that failed in its
+    // resampling or the last step left behind
+    HIPCHK(hipMemset(h.dev.hist, 0, (size_t)h.dev.nlev * 4), "clear the histogram");
+    HIPCHK(hipMemset(h.dev.loff, 0, (size_t)h.Rcap * 4), "clear the histogram");
     // energies from the spins (Eq. (1)) for the imported rows
     std::vector<Work> rows;
     for (int64_t r = 0; r < R; r += kRowsPerBlock) rows.push_back(Work{(uint32_t)i, (uint32_t)r, 0u, 0u});

@@ -21,15 +21,16 @@ namespace pamc {
 
 struct HostInst {
     int dim = 3;                       // lattice dimension (2 or 3), N = L^dim
-    int L = 0, N = 0, ncol = 0, layout = 0, variant = 0;
+    int L = 0, N = 0, ncol = 0, variant = 0;
     int row_bytes = 0, tile_rows = 0;
     int packed = 0;                    // spins stored one bit per position
     int real = 0;                      // real couplings in fixed point (Jq)
     int icm = 0;                       // cluster-move rounds per step
     double icm_bmin = 0.0;             // ... at steps with beta_k >= icm_bmin
     int srow_bytes = 0;                // bytes per stored spin row
-    int tpr = 0;                       // colour-major sweep: threads per replica
-    int rp = 0;                        // colour-major sweep: replica quads per workgroup
+    int tpr = 0;                       // real couplings: threads per replica quad
+    int rp = 0;                        // replica quads a sweep workgroup holds at once
+    int mrep = 0, sets = 0;            // +-1 couplings: replicas per word, sets of them per pass of a workgroup
     int64_t R = 0, Rcap = 0;
     int nT = 0, NS = 0;
     uint64_t seed = 0;
@@ -52,6 +53,15 @@ struct HostInst {
     bool poisoned = false;
 };
 
+// Takes over another description's sweep workgroup shape.
+inline void take_shape(HostInst &h, const HostInst &from)
+{
+    h.tile_rows = from.tile_rows;
+    h.rp = from.rp;
+    h.mrep = from.mrep;
+    h.sets = from.sets;
+}
+
 struct Allocator {
     void *(*alloc)(size_t, void *) = nullptr;
     void (*free)(void *, void *) = nullptr;
@@ -66,17 +76,16 @@ size_t inst_device_bytes(int L, int64_t Rcap, int nT, int n_ovl, bool packed, bo
 // to 16 bytes.
 int stored_row_bytes(int row_bytes, bool packed);
 int64_t default_capacity(int64_t R);
-// Storage layout for lattice size L, and the shape it implies.
+// Row layout for lattice size L, and the kernel that sweeps it.
 struct LayoutInfo {
-    int layout, variant, ncol;  // layout < 0: no kernel for this lattice
+    bool valid;       // a kernel covers this lattice
+    int variant, ncol;
     int ncs[3];       // sites per colour
-    int cbase[3];     // colour-major: first byte of each colour
+    int cbase[3];     // first storage position of each colour
     int row_bytes;    // bytes per replica row (multiple of 16)
     int gmax;         // Philox blocks of the largest colour
-    int tpr;          // colour-major: threads per replica
+    int tpr;          // threads per replica quad (real couplings)
 };
-// Real couplings use the colour-major layout for every L it covers (L = 8
-// and 16 included).
 LayoutInfo layout_for(int L, bool real = false, int dim = 3);
 
 class Runner {
@@ -111,7 +120,7 @@ public:
     int thresholds(int i, uint32_t *out, uint8_t *acc);
     // Changes the sweep workgroup shape of slot i (between steps; results
     // do not depend on it) and rebuilds the work lists of the active set.
-    int set_shape(int i, int tile_rows, int rp);
+    int set_shape(int i, const HostInst &shape);
     const HostInst &inst(int i) const { return inst_[i]; }
     HostInst &inst(int i) { return inst_[i]; }
     const std::vector<int> &active() const { return active_; }
@@ -174,7 +183,8 @@ private:
 
     // work lists for the current active set
     struct SweepGroup {
-        int variant, tile_rows, row_bytes, tpr, rp, icm;
+        SweepShape shape;
+        int icm;
         Work *work;
         int nwork;
     };

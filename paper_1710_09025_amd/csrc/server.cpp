@@ -33,7 +33,7 @@ namespace pamc {
 int make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const double *beta, int nT, int NS,
               uint64_t seed, const pamc_options &opt, HostInst &h);
 void tune_cache_load();
-bool shape_valid(const HostInst &h, int tile_rows, int rp, const char **why);
+bool shape_valid(const HostInst &h, const char **why);
 int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt);
 }
 
@@ -525,10 +525,7 @@ int pamc_server_submit(pamc_server *s, const pamc_instance *inst, uint64_t *req_
         o.autotune = 1;
         st = pamc::tune_shape(t, o, nullptr);
         if (st != PAMC_OK) return st;
-        if (pamc::shape_valid(r.h, t.tile_rows, t.rp, nullptr)) {
-            r.h.tile_rows = t.tile_rows;
-            r.h.rp = t.rp;
-        }
+        if (pamc::shape_valid(t, nullptr)) pamc::take_shape(r.h, t);
     }
     r.bytes = pamc::inst_device_bytes(inst->L, r.h.Rcap, inst->n_temps, r.h.ovl_n, r.h.packed != 0,
                                       r.h.real != 0) +

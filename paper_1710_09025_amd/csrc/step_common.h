@@ -1,9 +1,7 @@
 // step_common.h -- device routines shared by the sweep and resampling
 // kernels: the Philox4x32-10 generator, block reductions, the fixed pairwise
-// summation tree, counting with one atomic per distinct address of a wave,
-// the end-of-launch detection of the last workgroup of an instance, and the
-// measurement of a temperature step (paper Sec. II.B: reweighting factors
-// exp[-(beta'-beta) E_i] normalised to the nominal population R(beta')).
+// summation tree, the level weights, counting with few atomics per wave and
+// the end-of-launch detection of the last workgroup of an instance.
 #pragma once
 #include "pamc_dev.h"
 
@@ -170,36 +168,63 @@ __device__ __forceinline__ bool real_accept(float bq, int32_t dE, uint32_t u)
     return x >= -23.0f && (e >= 1.0f || u < T);
 }
 
-// Adds one count per valid lane to arr[idx], one atomic per distinct index
-// of the wave: at low temperature most replicas share a few energies (and
-// sorted families share ids), and per-lane atomics on one address would
-// serialise.  Every lane of the wave must call it.
+// Adds one count per valid lane to arr[idx]: at low temperature most replicas
+// share a few energies, and per-lane atomics on one address would serialise,
+// so the first kShared distinct indices found in the wave get one atomic
+// each; at high temperature, where nearly every lane has its own, the rest
+// go out in one instruction, a count per lane (a pass per distinct index
+// took a third of the whole launch at L = 8, beta = 0).  Every lane of the
+// wave must call it.
 __device__ __forceinline__ void count_wave(uint32_t *arr, uint32_t idx, bool valid)
 {
+    constexpr int kShared = 64;
     const int lane = threadIdx.x & 63;
     uint64_t pending = __ballot(valid);
-    while (pending) {
+    for (int i = 0; i < kShared && pending; ++i) {
         const int leader = __builtin_ctzll(pending);
-        const uint32_t li = __shfl(idx, leader);
+        const uint32_t li = __builtin_amdgcn_readlane(idx, leader);
         const uint64_t same = __ballot(valid && idx == li) & pending;
         if (lane == leader) atomicAdd(&arr[li], (uint32_t)__builtin_popcountll(same));
         pending &= ~same;
     }
+    if ((pending >> lane) & 1u) atomicAdd(&arr[idx], 1u);
+}
+
+// The same where equal indices come in runs of consecutive lanes: one count
+// per run, all in one instruction.
+__device__ __forceinline__ void count_runs(uint32_t *arr, uint32_t idx, bool valid)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t left = __shfl_up(idx, 1);
+    const uint64_t on = __ballot(valid);
+    const bool head = valid && (lane == 0 || !((on >> (lane - 1)) & 1u) || left != idx);
+    // a run ends at the next head or the next lane without a row
+    const uint64_t stop = (__ballot(head) | ~on) & ~(((uint64_t)2 << lane) - 1);
+    if (head) atomicAdd(&arr[idx], (uint32_t)((stop ? __builtin_ctzll(stop) : 64) - lane));
 }
 
 // Called by every workgroup of an instance at the end of its work in a
 // launch: returns true in exactly one workgroup, the last to finish, after
-// which the writes of all the others are visible to it.  Each workgroup
-// releases its writes (device scope: an L2 write-back, the L2s of the XCDs
-// not being coherent) before it counts itself in; only the last one
-// acquires (an L2 invalidate).  A full fence in every workgroup would also
-// invalidate the L2 under all the workgroups still running.
+// which the writes of all the others are visible to it.
+//   kStores: the last workgroup reads plain stores of the others.  Each
+// workgroup releases its writes (device scope: an L2 write-back, the L2s of
+// the XCDs not being coherent) before it counts itself in.
+//   else: it reads only what the others changed with device-scope atomics,
+// which are performed at the memory the XCDs share; each wave waits for its
+// own to complete, and no cache is written back (the write-backs of a sweep
+// launch's thousands of workgroups, each with its tile of spins dirty in the
+// L2, took longer than its sweeps at L = 8).
+// Only the last workgroup acquires (an L2 invalidate); a full fence in every
+// workgroup would also invalidate the L2 under all the workgroups still
+// running.
+template <bool kStores = true>
 __device__ __forceinline__ bool last_workgroup(uint32_t *counter, int expected)
 {
     __shared__ int is_last;
+    if constexpr (!kStores) __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if constexpr (kStores) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         is_last = atomicAdd(counter, 1u) == (uint32_t)(expected - 1);
     }
     __syncthreads();
@@ -209,120 +234,16 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *counter, int expected)
     return true;
 }
 
-// Measurement of step k after its sweeps, by one workgroup (blockDim a power
-// of two, <= 1024): E_min, E_max, sum E, sum E^2 from the energy histogram
-// (exact integers), and for k < nT-1 the level weights w[m] = exp(-2 dbeta m)
-// as a fixed product of rho^(2^b), their normaliser S by the pairwise tree
-// over 2^ceil(log2(M+1)) levels, and the table (floor(tau), floor(frac(tau)
-// 2^32)) with tau = R w / S.  Moves the buffer roles on when the sweep wrote
-// the other buffer; the post launch that follows clears the histogram.  NT
-// bounds the workgroup size (scratch capacity); any workgroup of a multiple
-// of 64 threads works.  This runs in one workgroup while the rest of the GPU
-// waits, so every global load it needs is issued as early as possible.
-template <int NT>
-__device__ void measure_step(const Inst &I, int k)
+// Part c of the energy histogram.
+__device__ __forceinline__ uint32_t *hist_copy(const Inst &I, int c)
 {
-    __shared__ int64_t sh64[2][16];
-    __shared__ int32_t sh32[2][16];
-    __shared__ double tree[NT];
-    __shared__ double roots[NT];
-    __shared__ double pw[40];
-    const bool resample = k < I.nT - 1;
-    // loaded before the histogram pass so that their latency overlaps it
-    const double rho_k = resample ? I.rho[k] : 1.0;
-    const double Rd = resample ? I.Rt[k + 1] : 0.0;  // nominal population at beta_{k+1}
-    const uint32_t Rk = I.Rk[k];
-    const int N3 = 3 * I.N, nlev = I.nlev, nt = (int)blockDim.x;
-    int64_t s1 = 0, s2 = 0;
-    int32_t lmin = 0x7FFFFFFF, lmax = -1;
-    // the counts come from memory (the election invalidated the L2): each
-    // thread issues its loads eight at a time before using any of them, so
-    // the pass waits for about one memory latency per eight levels per
-    // thread rather than one per level
-    for (int base = threadIdx.x; base < nlev; base += 8 * nt) {
-        uint32_t c[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int m = base + u * nt;
-            c[u] = m < nlev ? I.hist[m] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (!c[u]) continue;
-            const int m = base + u * nt;
-            const int64_t e = 2 * m - N3;
-            s1 += (int64_t)c[u] * e;
-            s2 += (int64_t)c[u] * e * e;
-            lmin = min(lmin, m);
-            lmax = max(lmax, m);
-        }
-    }
-    // the four reductions in one pass: within each wave, then over the waves
-    for (int off = 32; off > 0; off >>= 1) {
-        s1 += __shfl_xor(s1, off);
-        s2 += __shfl_xor(s2, off);
-        lmin = min(lmin, __shfl_xor(lmin, off));
-        lmax = max(lmax, __shfl_xor(lmax, off));
-    }
-    {
-        const int wave = threadIdx.x >> 6, nw = (nt + 63) >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            sh64[0][wave] = s1;
-            sh64[1][wave] = s2;
-            sh32[0][wave] = lmin;
-            sh32[1][wave] = lmax;
-        }
-        __syncthreads();
-        s1 = sh64[0][0];
-        s2 = sh64[1][0];
-        lmin = sh32[0][0];
-        lmax = sh32[1][0];
-        for (int i = 1; i < nw; ++i) {
-            s1 += sh64[0][i];
-            s2 += sh64[1][i];
-            lmin = min(lmin, sh32[0][i]);
-            lmax = max(lmax, sh32[1][i]);
-        }
-    }
-    StepRec *rec = I.rec + k;
-    if (threadIdx.x == 0) {
-        rec->R = Rk;
-        rec->sumE = s1;
-        rec->sumE2 = (uint64_t)s2;
-        rec->sumE2_hi = 0;
-        rec->Emin = 2 * lmin - N3;
-        rec->Emax = 2 * lmax - N3;
-        rec->S = __builtin_nan("");
-    }
-    if (resample) {
-        if (threadIdx.x == 0) {
-            pw[0] = rho_k;
-            for (int b = 1; b < 40; ++b) pw[b] = pw[b - 1] * pw[b - 1];
-        }
-        __syncthreads();
-        const int nl = lmax - lmin + 1;
-        int P = 1;
-        while (P < nl) P <<= 1;
-        const double S = tree_sum<NT>(
-            P,
-            [&](int m) { return m < nl ? (double)I.hist[lmin + m] * level_weight(pw, (uint32_t)m) : 0.0; },
-            tree, roots);
-        for (int m = threadIdx.x; m < nl; m += blockDim.x) {
-            const double tau = (Rd * level_weight(pw, (uint32_t)m)) / S;
-            const double fl = __builtin_floor(tau);
-            uint2 bf;
-            bf.x = (uint32_t)fl;
-            bf.y = (uint32_t)__builtin_floor((tau - fl) * 4294967296.0);
-            I.BF[m] = bf;
-        }
-        if (threadIdx.x == 0) rec->S = S;
-    }
-    // the sweep of this step moved the population to the other buffer
-    if (threadIdx.x == 0 && *I.mapped) {
-        *I.cur ^= 1;
-        *I.mapped = 0;
-    }
+    return c == 0 ? I.hist : I.loff + (size_t)(c - 1) * I.nlev;
 }
+
+// The buffer that holds the population once the sweeps of the step are done:
+// a sweep through the copy map wrote the other one, and the roles move on
+// when the post launch finishes (real couplings: when the sweep launch does).
+__device__ __forceinline__ int swept_buffer(const Inst &I) { return *I.cur ^ *I.mapped; }
 
 // Measurement of step k with real couplings, by the last sweep workgroup:
 // the energy moments the tiles accumulated (exact integers) go to the step

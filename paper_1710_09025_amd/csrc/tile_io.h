@@ -1,0 +1,151 @@
+// tile_io.h -- device routines shared by the sweep kernels: the rows of a tile
+// (through the copy map or in place, one byte or one bit per spin), the byte
+// transpose between rows and replica words, and the end of a sweep workgroup
+// (energies, family counts, the election of the measuring workgroup).
+#pragma once
+#include "pamc_dev.h"
+#include "step_common.h"
+
+namespace pamc {
+
+// Packed spin rows: bit p of a row (bit p & 7 of byte p >> 3) is the spin at
+// storage position p.  Kernels work on one byte per position in LDS; 16
+// stored bits are one 16-byte LDS vector.
+__device__ __forceinline__ uint32_t bits_to_bytes4(uint32_t nib)
+{
+    // bit i of the nibble lands on bit 8 i: nib + (nib << 7) + (nib << 14) + (nib << 21)
+    return (nib * 0x00204081u) & 0x01010101u;
+}
+__device__ __forceinline__ uint4 bits_to_bytes16(uint32_t b)
+{
+    return make_uint4(bits_to_bytes4(b & 15u), bits_to_bytes4((b >> 4) & 15u), bits_to_bytes4((b >> 8) & 15u),
+                      bits_to_bytes4((b >> 12) & 15u));
+}
+__device__ __forceinline__ uint32_t bytes_to_bits4(uint32_t w)
+{
+    // byte i (0 or 1) lands on bit 24 + i of w * (2^24 + 2^17 + 2^10 + 2^3)
+    return (uint32_t)(((uint64_t)w * 0x01020408ull) >> 24) & 15u;
+}
+__device__ __forceinline__ uint32_t bytes_to_bits16(uint4 v)
+{
+    return bytes_to_bits4(v.x) | (bytes_to_bits4(v.y) << 4) | (bytes_to_bits4(v.z) << 8) | (bytes_to_bits4(v.w) << 12);
+}
+// ---------------------------------------------------------------------------
+// Shared tile load / store.  Rows of the tile come from buffer `cur`, either
+// directly (in place) or through the copy map (then they go to the other
+// buffer, with their family ids).
+// ---------------------------------------------------------------------------
+struct TileIO {
+    const uint8_t *src;
+    uint8_t *dst;
+    const uint32_t *map;  // nullptr: identity
+    const uint32_t *fsrc;
+    uint32_t *fdst;
+    int32_t *Edst;
+    int64_t *Eqdst;       // real couplings: 64-bit energies
+    int packed;           // stored rows hold one bit per position
+    int srow;             // bytes per stored row
+};
+
+__device__ __forceinline__ TileIO tile_io(const Inst &I)
+{
+    TileIO io;
+    // (both buffers' pointers are read at once, not the one that cur picks
+    // after it has arrived)
+    uint8_t *const s0 = I.spins[0], *const s1 = I.spins[1];
+    uint32_t *const f0 = I.fam[0], *const f1 = I.fam[1], *const map = I.map;
+    int32_t *const e0 = I.E[0], *const e1 = I.E[1];
+    int64_t *const q0 = I.Eq[0], *const q1 = I.Eq[1];
+    io.packed = I.packed;
+    io.srow = I.srow_bytes;
+    const int cur = *I.cur, mapped = *I.mapped, out = cur ^ mapped;
+    io.src = cur ? s1 : s0;
+    io.dst = out ? s1 : s0;
+    io.map = mapped ? map : nullptr;
+    io.fsrc = cur ? f1 : f0;
+    io.fdst = mapped ? (out ? f1 : f0) : nullptr;
+    io.Edst = out ? e1 : e0;
+    io.Eqdst = out ? q1 : q0;
+    return io;
+}
+
+// 16-byte LDS vector c of stored row `row`: a copy, or 16 stored bits
+// expanded to bytes.
+__device__ __forceinline__ uint4 stored_vec(const TileIO &io, const uint8_t *row, int c)
+{
+    if (io.packed) return bits_to_bytes16(reinterpret_cast<const uint16_t *>(row)[c]);
+    return reinterpret_cast<const uint4 *>(row)[c];
+}
+__device__ __forceinline__ void store_vec(const TileIO &io, uint8_t *row, int c, uint4 v)
+{
+    if (io.packed)
+        reinterpret_cast<uint16_t *>(row)[c] = (uint16_t)bytes_to_bits16(v);
+    else
+        reinterpret_cast<uint4 *>(row)[c] = v;
+}
+
+// Energies of the tile's rows, stored and (populations too large for the
+// measurement to read them all) counted.  The workgroups count into
+// hist_copies histograms in turn: a launch's atomics fall on the same hundred
+// bins or less, and those on one address follow each other about 0.1 us apart.
+__device__ __forceinline__ void tile_energy_out(const Inst &I, const TileIO &io, const int *unsat, int r0, int nrows)
+{
+    const int copies = I.hist_copies;
+    uint32_t *hist = copies > 0 ? hist_copy(I, (int)blockIdx.x % copies) : nullptr;
+    for (int base = 0; base < nrows; base += blockDim.x) {
+        const int q = base + (int)threadIdx.x;
+        const bool valid = q < nrows;
+        int E = 0;
+        if (valid) {
+            E = 2 * unsat[q] - 3 * I.N;
+            io.Edst[r0 + q] = E;
+        }
+        if (copies > 0) count_wave(hist, (uint32_t)((E + 3 * I.N) >> 1), valid);
+    }
+}
+
+// Descendants per family: a tile's rows counted under their family ids fam[]
+// (sorted, unless a caller's imported state is not: then the runs are short).
+__device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t *fam, int nrows)
+{
+    for (int base = 0; base < nrows; base += blockDim.x) {
+        const int q = base + (int)threadIdx.x;
+        const bool valid = q < nrows;
+        count_runs(I.cnt, valid ? fam[q] : 0u, valid);
+    }
+}
+
+// A sweep launch runs the whole step (phase 0) or, for runs with cluster
+// moves, the first floor(N_S/2) sweeps (phase 1: through the copy map, no
+// energies) and later the remaining ones (phase 2: in place, with energies
+// and the measurement).
+__device__ __forceinline__ int phase_t0(const Inst &I, int phase) { return phase == 2 ? I.NS / 2 : 0; }
+__device__ __forceinline__ int phase_t1(const Inst &I, int phase) { return phase == 1 ? I.NS / 2 : I.NS; }
+
+// End of phase 1 in the last workgroup: the population now lives in the
+// buffer the tiles were written to.
+__device__ __forceinline__ void phase1_done(const Inst &I)
+{
+    const bool last = last_workgroup<false>(&I.sync[0], I.sweep_tiles);
+    if (last && threadIdx.x == 0 && *I.mapped) {
+        *I.cur ^= 1;
+        *I.mapped = 0;
+    }
+}
+
+// 4 x 4 byte transpose: word k of the result holds byte k of w0, w1, w2, w3
+// (v_perm selectors: bytes 0-3 of the second operand, 4-7 of the first).
+// It is its own inverse.
+__device__ __forceinline__ void transpose4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t (&o)[4])
+{
+    const uint32_t a_lo = __builtin_amdgcn_perm(w1, w0, 0x05010400u);  // [w0.0 w1.0 w0.1 w1.1]
+    const uint32_t a_hi = __builtin_amdgcn_perm(w1, w0, 0x07030602u);  // [w0.2 w1.2 w0.3 w1.3]
+    const uint32_t b_lo = __builtin_amdgcn_perm(w3, w2, 0x05010400u);
+    const uint32_t b_hi = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+    o[0] = __builtin_amdgcn_perm(b_lo, a_lo, 0x05040100u);
+    o[1] = __builtin_amdgcn_perm(b_lo, a_lo, 0x07060302u);
+    o[2] = __builtin_amdgcn_perm(b_hi, a_hi, 0x05040100u);
+    o[3] = __builtin_amdgcn_perm(b_hi, a_hi, 0x07060302u);
+}
+
+}  // namespace pamc

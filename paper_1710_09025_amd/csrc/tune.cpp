@@ -20,6 +20,7 @@
 // appended to the latter, so a later process finds them.
 #include <dlfcn.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -44,32 +45,41 @@ constexpr int kTimedSteps = 3;      // timed steps per candidate shape (after on
 constexpr int kBurnIn = 8;          // steps before the first candidate
 constexpr double kTuneBeta = 2.0;   // inside the low-temperature part where an anneal spends most steps
 
-bool is_cm(const HostInst &h)
-{
-    return h.variant == kSweepCM2 || h.variant == kSweepCM2T || h.variant == kSweepCM3 || h.variant == kSweepCM3T ||
-           h.variant == kSweepCQ2 || h.variant == kSweepCQ3 || h.variant == kSweepSQ2 || h.variant == kSweepSQ3;
-}
-bool is_cq(const HostInst &h)
-{
-    return h.variant == kSweepCQ2 || h.variant == kSweepCQ3 || h.variant == kSweepSQ2 || h.variant == kSweepSQ3;
-}
-bool is_eo(const HostInst &h) { return h.variant == kSweepEO8 || h.variant == kSweepEO16; }
+bool is_rb(const HostInst &h) { return h.variant == kSweepRB; }
 
-int64_t sweep_lds(const HostInst &h, int tile_rows, int rp)
+// Philox blocks of the largest colour.
+int max_blocks(const HostInst &h) { return layout_for(h.L, h.real != 0, h.dim).gmax; }
+
+// Dynamic LDS of a sweep workgroup.
+int64_t sweep_lds(const HostInst &h)
 {
-    if (is_cq(h)) return (int64_t)cm_slot_bytes(h.row_bytes, h.tpr, 4) * rp + 32 + 8 * (int64_t)tile_rows;
-    if (is_cm(h))
-        return (int64_t)cm_slot_bytes(h.row_bytes, h.tpr, 8) * rp + 32 + 4 * (int64_t)tile_rows +
-               cm_table_bytes(h.variant, h.tpr);
-    return (int64_t)tile_rows * h.row_bytes + 32 + 4 * (int64_t)tile_rows;
+    if (is_rb(h)) return (int64_t)rb_lds(rb_plane(h.row_bytes), h.sets);
+    return (int64_t)cm_slot_bytes(h.row_bytes, h.tpr, 4) * h.rp + 32 + 8 * (int64_t)h.tile_rows;
+}
+
+// A +-1 shape: m replicas per word, `sets` sets per pass, tile_rows rows per
+// workgroup.  rp, reported as group_replicas = 4 rp, is 0 where the caller
+// cannot choose it.
+bool fixed_group(const HostInst &h) { return is_rb(h) && (h.L == 8 || h.L == 16 || h.L > 21 || (h.L > 20 && h.L % 2 == 0)); }
+void set_rb(HostInst &h, int m, int sets, int tile_rows)
+{
+    h.mrep = m;
+    h.sets = sets;
+    h.tile_rows = tile_rows;
+    h.rp = fixed_group(h) ? 0 : (m * sets + 3) / 4;
 }
 
 struct Choice {
-    int tile_rows, rp;
+    int tile_rows, rp, mrep, sets;
     double ns_per_attempt;
 };
 
 using Key = std::tuple<int, int, int, int, int, int>;  // variant, dim, L, sweeps, log2 capacity, packed
+
+// The variant a +-1 choice is stored under tells the replicas per word
+// (kSweepRB + m, m <= kMaxWord); its workgroups sweep tile_rows = m sets rows
+// in one pass.
+constexpr int kMaxWord = 32;
 
 std::mutex g_mu;
 std::map<std::pair<std::string, Key>, Choice> g_cache;  // by device and key
@@ -108,7 +118,13 @@ void load_file(const std::string &path)
         int v, d, L, ns, cl, pk, tr, rp;
         double npa;
         if (std::sscanf(line, kLineFmt, dev, &v, &d, &L, &ns, &cl, &pk, &tr, &rp, &npa) != 10) continue;
-        g_cache[{dev, Key(v, d, L, ns, cl, pk)}] = Choice{tr, rp, npa};
+        Choice c{tr, rp, 0, 0, npa};
+        if (v > kSweepRB && v <= kSweepRB + kMaxWord) {
+            c.mrep = v - kSweepRB;
+            c.sets = tr / c.mrep;
+            v = kSweepRB;
+        }
+        g_cache[{dev, Key(v, d, L, ns, cl, pk)}] = c;
     }
     std::fclose(f);
 }
@@ -139,7 +155,7 @@ void save_choice(const std::string &dev, const Key &k, const Choice &c)
     if (g_save_path.empty()) return;
     FILE *f = std::fopen(g_save_path.c_str(), "a");
     if (!f) return;
-    std::fprintf(f, kLineOut, dev.c_str(), std::get<0>(k), std::get<1>(k), std::get<2>(k), std::get<3>(k),
+    std::fprintf(f, kLineOut, dev.c_str(), std::get<0>(k) + c.mrep, std::get<1>(k), std::get<2>(k), std::get<3>(k),
                  std::get<4>(k), std::get<5>(k), c.tile_rows, c.rp, c.ns_per_attempt);
     std::fputc('\n', f);
     std::fclose(f);
@@ -154,74 +170,195 @@ int ceil_log2(int64_t v)
 
 }  // namespace
 
-// Whether (tile_rows, rp) is a shape the instance's sweep kernel can run;
-// on failure *why says what is wrong.
-bool shape_valid(const HostInst &h, int tile_rows, int rp, const char **why)
+// Whether the sweep kernel of the instance can run its shape; on failure
+// *why says what is wrong.
+bool shape_valid(const HostInst &h, const char **why)
 {
     const char *w = nullptr;
-    if (tile_rows < 1 || tile_rows > 4096) {
+    if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
-    } else if (is_eo(h) && tile_rows % eo_replicas_per_pass(h.L) != 0) {
-        w = "tile_rows must be a multiple of the replicas one pass sweeps";
-    } else if (is_cm(h) && (rp < 1 || (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) ||
-                            cm_launch_threads(h.tpr, rp) > 1024)) {
+    } else if (is_rb(h)) {
+        const int G = max_blocks(h);
+        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (rb_uniform(G) && h.sets != 1) || rb_threads(G, h.sets) > 1024)
+            w = "no such grouping of replicas";
+    } else if (h.rp < 1 || (h.tpr <= 64 && (h.tpr * h.rp) % 64 != 0) || cm_launch_threads(h.tpr, h.rp) > 1024) {
         w = "group_replicas must be a multiple of four giving at most 1024 threads (whole waves when a quad "
             "takes at most 64)";
-    } else if (sweep_lds(h, tile_rows, is_cm(h) ? rp : 0) > kMaxLds) {
-        w = "the workgroup's tile does not fit in LDS";
     }
+    if (!w && sweep_lds(h) > kMaxLds) w = "the workgroup's tile does not fit in LDS";
     if (why) *why = w;
     return w == nullptr;
 }
 
-// The shape used without tuning: enough workgroups to fill the chip when
-// the population is small, up to four passes per workgroup when it is
-// large.  gmax: Philox blocks of the largest colour.
-void default_shape(HostInst &h, int gmax)
+// Sets of a +-1 workgroup of about `threads` threads: one where a set fills
+// whole waves, else the count up to that size (at least one) with the fewest
+// idle lanes.
+static int rb_sets(int G, int plane, int threads)
 {
-    const int64_t target = 512;  // workgroups: two per compute unit
-    if (is_eo(h)) {
-        const int rp = eo_replicas_per_pass(h.L);
-        const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (target * rp)));
-        h.tile_rows = (int)(m * rp);
-        h.rp = 0;
-    } else if (is_cm(h)) {
-        h.rp = cm_replicas_per_block(h.tpr);
-        const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (target * 4 * h.rp)));
-        h.tile_rows = (int)(m * 4 * h.rp);
-    } else {
-        // per-site kernel: about 512 Philox blocks of work per workgroup
-        int tr = (512 + gmax - 1) / gmax;
-        tr = std::min(tr, std::max(1, 16384 / h.row_bytes));
-        h.tile_rows = std::max(1, tr);
-        h.rp = 0;
+    int best = 1;
+    double best_use = 0.0;
+    if (rb_uniform(G)) return 1;
+    for (int s = 1; rb_threads(G, s) <= std::min(1024, std::max(threads, rb_threads(G, 1))); ++s) {
+        if ((int64_t)rb_lds(plane, s) > kMaxLds) break;
+        const double use = (double)G * s / rb_threads(G, s);
+        if (use >= best_use - 0.005) {
+            best = s;
+            best_use = std::max(use, best_use);
+        }
     }
+    return best;
 }
 
-std::vector<std::pair<int, int>> shape_candidates(const HostInst &h)
+// Workgroups of nt threads and lds bytes a compute unit holds at once: 24
+// waves (80 registers a lane), 160 KB of LDS.
+constexpr int kCU = 256;
+static int rb_per_cu(int nt, int64_t lds)
 {
-    std::vector<std::pair<int, int>> c;
+    return std::max<int>(1, (int)std::min<int64_t>(24 / (nt / 64), 160 * 1024 / (lds + 512)));
+}
+// Replicas per word worth trying (the table mode draws for four at a time).
+constexpr int kWords[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
+
+// The shape used without tuning.
+//   +-1 couplings: the sets and the replicas per word m that give the shortest
+// launch by what a colour step of a lane issues, about 190 instructions for
+// its fields and 42 per draw, at 4.45 cycles an instruction for each of the
+// waves that share a SIMD (6 for one, 9.3 for two).  Large words save fields,
+// small ones fill the chip and its last round of workgroups.  The figures are
+// measured; over 28 sizes from L = 4, R = 10^3 to L = 16, R = 5 10^5 the shape
+// chosen is within 10% of the best of all that can be tried.
+//   Real couplings: enough workgroups to fill the chip when the population
+// is small, up to four passes per workgroup when it is large.
+void default_shape(HostInst &h, int gmax)
+{
+    if (is_rb(h)) {
+        const int plane = rb_plane(h.row_bytes);
+        double best = INFINITY;
+        int last = 0;
+        for (int threads : {64, 256, 1024}) {
+            const int sets = rb_sets(gmax, plane, threads);
+            if (sets == last) continue;
+            last = sets;
+            const int nt = rb_threads(gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
+            const int per_cu = rb_per_cu(nt, (int64_t)rb_lds(plane, sets));
+            for (int m : kWords) {
+                if (m > 4 && m * sets > h.R) break;
+                const int64_t wgs = (h.R + m * sets - 1) / (m * sets), round = (int64_t)kCU * per_cu;
+                // cycles per instruction of a lane's colour step with n
+                // workgroups on the chip, from the waves that share a SIMD
+                auto cycles = [&](int64_t n) {
+                    const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
+                    return w == 0 ? 0.0 : w == 1 ? 6.0 : w == 2 ? 9.3 : 4.45 * (double)w;
+                };
+                const double t = (190.0 + 42.0 * m) * blocks *
+                                 ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
+                if (t < 0.98 * best) {
+                    best = t;
+                    set_rb(h, m, sets, m * sets);
+                }
+            }
+        }
+        return;
+    }
+    const int64_t target = 512;  // workgroups: two per compute unit
+    h.rp = cm_replicas_per_block(h.tpr);
+    const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (target * 4 * h.rp)));
+    h.tile_rows = (int)(m * 4 * h.rp);
+}
+
+// The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
+// With +-1 couplings the options keep the ranges documented for them: quads
+// of replicas in byte planes, tiles that fit the workgroup's LDS at one byte
+// per spin (and, L = 8 and 16, whole passes of 8 and 2 rows; group_replicas
+// is ignored there and where a lattice has no quads).  The words of M
+// replicas then take as many of the group's replicas as they can.
+// h holds the default shape on entry.
+bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why)
+{
+    const char *w = nullptr;
+    if (!is_rb(h)) {
+        const int rp = group_replicas > 0 ? group_replicas / 4 : h.rp;
+        // without an explicit tile: the default number of passes per workgroup
+        h.tile_rows = tile_rows > 0 ? tile_rows : h.tile_rows / h.rp * rp;
+        h.rp = rp;
+        return shape_valid(h, why);
+    }
+    int group = 0;
+    const int rb = h.row_bytes;
+    if (h.L == 8 || h.L == 16) {
+        const int p = h.L == 8 ? 8 : 2;
+        tile_rows = (tile_rows + p - 1) / p * p;
+        if (tile_rows > 4096)
+            w = "tile_rows must be in [1, 4096]";
+        else if ((int64_t)tile_rows * h.N + 32 + 4 * (int64_t)tile_rows > kMaxLds)
+            w = "the workgroup's tile does not fit in LDS";
+    } else if (fixed_group(h)) {
+        if ((int64_t)tile_rows * ((h.N + 15) & ~15) + 32 + 4 * (int64_t)tile_rows > kMaxLds)
+            w = "the workgroup's tile does not fit in LDS";
+    } else {
+        const int rp0 = cm_replicas_per_block(h.tpr), rp = group_replicas > 0 ? group_replicas / 4 : rp0;
+        const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (512 * 4 * rp0)));
+        if (tile_rows <= 0) tile_rows = (int)m * 4 * rp;
+        int64_t table = h.ncol == 3 ? 16 + 144 * h.tpr : h.tpr <= 128 ? 16 + 96 * h.tpr : 0;
+        const int64_t slot = cm_slot_bytes(rb, h.tpr, 8);
+        if (slot * rp0 + 32 + 4 * 64 + table > kMaxLds || 8 * (int64_t)cm_plane_bytes(rb) > 65536) table = 0;
+        group = 4 * rp;
+        if (tile_rows > 4096)
+            w = "tile_rows must be in [1, 4096]";
+        else if (rp < 1 || (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) || cm_launch_threads(h.tpr, rp) > 1024)
+            w = "group_replicas must be a multiple of four giving at most 1024 threads (whole waves when a quad "
+                "takes at most 64)";
+        else if (slot * rp + 32 + 4 * (int64_t)tile_rows + table > kMaxLds)
+            w = "the workgroup's tile does not fit in LDS";
+    }
+    if (why) *why = w;
+    if (w) return false;
+    const int rows = group > 0 ? std::min(group, tile_rows) : tile_rows;
+    const int m = std::min(rows, kMaxWord), plane = rb_plane(rb);
+    set_rb(h, m, std::max(1, std::min(rb_sets(gmax, plane, 256), rows / m)), tile_rows);
+    return shape_valid(h, why);
+}
+
+static std::vector<HostInst> shape_candidates(const HostInst &h)
+{
+    // (only the shape fields of the returned descriptions are used)
+    std::vector<HostInst> c;
+    HostInst t;
+    t.dim = h.dim;
+    t.L = h.L;
+    t.N = h.N;
+    t.variant = h.variant;
+    t.row_bytes = h.row_bytes;
+    t.real = h.real;
+    t.tpr = h.tpr;
+    if (is_rb(h)) {
+        const int G = max_blocks(h), plane = rb_plane(h.row_bytes);
+        int last = 0;
+        for (int threads : {64, 128, 256, 512, 1024}) {
+            const int sets = rb_sets(G, plane, threads);
+            if (sets == last) continue;
+            last = sets;
+            for (int m : kWords) {
+                set_rb(t, m, sets, m * sets);
+                if ((m == 1 || m * sets <= 2 * h.Rcap) && shape_valid(t, nullptr)) c.push_back(t);
+            }
+        }
+        return c;
+    }
     // tile sizes between the powers of two matter: the number of tiles
     // against the number of resident workgroups decides how full the last
     // round of workgroups is
-    if (is_eo(h)) {
-        const int rp = eo_replicas_per_pass(h.L);
-        for (int m = 1; m <= 16; ++m)
-            if (shape_valid(h, m * rp, 0, nullptr) && m * rp <= 2 * h.Rcap) c.emplace_back(m * rp, 0);
-    } else if (is_cm(h)) {
-        static const int kPasses[] = {1, 2, 3, 4, 6, 8};
-        // quads of up to 64 threads: groups of whole waves; wider quads: any
-        // count whose last wave is at least 80% used
-        for (int rp = 1; cm_launch_threads(h.tpr, rp) <= 1024; rp = h.tpr <= 64 ? 2 * rp : rp + 1) {
-            if (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) continue;
-            if (h.tpr > 64 && rp > 1 && 5 * h.tpr * rp < 4 * cm_launch_threads(h.tpr, rp)) continue;
-            for (int m : kPasses)
-                if (shape_valid(h, 4 * m * rp, rp, nullptr) && 4 * m * rp <= 2 * h.Rcap)
-                    c.emplace_back(4 * m * rp, rp);
+    static const int kPasses[] = {1, 2, 3, 4, 6, 8};
+    // quads of up to 64 threads: groups of whole waves; wider quads: any
+    // count whose last wave is at least 80% used
+    for (int rp = 1; cm_launch_threads(h.tpr, rp) <= 1024; rp = h.tpr <= 64 ? 2 * rp : rp + 1) {
+        if (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) continue;
+        if (h.tpr > 64 && rp > 1 && 5 * h.tpr * rp < 4 * cm_launch_threads(h.tpr, rp)) continue;
+        for (int m : kPasses) {
+            t.tile_rows = 4 * m * rp;
+            t.rp = rp;
+            if (shape_valid(t, nullptr) && 4 * m * rp <= 2 * h.Rcap) c.push_back(t);
         }
-    } else {
-        for (int t = 1; t <= 4096; t *= 2)
-            if (shape_valid(h, t, 0, nullptr) && t <= 2 * h.Rcap) c.emplace_back(t, 0);
     }
     return c;
 }
@@ -234,11 +371,24 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
         std::lock_guard<std::mutex> lk(g_mu);
         load_persistent();
         auto it = g_cache.find(key);
-        if (it != g_cache.end() && shape_valid(h, it->second.tile_rows, it->second.rp, nullptr)) {
-            h.tile_rows = it->second.tile_rows;
-            h.rp = it->second.rp;
-            if (ns_per_attempt) *ns_per_attempt = it->second.ns_per_attempt;
-            return PAMC_OK;
+        if (it != g_cache.end()) {
+            const Choice &c = it->second;
+            HostInst t;
+            t.dim = h.dim;
+            t.L = h.L;
+            t.variant = h.variant;
+            t.row_bytes = h.row_bytes;
+            t.real = h.real;
+            t.tpr = h.tpr;
+            t.tile_rows = c.tile_rows;
+            t.rp = c.rp;
+            t.mrep = c.mrep;
+            t.sets = c.sets;
+            if (shape_valid(t, nullptr)) {
+                take_shape(h, t);
+                if (ns_per_attempt) *ns_per_attempt = c.ns_per_attempt;
+                return PAMC_OK;
+            }
         }
     }
     const auto cand = shape_candidates(h);
@@ -282,10 +432,10 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
     if (st == PAMC_OK) st = run.sync();
     if (st == PAMC_OK) st = run.phase_times(nullptr, nullptr, nullptr, nullptr);
     if (st != PAMC_OK) return st;
-    Choice best{h.tile_rows, h.rp, INFINITY};
+    Choice best{h.tile_rows, h.rp, h.mrep, h.sets, INFINITY};
     for (const auto &c : cand) {
         // one warm-up step, then the fastest of three timed steps
-        st = run.set_shape(slot, c.first, c.second);
+        st = run.set_shape(slot, c);
         double best_ms = INFINITY;
         for (int rep = 0; rep < 1 + kTimedSteps && st == PAMC_OK; ++rep) {
             double sw = 0.0;
@@ -297,7 +447,7 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
         if (st == PAMC_OK) st = run.inst_status(slot, nullptr, nullptr);
         if (st != PAMC_OK) return st;
         const double ns = best_ms * 1e6 / attempts;
-        if (ns < best.ns_per_attempt) best = Choice{c.first, c.second, ns};
+        if (ns < best.ns_per_attempt) best = Choice{c.tile_rows, c.rp, c.mrep, c.sets, ns};
     }
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -306,6 +456,8 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
     }
     h.tile_rows = best.tile_rows;
     h.rp = best.rp;
+    h.mrep = best.mrep;
+    h.sets = best.sets;
     if (ns_per_attempt) *ns_per_attempt = best.ns_per_attempt;
     return PAMC_OK;
 }
