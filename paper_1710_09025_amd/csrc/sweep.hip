@@ -35,15 +35,18 @@ __device__ __forceinline__ int stored_spin(const Inst &I, const uint8_t *row, in
 // ---------------------------------------------------------------------------
 // Initial replicas (Sec. II.B: random configurations at beta = 0).  Site s
 // of row r takes S = +1 when bit 31 of word (s & 3) of Philox at counter
-// (s >> 2, r, 0, TAG_INIT) is set.  One thread per Philox block.
+// (s >> 2, r, 0, TAG_INIT) is set.  One thread per Philox block; gridDim.y
+// workgroups share the 1024 rows of a work item.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_init(const Inst *insts, const Work *work)
 {
     extern __shared__ __align__(16) uint8_t stage[];
-    const Work w = work[blockIdx.x];
+    Work w = work[blockIdx.x];
     const Inst &I = inst_ref(insts, w.inst);
     const int nq = (I.N + 3) >> 2;
-    const int rows = min(kRowsPerBlock, I.R - (int)w.row0);
+    const int per = kRowsPerBlock / (int)gridDim.y;
+    w.row0 += blockIdx.y * per;
+    const int rows = min(per, I.R - (int)w.row0);
     if (!I.packed) {
         uint8_t *sp = I.spins[0];
         for (int it = threadIdx.x; it < rows * nq; it += blockDim.x) {
@@ -90,14 +93,17 @@ __global__ __launch_bounds__(256) void k_init(const Inst *insts, const Work *wor
 // ---------------------------------------------------------------------------
 // Energies of the rows of the current buffer, Eq. (1): E = -sum over the
 // D N bonds (s, s + e_d) of J S_s S_{s+e_d} (D = 3, or 2 on the square
-// lattice, real couplings only).  One wave per row.
+// lattice, real couplings only).  One wave per row; gridDim.y workgroups
+// share the 1024 rows of a work item.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_energy(const Inst *insts, const Work *work, const int8_t *const *Jraw)
 {
-    const Work w = work[blockIdx.x];
+    Work w = work[blockIdx.x];
     const Inst &I = inst_ref(insts, w.inst);
     const int k = *I.k;
     if (k >= I.nT) return;
+    const int per = kRowsPerBlock / (int)gridDim.y;
+    w.row0 += blockIdx.y * per;
     const int Rk = (int)I.Rk[k];
     const int cur = *I.cur;
     const int8_t *J = Jraw[w.inst];
@@ -108,7 +114,7 @@ __global__ __launch_bounds__(256) void k_energy(const Inst *insts, const Work *w
         // the square lattice z = 0 and the z bond is absent
         const int32_t *Jq = reinterpret_cast<const int32_t *>(J);
         const int Lz = I.dim == 3 ? L : 1;
-        for (int q = wave; q < kRowsPerBlock; q += 4) {
+        for (int q = wave; q < per; q += 4) {
             const int r = (int)w.row0 + q;
             if (r >= Rk) break;
             const uint8_t *S = I.spins[cur] + (size_t)r * I.srow_bytes;
@@ -126,7 +132,7 @@ __global__ __launch_bounds__(256) void k_energy(const Inst *insts, const Work *w
         }
         return;
     }
-    for (int q = wave; q < kRowsPerBlock; q += 4) {
+    for (int q = wave; q < per; q += 4) {
         const int r = (int)w.row0 + q;
         if (r >= Rk) break;
         const uint8_t *S = I.spins[cur] + (size_t)r * I.srow_bytes;
@@ -522,14 +528,24 @@ hipError_t sweep_kernels_init()
     return hipSuccess;
 }
 
+// Workgroups per work item of 1024 rows: down to 8 rows each where there are
+// few items (whole items in one workgroup left most of the chip idle: 70 ms
+// for the 4000 rows of an L = 24 run).
+static unsigned row_slices(int nwork)
+{
+    unsigned s = 1;
+    while (s < 128 && s * (unsigned)nwork < 4096) s *= 2;
+    return s;
+}
+
 void launch_init(const Inst *insts, const Work *work, int nwork, size_t lds_bytes, hipStream_t st)
 {
-    if (nwork) k_init<<<nwork, 256, lds_bytes, st>>>(insts, work);
+    if (nwork) k_init<<<dim3(nwork, row_slices(nwork)), 256, lds_bytes, st>>>(insts, work);
 }
 
 void launch_energy(const Inst *insts, const Work *work, int nwork, const int8_t *const *Jraw, hipStream_t st)
 {
-    if (nwork) k_energy<<<nwork, 256, 0, st>>>(insts, work, Jraw);
+    if (nwork) k_energy<<<dim3(nwork, row_slices(nwork)), 256, 0, st>>>(insts, work, Jraw);
 }
 
 // Default workgroup shape of the colour-major sweep: 256 / tpr quads for
