@@ -16,7 +16,7 @@ namespace pamc {
 // workgroup of the gather do that instead costs a device-scope release fence
 // in every one of its many short workgroups, which slowed the gather about
 // five-fold.)
-// A work item is a block of w.pad destination rows (about 32 KB of spins);
+// A work item is a block of w.n destination rows (about 32 KB of spins);
 // each thread keeps four 16-byte loads in flight before its stores.  The
 // rows are written with nontemporal (streaming) stores: the new population
 // is not read again before the next sweep, and ordinary stores let it evict
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void k_gather(const Inst *insts, const Work *w
     if (k >= I.nT || I.status[0] || !*I.mapped) return;
     const int Rn = (int)I.Rk[k];
     const int row0 = (int)w.row0;
-    const int rows = min((int)w.pad, Rn - row0);
+    const int rows = min((int)w.n, Rn - row0);
     if (rows <= 0) return;
     const int cur = *I.cur;
     const int per_row = I.srow_bytes >> 4;

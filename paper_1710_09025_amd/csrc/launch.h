@@ -6,23 +6,28 @@
 
 namespace pamc {
 
-// RB: +-1 couplings, replicas as bits of an LDS word; CQ: real couplings,
-// replica quads (two or three colours); SQ: CQ on the square lattice (four
-// neighbours)
+// CQ: real couplings, replica quads (two or three colours); RB: +-1 couplings,
+// replicas as bits of an LDS word; RQ: the same with real couplings, on the
+// cubic (3) or square (2) lattice, with thresholds per site in LDS where they
+// fit and pay, else bond sums
 enum SweepVariant {
     kSweepCQ2 = 5,
     kSweepCQ3 = 6,
-    kSweepSQ2 = 7,
-    kSweepSQ3 = 8,
-    kSweepRB = 16
+    kSweepRB = 64,
+    kSweepRQ3Thr = 128,
+    kSweepRQ3Field = 192,
+    kSweepRQ2Thr = 256,
+    kSweepRQ2Field = 320
 };
+enum RQKind { kRQThr, kRQField };  // a table of thresholds, or of bond sums
+inline bool is_rq(int variant) { return variant >= kSweepRQ3Thr; }
 
 // What a sweep launch needs to know of its instances' lattice and shape.
 struct SweepShape {
     int variant = 0, tile_rows = 0, row_bytes = 0;
-    int tpr = 0, rp = 0;  // CQ, SQ: threads per replica quad, quads per workgroup
-    int G = 0, plane = 0; // RB: Philox blocks of the largest colour, words per site plane
-    int M = 0, sets = 0;  // RB: replicas per word, sets (of M replicas) per pass of a workgroup
+    int tpr = 0, rp = 0;  // CQ: threads per replica quad, quads per workgroup
+    int G = 0, plane = 0; // RB, RQ: Philox blocks of the largest colour, words per site plane
+    int M = 0, sets = 0;  // RB, RQ: replicas per word, sets (of M replicas) per pass of a workgroup
 };
 
 // Dynamic LDS a sweep workgroup may take: gfx950 gives one workgroup up to
@@ -70,6 +75,14 @@ inline int rb_plane(int row_bytes) { return row_bytes <= 128 ? row_bytes / 4 : (
 bool rb_uniform(int G);
 int rb_threads(int G, int sets);
 size_t rb_lds(int plane, int sets);
+// The same with real couplings, the tables included (thresholds or bond sums
+// by the rows of a pass).  These kernels have
+// little LDS of their own.
+constexpr int64_t kMaxWordLds = 160 * 1024 - 2048;
+bool rq_uniform(int G);
+int rq_threads(int G, int sets);
+int rq_kind(int variant, int rows);
+int64_t rq_lds(int variant, int plane, int m, int sets);
 
 // LDS of one cluster-move pair (the island search of one lane group): the
 // sector flags of every lexicographic site (a byte: bit 0 where the replicas
@@ -99,6 +112,8 @@ void launch_energy(const Inst *insts, const Work *work, int nwork, const int8_t 
 void launch_sweep(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 void launch_sweep_rb(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 hipError_t sweep_rb_init();
+void launch_sweep_rq(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
+hipError_t sweep_rq_init();
 // resampling weights and their normaliser (instances with real couplings;
 // work items are 1024-row blocks)
 void launch_weights(const Inst *insts, const Work *work, int nwork, hipStream_t st);

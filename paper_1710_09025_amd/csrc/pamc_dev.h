@@ -45,8 +45,9 @@ struct StepRec {
 };
 
 // Energy moments of a step's population with real couplings, accumulated
-// with atomics by the sweep workgroups (one update per tile) and read and
-// reset by the step measurement.  Sums are exact: E^2 as a 128-bit integer.
+// with atomics by the sweep workgroups (one update per pass, in kMomentParts
+// parts), read by the weights launch and reset by k_expand.  Sums are exact: E^2 as a 128-bit integer.
+constexpr int kMomentParts = 64;
 struct EMoments {
     long long emin, emax;
     unsigned long long sum;      // sum of E, two's complement
@@ -84,9 +85,7 @@ struct Inst {
     uint32_t *bsum;     // [nblk]
     uint32_t *boff;     // [nblk]
     uint32_t *sync;     // [4] workgroups finished in the current sweep / post / weights launch
-    int32_t sweep_tiles;  // workgroups of this instance in a sweep launch
     int32_t post_blocks;  // workgroups of this instance in a post launch
-    int32_t tile_rows;    // replica rows per sweep workgroup
     uint32_t *hist;     // [nlev] energy histogram, (E + 3N)/2
     int32_t hist_copies;  // parts the sweep's workgroups count into: hist, and more in loff (cleared by k_expand);
                           //    0: at most kDirectRows rows, measured from their energies
@@ -121,7 +120,7 @@ struct Inst {
     int64_t *Eq[2];     // energies, units of 2^-20
     double *wrep;       // [Rcap] resampling weight of each row
     double *wpart;      // [nblk] pairwise-tree roots of the 1024-row blocks
-    EMoments *emom;     // energy moments of the step being swept
+    EMoments *emom;     // [kMomentParts] energy moments of the step being swept
     const int32_t *cmj; // [ncol][gmax][24] coupling of each neighbour bond, in cmdesc order
     const float *bq;    // [nT] beta_k 2^-20 rounded to binary32
     const double *gpw;  // [nT][40] exp(-(beta_{k+1} - beta_k) 2^(b-20)), host libm
@@ -144,8 +143,8 @@ enum PostRole : uint32_t { kRoleCopies = 0, kRoleFamilies = 1, kRoleOverlap = 2 
 struct Work {
     uint32_t inst;
     uint32_t row0;
-    uint32_t role;
-    uint32_t pad;
+    uint32_t role;   // k_post: what to do
+    uint32_t n;      // sweeps: workgroups of the instance in the launch; gather: rows
 };
 
 }  // namespace pamc

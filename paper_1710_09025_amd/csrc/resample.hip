@@ -20,36 +20,82 @@
 
 namespace pamc {
 
+// The moments of a step with real couplings from their parts, by a wave
+// (lane = part); every lane returns them.
+struct Moments {
+    long long emin, emax;
+    unsigned long long sum, lo, hi;
+};
+__device__ __forceinline__ Moments fold_moments(const EMoments *parts)
+{
+    static_assert(kMomentParts == 64, "one part per lane");
+    const EMoments &p = parts[threadIdx.x & 63];
+    Moments m{p.emin, p.emax, p.sum, p.sq_lo, p.sq_hi};
+    for (int off = 32; off > 0; off >>= 1) {
+        const long long a = __shfl_xor(m.emin, off), b = __shfl_xor(m.emax, off);
+        const unsigned long long s = __shfl_xor(m.sum, off), l = __shfl_xor(m.lo, off), h = __shfl_xor(m.hi, off);
+        m.emin = a < m.emin ? a : m.emin;
+        m.emax = b > m.emax ? b : m.emax;
+        m.sum += s;
+        const unsigned long long nl = m.lo + l;
+        m.hi += h + (nl < m.lo ? 1ull : 0ull);
+        m.lo = nl;
+    }
+    return m;
+}
+
 // Resampling weights with real couplings (Sec. II.B), for rows
 // [row0, row0 + 1024) of one instance after the sweeps of step k:
 // w_r = exp(-dbeta (E_r - E_min)) as the product over the set bits b of
 // E_r - E_min (units of 2^-20) of exp(-dbeta 2^(b-20)), in ascending b.  The
 // block's 1024 leaves (zero beyond R_k) form an aligned subtree of the
 // pairwise tree over rows 0 .. P-1 (P the smallest power of two >= R_k); the
-// last workgroup of the instance folds the block roots (zero for blocks
-// beyond R_k) into the normaliser S.  For P < 1024 the block tree adds only
-// zeros above the P-leaf subtree, which leaves its sum unchanged.
+// copies workgroups fold the block roots (real_normaliser).  For P < 1024 the
+// block tree adds only zeros above the P-leaf subtree, which leaves its sum
+// unchanged.  The instance's first workgroup writes the step's energy record.
 __global__ __launch_bounds__(512) void k_weights(const Inst *insts, const Work *work)
 {
     __shared__ double pw[40];
     __shared__ double a[512];
-    __shared__ double roots[512];
+    __shared__ Moments sh;
     const Work w = work[blockIdx.x];
     const Inst &I = insts[w.inst];
     const int k = *I.k;
-    if (!inst_live(I, k) || k >= I.nT - 1) return;
+    if (!inst_live(I, k)) return;
+    const bool resample = k < I.nT - 1;
+    if (!resample && w.row0 != 0) return;
     const int Rk = (int)I.Rk[k];
     const int t = threadIdx.x;
-    if (t < 40) pw[t] = I.gpw[(size_t)k * 40 + t];
+    if (resample && t < 40) pw[t] = I.gpw[(size_t)k * 40 + t];
+    if (t < 64) {
+        const Moments m = fold_moments(I.emom);
+        if (t == 0) sh = m;
+    }
+    const int64_t *E = I.Eq[swept_buffer(I)];
+    int64_t e[2] = {0, 0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int r = (int)w.row0 + 2 * t + j;
+        if (resample && r < Rk) e[j] = E[r];
+    }
     __syncthreads();
-    const long long Emin = I.rec[k].Emin;
-    const int64_t *E = I.Eq[*I.cur];
+    if (w.row0 == 0 && t == 0) {
+        StepRec *rec = I.rec + k;
+        rec->R = Rk;
+        rec->sumE = (int64_t)sh.sum;
+        rec->sumE2 = sh.lo;
+        rec->sumE2_hi = (int64_t)sh.hi;
+        rec->Emin = sh.emin;
+        rec->Emax = sh.emax;
+        rec->S = __builtin_nan("");
+    }
+    if (!resample) return;
     double l[2] = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int r = (int)w.row0 + 2 * t + j;
         if (r < Rk) {
-            const double x = weight64(pw, (uint64_t)(E[r] - Emin));
+            const double x = weight64(pw, (uint64_t)(e[j] - sh.emin));
             I.wrep[r] = x;
             l[j] = x;
         }
@@ -58,14 +104,17 @@ __global__ __launch_bounds__(512) void k_weights(const Inst *insts, const Work *
     __syncthreads();
     const double root = lds_pairwise(a, 512);
     if (t == 0) I.wpart[w.row0 / kRowsPerBlock] = root;
-    if (last_workgroup(&I.sync[2], I.nblk)) {
-        int P = 1;
-        while (P < Rk) P <<= 1;
-        const int nroot = P > kRowsPerBlock ? P / kRowsPerBlock : 1;
-        const double S = tree_sum<512>(
-            nroot, [&](int b) { return b * kRowsPerBlock < Rk ? I.wpart[b] : 0.0; }, a, roots);
-        if (t == 0) I.rec[k].S = S;
-    }
+}
+
+// The normaliser of a step with real couplings: the pairwise tree over the
+// block roots (zero for blocks beyond R_k).
+__device__ __forceinline__ double real_normaliser(const Inst &I, int Rk, double *a)
+{
+    int P = 1;
+    while (P < Rk) P <<= 1;
+    const int nroot = P > kRowsPerBlock ? P / kRowsPerBlock : 1;
+    return tree_sum<1024>(
+        nroot, [&](int b) { return b * kRowsPerBlock < Rk ? I.wpart[b] : 0.0; }, a, a + 1024);
 }
 
 // Exclusive scan over the workgroup (1024 threads, 16 waves).
@@ -316,19 +365,16 @@ __device__ void copies_role(const Inst &I, int k, uint32_t row0, uint32_t *sh, d
     const int E = !I.real && resample && r < Rk ? I.E[buf][r] : 0;
     if (!I.real && (resample || row0 == 0)) lv = measure_levels(I, k, buf, row0 == 0, pw, a);
     if (!resample) return;
+    if (I.real) {
+        lv.S = real_normaliser(I, Rk, a);
+        if (row0 == 0 && threadIdx.x == 0) I.rec[k].S = lv.S;
+    }
     uint32_t n = 0;
     if (r < Rk) {
         const uint32_t u = philox10(make_uint4(0u, (uint32_t)r, (uint32_t)k, kTagResample), I.key0, I.key1).x;
-        double w, S;
-        if (I.real) {
-            // per-replica weight from the weights launch
-            w = I.wrep[r];
-            S = I.rec[k].S;
-        } else {
-            w = level_weight(pw, (uint32_t)(((E + 3 * I.N) >> 1) - lv.lmin));
-            S = lv.S;
-        }
-        const double tau = (I.Rt[k + 1] * w) / S;
+        // (real couplings: the row's weight from the weights launch)
+        const double w = I.real ? I.wrep[r] : level_weight(pw, (uint32_t)(((E + 3 * I.N) >> 1) - lv.lmin));
+        const double tau = (I.Rt[k + 1] * w) / lv.S;
         const double fl = __builtin_floor(tau);
         n = (uint32_t)fl + (u < (uint32_t)__builtin_floor((tau - fl) * 4294967296.0) ? 1u : 0u);
     }
@@ -502,6 +548,14 @@ __global__ __launch_bounds__(1024) void k_expand(const Inst *insts, const Work *
     if (!inst_live(I, k) || k == 0 || !*I.mapped) return;
     const int Rold = (int)I.Rk[k - 1];
     const int row0 = (int)w.row0;
+    if (I.real && row0 == 0 && threadIdx.x < kMomentParts) {
+        EMoments *m = I.emom + threadIdx.x;
+        m->emin = 0x7FFFFFFFFFFFFFFFll;
+        m->emax = -0x7FFFFFFFFFFFFFFFll - 1;
+        m->sum = 0ull;
+        m->sq_lo = 0ull;
+        m->sq_hi = 0ull;
+    }
     if (!I.real && I.hist_copies > 0) {
         // every copies workgroup has measured the step: the nblk workgroups
         // clear its energy histogram for the next sweep, a slice each

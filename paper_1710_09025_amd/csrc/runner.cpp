@@ -51,7 +51,10 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // Colour-major rows for every lattice.  Real couplings need a replica quad's
 // slot of four byte planes in the workgroup's LDS and its largest colour in
 // 1024 threads (even L up to 20, odd L up to 21); no kernel beyond it.  The
-// square lattice (dim = 2) runs only with real couplings.
+// square lattice (dim = 2) runs only with real couplings.  The replica-word
+// kernels sweep what their tables of the sites' thresholds or bond sums leave
+// LDS for (cubic: L <= 8 and L <= 13, square: L <= 48 and all); the quad
+// kernel the rest (L = 14 ... 21).
 LayoutInfo layout_for(int L, bool real, int dim)
 {
     LayoutInfo li{};
@@ -84,7 +87,12 @@ LayoutInfo layout_for(int L, bool real, int dim)
         li.variant = kSweepRB;
     } else if (li.tpr <= 1024 && 2 * li.row_bytes <= 65535 &&
                (size_t)cm_slot_bytes(li.row_bytes, li.tpr, 4) * cm_replicas_per_block(li.tpr) + 32 + 8 * 64 <= kMaxSweepLds) {
-        li.variant = dim == 2 ? (li.ncol == 2 ? kSweepSQ2 : kSweepSQ3) : (li.ncol == 2 ? kSweepCQ2 : kSweepCQ3);
+        const int thr = dim == 3 ? kSweepRQ3Thr : kSweepRQ2Thr, field = dim == 3 ? kSweepRQ3Field : kSweepRQ2Field;
+        const int plane = rb_plane(li.row_bytes);
+        li.variant = rq_lds(thr, plane, 32, 1) <= kMaxWordLds     ? thr
+                     : rq_lds(field, plane, 32, 1) <= kMaxWordLds ? field
+                     : li.ncol == 2                               ? kSweepCQ2
+                                                                  : kSweepCQ3;
     } else {
         li.valid = false;
     }
@@ -134,18 +142,19 @@ InstLayout layout_of(int L, int64_t R, int64_t Rcap, int nT, int n_ovl, bool pac
     l.loff = c.take((size_t)Rcap * 4);
     l.bsum = c.take((size_t)nblk * 4);
     l.boff = c.take((size_t)nblk * 4);
-    l.hist = c.take((size_t)nlev * 4);
+    l.hist = c.take(real ? 16 : (size_t)nlev * 4);
     l.cnt = c.take((size_t)R * 4);
     l.fpart = c.take((size_t)std::max<int64_t>(1, fp2 / 2048) * 8);
     l.thr = c.take((size_t)nT * 16);
     l.beta = c.take((size_t)nT * 8);
     l.rho = c.take((size_t)nT * 8);
     l.Rt = c.take((size_t)nT * 8);
-    l.rbtab = c.take(real ? 16 : (size_t)ncol * gmax * 64);
+    const bool cq = li.variant == kSweepCQ2 || li.variant == kSweepCQ3;
+    l.rbtab = c.take(cq ? 16 : (size_t)ncol * gmax * 64);
     l.J = c.take((size_t)dim * N * (real ? 4 : 1));
     l.pos = c.take((size_t)N * 2);
     l.lexof = c.take((size_t)li.row_bytes * 2);
-    l.cmdesc = c.take(real ? (size_t)ncol * gmax * 32 * 2 : 16);
+    l.cmdesc = c.take(cq ? (size_t)ncol * gmax * 32 * 2 : 16);
     l.Rk = c.take((size_t)(nT + 1) * 4);
     l.rec = c.take((size_t)nT * sizeof(StepRec));
     l.ovl_slot = c.take((size_t)nT * 4);
@@ -156,7 +165,7 @@ InstLayout layout_of(int L, int64_t R, int64_t Rcap, int nT, int n_ovl, bool pac
     l.Eq1 = c.take(real ? (size_t)Rcap * 8 : 16);
     l.wrep = c.take(real ? (size_t)Rcap * 8 : 16);
     l.wpart = c.take(real ? (size_t)nblk * 8 : 16);
-    l.emom = c.take(sizeof(EMoments));
+    l.emom = c.take(real ? kMomentParts * sizeof(EMoments) : 16);
     l.cmj = c.take(real ? (size_t)ncol * gmax * 24 * 4 : 16);
     l.bq = c.take((size_t)nT * 4);
     l.gpw = c.take(real ? (size_t)nT * 40 * 8 : 16);
@@ -417,6 +426,14 @@ void Runner::remove_instance(int slot)
     used_[slot] = 0;
 }
 
+static EMoments no_moments()
+{
+    EMoments m{};
+    m.emin = std::numeric_limits<long long>::max();
+    m.emax = std::numeric_limits<long long>::min();
+    return m;
+}
+
 int Runner::upload_inst(int i)
 {
     HostInst &h = inst_[i];
@@ -501,8 +518,6 @@ int Runner::upload_inst(int i)
     d.gpw = (const double *)(b + lay.gpw);
     d.Jtot = 0;
     for (int32_t v : h.Jq) d.Jtot += v;
-    d.tile_rows = h.tile_rows;
-    d.sweep_tiles = (int32_t)((h.Rcap + h.tile_rows - 1) / h.tile_rows);
     {
         const int64_t nchunks = std::max<int64_t>(1, fp2 / 2048);
         const int64_t novl = (h.Rcap / 2 + kOvlPairs - 1) / kOvlPairs;
@@ -568,20 +583,19 @@ int Runner::upload_inst(int i)
     for (int s = 0; s < N; ++s) lexof16[(size_t)h.lex_pos[s]] = (uint16_t)s;
     // per colour, Philox block and site: its six neighbours and couplings.
     // On the square lattice the two z entries of a site point at the site
-    // itself with coupling 0: they add nothing to its field or to the
-    // energy, so the sweep kernel runs unchanged.  Padding sites point at
+    // itself with coupling 0 and are not read.  Padding sites point at
     // themselves.
     std::vector<uint16_t> cmdesc;
     std::vector<int32_t> cmj;
     std::vector<uint32_t> rbtab;
     std::vector<int> site_at((size_t)3 * N, -1);
     for (int s = 0; s < N; ++s) site_at[(size_t)col[s] * N + rank[s]] = s;
-    if (h.real) {
+    const bool cq = li.variant == kSweepCQ2 || li.variant == kSweepCQ3;
+    if (cq)
         cmdesc.assign((size_t)h.ncol * d.gmax * 32, 0);
-        cmj.assign((size_t)h.ncol * d.gmax * 24, 0);
-    } else {
+    else
         rbtab.assign((size_t)h.ncol * d.gmax * 16, 0u);
-    }
+    if (h.real) cmj.assign((size_t)h.ncol * d.gmax * 24, 0);
     const bool sq = h.dim == 2;
     for (int c = 0; c < h.ncol; ++c)
         for (int g = 0; g < d.gcs[c]; ++g) {
@@ -607,17 +621,19 @@ int Runner::upload_inst(int i)
                 }
                 for (int dd = 0; dd < 6; ++dd) {
                     const int e = 4 * dd + bb;
-                    if (h.real) {
+                    if (cq) {
                         cmdesc[blk * 32 + e] = (uint16_t)nbp[dd];
-                        cmj[blk * 24 + e] = jv[dd];
                     } else {
                         const uint32_t word = (uint32_t)((nbp[dd] & 3) * d.rb_plane + (nbp[dd] >> 2));
                         rbtab[blk * 16 + (e >> 1)] |= word << (16 * (e & 1));
-                        if (jv[dd] < 0) rbtab[blk * 16 + 12] |= 1u << e;
                     }
+                    if (h.real)
+                        cmj[blk * 24 + e] = jv[dd];
+                    else if (jv[dd] < 0)
+                        rbtab[blk * 16 + 12] |= 1u << e;
                 }
             }
-            if (h.real) {
+            if (cq) {
                 cmdesc[blk * 32 + 24] = (uint16_t)(vmask & 0xFFFFu);
                 cmdesc[blk * 32 + 25] = (uint16_t)(vmask >> 16);
             } else {
@@ -637,9 +653,7 @@ int Runner::upload_inst(int i)
             for (int bb = 0; bb < 40; ++bb) gpw[(size_t)k * 40 + bb] = std::exp(-db * std::ldexp(1.0, bb - 20));
         }
     }
-    EMoments em{};
-    em.emin = std::numeric_limits<long long>::max();
-    em.emax = std::numeric_limits<long long>::min();
+    const std::vector<EMoments> em(h.real ? kMomentParts : 0, no_moments());
     std::vector<uint32_t> Rk0((size_t)h.nT + 1, 0u);
     Rk0[0] = (uint32_t)h.R;
     int32_t ctl[4] = {0, 0, 0, 0};
@@ -658,7 +672,7 @@ int Runner::upload_inst(int i)
     else
         put(lay.J, h.J.data(), h.J.size());
     put(lay.bq, bq.data(), bq.size() * 4);
-    put(lay.emom, &em, sizeof(em));
+    if (!em.empty()) put(lay.emom, em.data(), em.size() * sizeof(EMoments));
     if (!gpw.empty()) put(lay.gpw, gpw.data(), gpw.size() * 8);
     if (!cmj.empty()) put(lay.cmj, cmj.data(), cmj.size() * 4);
     put(lay.pos, pos16.data(), pos16.size() * 2);
@@ -688,10 +702,6 @@ int Runner::set_shape(int i, const HostInst &shape)
     if (i < 0 || i >= max_slots_ || !used_[i]) return PAMC_ERR_STATE;
     HostInst &h = inst_[i];
     take_shape(h, shape);
-    h.dev.tile_rows = h.tile_rows;
-    h.dev.sweep_tiles = (int32_t)((h.Rcap + h.tile_rows - 1) / h.tile_rows);
-    HIPCHK(hipStreamSynchronize(stream_), "set_shape sync");
-    HIPCHK(hipMemcpy(d_insts_ + i, &h.dev, sizeof(Inst), hipMemcpyHostToDevice), "update instance shape");
     return build_work(active_);
 }
 
@@ -726,9 +736,38 @@ int Runner::build_work(const std::vector<int> &active)
     icm_rounds_ = 0;
     icm_N_ = 0;
     std::vector<uint32_t> list;
+    // instances of one lattice without a shape of their own sweep in the
+    // shape that suits their populations together (each its own: small words
+    // that fill the chip alone; a launch of 36 real-coupled instances of
+    // L = 4 ... 8 with 5000 rows each took 1.6 times as long)
+    std::map<std::tuple<int, int, int>, std::vector<int64_t>> pops;
+    std::map<std::tuple<int, int, int>, HostInst> joint;
+    auto lattice = [](const HostInst &h) { return std::make_tuple(h.icm > 0 ? 1 : 0, h.variant, h.L); };
+    for (int i : active)
+        if (!inst_[i].own_shape) pops[lattice(inst_[i])].push_back(inst_[i].R);
     for (int i : active) {
-        const HostInst &h = inst_[i];
+        HostInst &h = inst_[i];
         const uint32_t ii = (uint32_t)i;
+        if (!h.own_shape) {
+            HostInst &s = joint[lattice(h)];
+            if (s.L == 0) {
+                s.dim = h.dim;
+                s.L = h.L;
+                s.N = h.N;
+                s.NS = h.NS;
+                s.ncol = h.ncol;
+                s.variant = h.variant;
+                s.row_bytes = h.row_bytes;
+                s.real = h.real;
+                s.tpr = h.tpr;
+                s.Rcap = h.Rcap;
+                default_shape(s, h.dev.gmax, pops[lattice(h)]);
+            }
+            h.tile_rows = s.tile_rows;
+            h.rp = s.rp;
+            h.mrep = s.mrep;
+            h.sets = s.sets;
+        }
         const auto key = std::make_tuple(h.icm > 0 ? 1 : 0, h.variant, h.L, h.tile_rows, h.row_bytes, h.tpr, h.rp, h.mrep,
                                          h.sets);
         auto &g = groups[key];
@@ -747,7 +786,8 @@ int Runner::build_work(const std::vector<int> &active)
             icm_rounds_ = std::max(icm_rounds_, h.icm);
             icm_N_ = std::max(icm_N_, h.N);
         }
-        for (int64_t r = 0; r < h.Rcap; r += h.tile_rows) g.push_back(Work{ii, (uint32_t)r, 0u, 0u});
+        const uint32_t tiles = (uint32_t)((h.Rcap + h.tile_rows - 1) / h.tile_rows);
+        for (int64_t r = 0; r < h.Rcap; r += h.tile_rows) g.push_back(Work{ii, (uint32_t)r, 0u, tiles});
         for (int64_t r = 0; r < h.Rcap; r += kRowsPerBlock) {
             rows.push_back(Work{ii, (uint32_t)r, 0u, 0u});
             post.push_back(Work{ii, (uint32_t)r, kRoleCopies, 0u});
@@ -1271,10 +1311,15 @@ int Runner::set_state(int i, const pamc_state *st)
     HIPCHK(hipMemcpy(h.ctl, ctl, 12, hipMemcpyHostToDevice), "write ctl");
     HIPCHK(hipMemcpy(h.dev.status, status, 8, hipMemcpyHostToDevice), "write status");
     HIPCHK(hipMemcpy(h.dev.Rk + st->step, &Rk, 4, hipMemcpyHostToDevice), "write Rk");
-    // parts of the energy histogram, which a step that failed in its
-    // resampling or the last step left behind
-    HIPCHK(hipMemset(h.dev.hist, 0, (size_t)h.dev.nlev * 4), "clear the histogram");
-    HIPCHK(hipMemset(h.dev.loff, 0, (size_t)h.Rcap * 4), "clear the histogram");
+    // parts of the energy histogram or moments, which a step that failed in
+    // its resampling or the last step left behind
+    if (h.real) {
+        const std::vector<EMoments> em(kMomentParts, no_moments());
+        HIPCHK(hipMemcpy(h.dev.emom, em.data(), em.size() * sizeof(EMoments), hipMemcpyHostToDevice), "clear the moments");
+    } else {
+        HIPCHK(hipMemset(h.dev.hist, 0, (size_t)h.dev.nlev * 4), "clear the histogram");
+        HIPCHK(hipMemset(h.dev.loff, 0, (size_t)h.Rcap * 4), "clear the histogram");
+    }
     // energies from the spins (Eq. (1)) for the imported rows
     std::vector<Work> rows;
     for (int64_t r = 0; r < R; r += kRowsPerBlock) rows.push_back(Work{(uint32_t)i, (uint32_t)r, 0u, 0u});

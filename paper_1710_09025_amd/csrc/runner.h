@@ -30,7 +30,8 @@ struct HostInst {
     int srow_bytes = 0;                // bytes per stored spin row
     int tpr = 0;                       // real couplings: threads per replica quad
     int rp = 0;                        // replica quads a sweep workgroup holds at once
-    int mrep = 0, sets = 0;            // +-1 couplings: replicas per word, sets of them per pass of a workgroup
+    int mrep = 0, sets = 0;            // replicas per word, sets of them per pass of a workgroup
+    bool own_shape = false;            // the shape was asked for or measured: launches keep it
     int64_t R = 0, Rcap = 0;
     int nT = 0, NS = 0;
     uint64_t seed = 0;
@@ -60,7 +61,12 @@ inline void take_shape(HostInst &h, const HostInst &from)
     h.rp = from.rp;
     h.mrep = from.mrep;
     h.sets = from.sets;
+    h.own_shape = true;
 }
+
+// Sweep workgroup shape for instances of h's lattice with these populations
+// swept as one launch (tune.cpp).
+void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows);
 
 struct Allocator {
     void *(*alloc)(size_t, void *) = nullptr;

@@ -242,35 +242,7 @@ __device__ __forceinline__ uint32_t *hist_copy(const Inst &I, int c)
 
 // The buffer that holds the population once the sweeps of the step are done:
 // a sweep through the copy map wrote the other one, and the roles move on
-// when the post launch finishes (real couplings: when the sweep launch does).
+// when the post launch finishes.
 __device__ __forceinline__ int swept_buffer(const Inst &I) { return *I.cur ^ *I.mapped; }
-
-// Measurement of step k with real couplings, by the last sweep workgroup:
-// the energy moments the tiles accumulated (exact integers) go to the step
-// record and are reset for the next step; the weights and the normaliser
-// follow in the weights launch.  Moves the buffer roles on when the sweep
-// wrote the other buffer.
-__device__ __forceinline__ void measure_step_real(const Inst &I, int k)
-{
-    if (threadIdx.x != 0) return;
-    EMoments *m = I.emom;
-    StepRec *rec = I.rec + k;
-    rec->R = I.Rk[k];
-    rec->sumE = (int64_t)m->sum;
-    rec->sumE2 = m->sq_lo;
-    rec->sumE2_hi = (int64_t)m->sq_hi;
-    rec->Emin = m->emin;
-    rec->Emax = m->emax;
-    rec->S = __builtin_nan("");
-    m->emin = 0x7FFFFFFFFFFFFFFFll;
-    m->emax = -0x7FFFFFFFFFFFFFFFll - 1;
-    m->sum = 0ull;
-    m->sq_lo = 0ull;
-    m->sq_hi = 0ull;
-    if (*I.mapped) {
-        *I.cur ^= 1;
-        *I.mapped = 0;
-    }
-}
 
 }  // namespace pamc

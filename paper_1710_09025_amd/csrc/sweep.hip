@@ -7,8 +7,7 @@
 // from the final spins, and writes the rows back once.  When the previous
 // resampling left a copy map, the tile is read through it, so the gather of
 // surviving replicas costs no separate pass over HBM.  The epilogue adds the
-// tile to the step's energy moments and the family counts; the last workgroup
-// of an instance to finish then moves the moments to the step's record.
+// tile to the step's energy moments and the family counts.
 //
 // Random numbers: the draw for a site of colour c whose rank among the
 // sites of that colour is i, in replica row r, step k and sweep t, is word
@@ -185,16 +184,12 @@ __device__ __forceinline__ uint32_t lds_word(const uint8_t *lds, uint32_t a)
 // S S_nb = 1 - 2 sigma,
 //   dE = 2 S sum_d J_d S_d = 2 sum_d J_d - 4 sum_d sigma_d J_d,
 // where sigma_d J_d is the sign-extended byte ANDed with j.  Each
-// thread keeps the 4 NB neighbour addresses and couplings of its block of
-// every colour in registers (NB = 6 on the cubic lattice; the square-lattice
-// kernel reads the first NB = 4 directions of the same tables, whose z
-// entries are zero bonds).  Energy: every bond is seen from both of its
-// sites, so E = -sum_b J_b + sum over sites of sum_d sigma_d J_d.
+// thread keeps the 24 neighbour addresses and couplings of its block of every
+// colour in registers.  Energy: every bond is seen from both of its sites, so E = -sum_b J_b + sum over sites of sum_d sigma_d J_d.
 // ---------------------------------------------------------------------------
-template <int NB>
 struct CQBlock {
-    uint32_t nb[4 * NB];  // LDS offsets of the neighbour words, [direction][site]
-    int32_t j[4 * NB];    // coupling of each of those bonds (units of 2^-20)
+    uint32_t nb[24];  // LDS offsets of the neighbour words, [direction][site]
+    int32_t j[24];    // coupling of each of those bonds (units of 2^-20)
     int32_t j2[4];        // twice the sum of the couplings of each site
     uint32_t own;     // LDS offset of site 0's word (site i at + i plane_bytes)
     uint32_t vbits;   // bit i set when site i of the block is a real site
@@ -204,13 +199,12 @@ struct CQBlock {
 
 // sum_d sigma_d J_d of site i of block b for the four replicas (bytes of the
 // XOR words, 0x00 or 0xFF), given the site's own word.
-template <int NB>
-__device__ __forceinline__ void cq_field(const uint8_t *lds, const CQBlock<NB> &b, int i, uint32_t own,
+__device__ __forceinline__ void cq_field(const uint8_t *lds, const CQBlock &b, int i, uint32_t own,
                                          int32_t (&a)[4])
 {
     a[0] = a[1] = a[2] = a[3] = 0;
 #pragma unroll
-    for (int d = 0; d < NB; ++d) {
+    for (int d = 0; d < 6; ++d) {
         const uint32_t x = own ^ lds_word(lds, b.nb[4 * d + i]);
         const int32_t jj = b.j[4 * d + i];
 #pragma unroll
@@ -229,8 +223,8 @@ __device__ __forceinline__ uint4 spin_01(uint4 v)
     return make_uint4(v.x & 0x01010101u, v.y & 0x01010101u, v.z & 0x01010101u, v.w & 0x01010101u);
 }
 
-template <int NCOL, bool ALL, int NB>
-__device__ __forceinline__ void cq_passes(const Inst &I, int k, uint8_t *lds, const CQBlock<NB> (&blk)[NCOL], float bq,
+template <int NCOL, bool ALL>
+__device__ __forceinline__ void cq_passes(const Inst &I, int k, uint8_t *lds, const CQBlock (&blk)[NCOL], float bq,
                                           unsigned long long *eacc, const TileIO &io, int r0, int nrows, int phase)
 {
     const int tpr = I.tpr;
@@ -270,7 +264,7 @@ __device__ __forceinline__ void cq_passes(const Inst &I, int k, uint8_t *lds, co
         for (int t = phase_t0(I, phase); t < t1; ++t) {
 #pragma unroll
             for (int c = 0; c < NCOL; ++c) {
-                const CQBlock<NB> &b = blk[c];
+                const CQBlock &b = blk[c];
                 if (act && b.has) {
                     // raised issue priority for the field reads: a wave whose
                     // reads are due goes ahead of the others' multiply chains
@@ -284,7 +278,6 @@ __device__ __forceinline__ void cq_passes(const Inst &I, int k, uint8_t *lds, co
                     if constexpr (!ALL) {
                         // the fields (24 neighbour reads) before the draws,
                         // whose arithmetic then covers the reads' latency
-                        // (3-4% at L = 8, 12 and 32 in 2D)
                         int32_t aa[4][4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) cq_field(lds, b, i, own[i], aa[i]);
@@ -355,67 +348,7 @@ __device__ __forceinline__ void cq_passes(const Inst &I, int k, uint8_t *lds, co
     }
 }
 
-// Energies of the tile's rows (E = -sum_b J_b + the accumulated sums) and
-// their moments, added to the step's accumulators once per workgroup: min,
-// max, sum E (two's complement) and sum E^2 as an exact 128-bit integer
-// (low word added first; its carry goes into the high word).
-__device__ __forceinline__ void tile_moments_real(const Inst &I, const TileIO &io, const unsigned long long *eacc,
-                                                  int r0, int nrows)
-{
-    __shared__ long long smin[16], smax[16];
-    __shared__ unsigned long long ssum[16], slo[16], shi[16];
-    long long lmin = 0x7FFFFFFFFFFFFFFFll, lmax = -0x7FFFFFFFFFFFFFFFll - 1;
-    unsigned long long s1 = 0ull, lo = 0ull, hi = 0ull;
-    for (int q = threadIdx.x; q < nrows; q += blockDim.x) {
-        const long long E = (long long)eacc[q] - I.Jtot;
-        io.Eqdst[r0 + q] = E;
-        lmin = E < lmin ? E : lmin;
-        lmax = E > lmax ? E : lmax;
-        s1 += (unsigned long long)E;
-        const unsigned __int128 e2 = (unsigned __int128)((__int128)E * (__int128)E);
-        const unsigned long long l2 = (unsigned long long)e2;
-        const unsigned long long nl = lo + l2;
-        hi += (unsigned long long)(e2 >> 64) + (nl < lo ? 1ull : 0ull);
-        lo = nl;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const long long omin = __shfl_xor(lmin, off), omax = __shfl_xor(lmax, off);
-        const unsigned long long os = __shfl_xor(s1, off), ol = __shfl_xor(lo, off), oh = __shfl_xor(hi, off);
-        lmin = omin < lmin ? omin : lmin;
-        lmax = omax > lmax ? omax : lmax;
-        s1 += os;
-        const unsigned long long nl = lo + ol;
-        hi += oh + (nl < lo ? 1ull : 0ull);
-        lo = nl;
-    }
-    const int wave = threadIdx.x >> 6, nw = ((int)blockDim.x + 63) >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        smin[wave] = lmin;
-        smax[wave] = lmax;
-        ssum[wave] = s1;
-        slo[wave] = lo;
-        shi[wave] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < nw; ++v) {
-            lmin = smin[v] < lmin ? smin[v] : lmin;
-            lmax = smax[v] > lmax ? smax[v] : lmax;
-            s1 += ssum[v];
-            const unsigned long long nl = lo + slo[v];
-            hi += shi[v] + (nl < lo ? 1ull : 0ull);
-            lo = nl;
-        }
-        EMoments *m = I.emom;
-        atomicMin(&m->emin, lmin);
-        atomicMax(&m->emax, lmax);
-        atomicAdd(&m->sum, s1);
-        const unsigned long long old = atomicAdd(&m->sq_lo, lo);
-        atomicAdd(&m->sq_hi, hi + (old + lo < old ? 1ull : 0ull));
-    }
-}
-
-template <int NCOL, int NB>
+template <int NCOL>
 __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds, int r0, int nrows, int tile_rows,
                                               int phase)
 {
@@ -426,7 +359,7 @@ __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds
     const TileIO io = tile_io(I);
     const int lane_r = (int)threadIdx.x % tpr, qsub = (int)threadIdx.x / tpr;
     const uint32_t slot = (uint32_t)(qsub * I.slot_bytes);
-    CQBlock<NB> blk[NCOL];
+    CQBlock blk[NCOL];
 #pragma unroll
     for (int c = 0; c < NCOL; ++c) {
         const int g = lane_r;
@@ -436,7 +369,7 @@ __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds
         const uint16_t *d = I.cmdesc + ((size_t)c * I.gmax + gg) * 32;
         const int32_t *jd = I.cmj + ((size_t)c * I.gmax + gg) * 24;
 #pragma unroll
-        for (int i = 0; i < 4 * NB; ++i) {
+        for (int i = 0; i < 24; ++i) {
             blk[c].nb[i] = slot + quad_pos((uint32_t)d[i], (uint32_t)ps);
             blk[c].j[i] = jd[i];
         }
@@ -444,7 +377,7 @@ __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds
         for (int i = 0; i < 4; ++i) {
             int32_t s2 = 0;
 #pragma unroll
-            for (int dd = 0; dd < NB; ++dd) s2 += blk[c].j[4 * dd + i];
+            for (int dd = 0; dd < 6; ++dd) s2 += blk[c].j[4 * dd + i];
             blk[c].j2[i] = 2 * s2;
         }
         const uint32_t vm = blk[c].has ? (uint32_t)d[24] | ((uint32_t)d[25] << 16) : 0u;
@@ -456,14 +389,14 @@ __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds
     for (int q = threadIdx.x; q < tile_rows; q += blockDim.x) eacc[q] = 0ull;
     __syncthreads();
     if (all)
-        cq_passes<NCOL, true, NB>(I, k, lds, blk, bq, eacc, io, r0, nrows, phase);
+        cq_passes<NCOL, true>(I, k, lds, blk, bq, eacc, io, r0, nrows, phase);
     else
-        cq_passes<NCOL, false, NB>(I, k, lds, blk, bq, eacc, io, r0, nrows, phase);
+        cq_passes<NCOL, false>(I, k, lds, blk, bq, eacc, io, r0, nrows, phase);
     __syncthreads();
     if (io.map)
         for (int q = threadIdx.x; q < nrows; q += blockDim.x) io.fdst[r0 + q] = io.fsrc[io.map[r0 + q]];
     if (phase == 1) return;
-    tile_moments_real(I, io, eacc, r0, nrows);
+    tile_moments_real(I, io, eacc, r0, nrows, I.Jtot);
     __syncthreads();
     uint32_t *fam = reinterpret_cast<uint32_t *>(eacc);  // (the energies are out)
     for (int q = threadIdx.x; q < nrows; q += blockDim.x) fam[q] = io.fsrc[io.map ? io.map[r0 + q] : r0 + q];
@@ -482,30 +415,8 @@ __global__ __launch_bounds__(MAXT, 2) void k_sweep_cq(const Inst *insts, const W
     const int Rk = (int)I.Rk[k];
     const int r0 = (int)w.row0;
     const int nrows = min(tile_rows, Rk - r0);
-    if (nrows > 0) sweep_tile_cq<NCOL, 6>(I, k, lds, r0, nrows, tile_rows, phase);
-    if (phase == 1)
-        phase1_done(I);
-    else if (last_workgroup<false>(&I.sync[0], I.sweep_tiles))
-        measure_step_real(I, k);
-}
-
-// The same on the square lattice: four neighbours per site.
-template <int NCOL, int MAXT>
-__global__ __launch_bounds__(MAXT, 2) void k_sweep_sq(const Inst *insts, const Work *work, int tile_rows, int phase)
-{
-    extern __shared__ __align__(16) uint8_t lds[];
-    const Work w = work[blockIdx.x];
-    const Inst &I = inst_ref(insts, w.inst);
-    const int k = *I.k;
-    if (k >= I.nT || I.status[0]) return;
-    const int Rk = (int)I.Rk[k];
-    const int r0 = (int)w.row0;
-    const int nrows = min(tile_rows, Rk - r0);
-    if (nrows > 0) sweep_tile_cq<NCOL, 4>(I, k, lds, r0, nrows, tile_rows, phase);
-    if (phase == 1)
-        phase1_done(I);
-    else if (last_workgroup<false>(&I.sync[0], I.sweep_tiles))
-        measure_step_real(I, k);
+    if (nrows > 0) sweep_tile_cq<NCOL>(I, k, lds, r0, nrows, tile_rows, phase);
+    if (phase == 1) phase1_done(I, w.n);
 }
 
 // ---------------------------------------------------------------------------
@@ -513,13 +424,12 @@ __global__ __launch_bounds__(MAXT, 2) void k_sweep_sq(const Inst *insts, const W
 // ---------------------------------------------------------------------------
 hipError_t sweep_kernels_init()
 {
-    const hipError_t r = sweep_rb_init();
+    hipError_t r = sweep_rb_init();
+    if (r == hipSuccess) r = sweep_rq_init();
     if (r != hipSuccess) return r;
     const void *fns[] = {
         reinterpret_cast<const void *>(&k_sweep_cq<2, 512>), reinterpret_cast<const void *>(&k_sweep_cq<2, 1024>),
         reinterpret_cast<const void *>(&k_sweep_cq<3, 512>), reinterpret_cast<const void *>(&k_sweep_cq<3, 1024>),
-        reinterpret_cast<const void *>(&k_sweep_sq<2, 512>), reinterpret_cast<const void *>(&k_sweep_sq<2, 1024>),
-        reinterpret_cast<const void *>(&k_sweep_sq<3, 512>), reinterpret_cast<const void *>(&k_sweep_sq<3, 1024>),
     };
     for (const void *f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSweepLds);
@@ -577,21 +487,8 @@ void launch_sweep(const SweepShape &sh, const Inst *insts, const Work *work, int
         launch_sweep_rb(sh, insts, work, nwork, phase, st);
         return;
     }
-    if (variant == kSweepSQ2 || variant == kSweepSQ3) {
-        // as below, on the square lattice
-        const size_t lds = (size_t)cm_slot_bytes(row_bytes, tpr, 4) * rp + 32 + 8 * (size_t)tile_rows;
-        const int nt = cm_launch_threads(tpr, rp);
-        if (variant == kSweepSQ2) {
-            if (nt <= 512)
-                k_sweep_sq<2, 512><<<nwork, nt, lds, st>>>(insts, work, tile_rows, phase);
-            else
-                k_sweep_sq<2, 1024><<<nwork, nt, lds, st>>>(insts, work, tile_rows, phase);
-        } else {
-            if (nt <= 512)
-                k_sweep_sq<3, 512><<<nwork, nt, lds, st>>>(insts, work, tile_rows, phase);
-            else
-                k_sweep_sq<3, 1024><<<nwork, nt, lds, st>>>(insts, work, tile_rows, phase);
-        }
+    if (is_rq(variant)) {
+        launch_sweep_rq(sh, insts, work, nwork, phase, st);
         return;
     }
     if (variant == kSweepCQ2 || variant == kSweepCQ3) {

@@ -45,20 +45,36 @@ constexpr int kTimedSteps = 3;      // timed steps per candidate shape (after on
 constexpr int kBurnIn = 8;          // steps before the first candidate
 constexpr double kTuneBeta = 2.0;   // inside the low-temperature part where an anneal spends most steps
 
+constexpr int kMaxWord = 32;        // replicas per word
+
 bool is_rb(const HostInst &h) { return h.variant == kSweepRB; }
+// replicas as bits of a word, +-1 or real couplings
+bool is_words(const HostInst &h) { return is_rb(h) || is_rq(h.variant); }
 
 // Philox blocks of the largest colour.
 int max_blocks(const HostInst &h) { return layout_for(h.L, h.real != 0, h.dim).gmax; }
 
+// The word kernels' launch: threads and LDS of a workgroup of `sets` sets, the
+// waves a compute unit holds (80 or 128 registers a lane).
+bool words_uniform(const HostInst &h, int G) { return is_rb(h) ? rb_uniform(G) : rq_uniform(G); }
+int words_threads(const HostInst &h, int G, int sets) { return is_rb(h) ? rb_threads(G, sets) : rq_threads(G, sets); }
+int64_t words_lds(const HostInst &h, int m, int sets)
+{
+    const int plane = rb_plane(h.row_bytes);
+    return is_rb(h) ? (int64_t)rb_lds(plane, sets) : rq_lds(h.variant, plane, m, sets);
+}
+int64_t words_max_lds(const HostInst &h) { return is_rb(h) ? kMaxLds : kMaxWordLds; }
+int words_cu_waves(const HostInst &h) { return is_rb(h) ? 24 : 16; }
+
 // Dynamic LDS of a sweep workgroup.
 int64_t sweep_lds(const HostInst &h)
 {
-    if (is_rb(h)) return (int64_t)rb_lds(rb_plane(h.row_bytes), h.sets);
+    if (is_words(h)) return words_lds(h, h.mrep, h.sets);
     return (int64_t)cm_slot_bytes(h.row_bytes, h.tpr, 4) * h.rp + 32 + 8 * (int64_t)h.tile_rows;
 }
 
-// A +-1 shape: m replicas per word, `sets` sets per pass, tile_rows rows per
-// workgroup.  rp, reported as group_replicas = 4 rp, is 0 where the caller
+// A shape of words: m replicas per word, `sets` sets per pass, tile_rows rows
+// per workgroup.  rp, reported as group_replicas = 4 rp, is 0 where the caller
 // cannot choose it.
 bool fixed_group(const HostInst &h) { return is_rb(h) && (h.L == 8 || h.L == 16 || h.L > 21 || (h.L > 20 && h.L % 2 == 0)); }
 void set_rb(HostInst &h, int m, int sets, int tile_rows)
@@ -76,10 +92,9 @@ struct Choice {
 
 using Key = std::tuple<int, int, int, int, int, int>;  // variant, dim, L, sweeps, log2 capacity, packed
 
-// The variant a +-1 choice is stored under tells the replicas per word
-// (kSweepRB + m, m <= kMaxWord); its workgroups sweep tile_rows = m sets rows
-// in one pass.
-constexpr int kMaxWord = 32;
+// The variant a choice of words is stored under tells the replicas per word
+// (kSweepRB + m, m <= kMaxWord; the variants are 64 apart); its workgroups
+// sweep tile_rows = m sets rows in one pass.
 
 std::mutex g_mu;
 std::map<std::pair<std::string, Key>, Choice> g_cache;  // by device and key
@@ -119,10 +134,11 @@ void load_file(const std::string &path)
         double npa;
         if (std::sscanf(line, kLineFmt, dev, &v, &d, &L, &ns, &cl, &pk, &tr, &rp, &npa) != 10) continue;
         Choice c{tr, rp, 0, 0, npa};
-        if (v > kSweepRB && v <= kSweepRB + kMaxWord) {
-            c.mrep = v - kSweepRB;
+        if (v >= kSweepRB) {
+            c.mrep = v % 64;
+            if (c.mrep < 1) continue;
             c.sets = tr / c.mrep;
-            v = kSweepRB;
+            v -= c.mrep;
         }
         g_cache[{dev, Key(v, d, L, ns, cl, pk)}] = c;
     }
@@ -177,30 +193,31 @@ bool shape_valid(const HostInst &h, const char **why)
     const char *w = nullptr;
     if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
-    } else if (is_rb(h)) {
+    } else if (is_words(h)) {
         const int G = max_blocks(h);
-        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (rb_uniform(G) && h.sets != 1) || rb_threads(G, h.sets) > 1024)
+        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (is_rb(h) && rb_uniform(G) && h.sets != 1) ||
+            words_threads(h, G, h.sets) > 1024)
             w = "no such grouping of replicas";
     } else if (h.rp < 1 || (h.tpr <= 64 && (h.tpr * h.rp) % 64 != 0) || cm_launch_threads(h.tpr, h.rp) > 1024) {
         w = "group_replicas must be a multiple of four giving at most 1024 threads (whole waves when a quad "
             "takes at most 64)";
     }
-    if (!w && sweep_lds(h) > kMaxLds) w = "the workgroup's tile does not fit in LDS";
+    if (!w && sweep_lds(h) > (is_words(h) ? words_max_lds(h) : kMaxLds)) w = "the workgroup's tile does not fit in LDS";
     if (why) *why = w;
     return w == nullptr;
 }
 
-// Sets of a +-1 workgroup of about `threads` threads: one where a set fills
-// whole waves, else the count up to that size (at least one) with the fewest
-// idle lanes.
-static int rb_sets(int G, int plane, int threads)
+// Sets of a workgroup of about `threads` threads: with +-1 couplings one where
+// a set fills whole waves; else the count up to that size (at least one) with
+// the fewest idle lanes.
+static int words_sets(const HostInst &h, int G, int threads)
 {
     int best = 1;
     double best_use = 0.0;
-    if (rb_uniform(G)) return 1;
-    for (int s = 1; rb_threads(G, s) <= std::min(1024, std::max(threads, rb_threads(G, 1))); ++s) {
-        if ((int64_t)rb_lds(plane, s) > kMaxLds) break;
-        const double use = (double)G * s / rb_threads(G, s);
+    if (is_rb(h) && rb_uniform(G)) return 1;
+    for (int s = 1; words_threads(h, G, s) <= std::min(1024, std::max(threads, words_threads(h, G, 1))); ++s) {
+        if (words_lds(h, kMaxWord, s) > words_max_lds(h)) break;
+        const double use = (double)G * s / words_threads(h, G, s);
         if (use >= best_use - 0.005) {
             best = s;
             best_use = std::max(use, best_use);
@@ -209,48 +226,59 @@ static int rb_sets(int G, int plane, int threads)
     return best;
 }
 
-// Workgroups of nt threads and lds bytes a compute unit holds at once: 24
-// waves (80 registers a lane), 160 KB of LDS.
+// Workgroups of nt threads and lds bytes a compute unit holds at once.
 constexpr int kCU = 256;
-static int rb_per_cu(int nt, int64_t lds)
+static int words_per_cu(const HostInst &h, int nt, int64_t lds)
 {
-    return std::max<int>(1, (int)std::min<int64_t>(24 / (nt / 64), 160 * 1024 / (lds + 512)));
+    return std::max<int>(1, (int)std::min<int64_t>(words_cu_waves(h) / (nt / 64), 160 * 1024 / (lds + 512)));
 }
-// Replicas per word worth trying (the table mode draws for four at a time).
-constexpr int kWords[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
-
 // The shape used without tuning.
-//   +-1 couplings: the sets and the replicas per word m that give the shortest
-// launch by what a colour step of a lane issues, about 190 instructions for
-// its fields and 42 per draw, at 4.45 cycles an instruction for each of the
+//   Words: the sets and the replicas per word m that give the shortest launch
+// by what a colour step of a lane issues, about a instructions for its fields
+// and b per draw of four sites, at 4.45 cycles an instruction for each of the
 // waves that share a SIMD (6 for one, 9.3 for two).  Large words save fields,
 // small ones fill the chip and its last round of workgroups.  The figures are
-// measured; over 28 sizes from L = 4, R = 10^3 to L = 16, R = 5 10^5 the shape
-// chosen is within 10% of the best of all that can be tried.
-//   Real couplings: enough workgroups to fill the chip when the population
-// is small, up to four passes per workgroup when it is large.
-void default_shape(HostInst &h, int gmax)
+// measured; over 28 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
+// R = 5 10^5 the shape chosen is within 10% of the best of all that can be
+// tried.
+//   Quads (real couplings, L > 13): enough workgroups to fill the chip when
+// the population is small, up to four passes per workgroup when it is large.
+void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
 {
-    if (is_rb(h)) {
-        const int plane = rb_plane(h.row_bytes);
+    if (is_words(h)) {
+        const int64_t most = *std::max_element(rows.begin(), rows.end());
         double best = INFINITY;
         int last = 0;
-        for (int threads : {64, 256, 1024}) {
-            const int sets = rb_sets(gmax, plane, threads);
+        for (int threads : {64, 256, 512, 1024}) {
+            if (is_rb(h) && threads == 512) continue;
+            const int sets = words_sets(h, gmax, threads);
             if (sets == last) continue;
             last = sets;
-            const int nt = rb_threads(gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
-            const int per_cu = rb_per_cu(nt, (int64_t)rb_lds(plane, sets));
-            for (int m : kWords) {
-                if (m > 4 && m * sets > h.R) break;
-                const int64_t wgs = (h.R + m * sets - 1) / (m * sets), round = (int64_t)kCU * per_cu;
+            const int nt = words_threads(h, gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
+            for (int m = 1; m <= kMaxWord; ++m) {
+                if (m > 4 && m * sets > most) break;
+                // (+-1 couplings: the table mode draws for four at a time)
+                if (is_rb(h) && m > 2 && m % 4 != 0) continue;
+                const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets));
+                // instructions of a lane's colour step: fields, and draws
+                // and decisions of four sites; tables, once a launch
+                double a = 190.0, b = 42.0, once = 0.0;
+                if (!is_rb(h)) {
+                    const bool thr = rq_kind(h.variant, m * sets) == kRQThr;
+                    a = m <= 4 ? 120.0 : 320.0;
+                    b = (thr ? 62.0 : 105.0) + (m <= 4 ? 48.0 : 0.0);
+                    once = (double)h.N / nt * (thr ? h.dim == 3 ? 1400.0 : 400.0 : 150.0) / (h.NS * h.ncol);
+                }
+                const int64_t round = (int64_t)kCU * per_cu;
+                int64_t wgs = 0;
+                for (int64_t r : rows) wgs += (r + m * sets - 1) / (m * sets);
                 // cycles per instruction of a lane's colour step with n
                 // workgroups on the chip, from the waves that share a SIMD
                 auto cycles = [&](int64_t n) {
                     const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
                     return w == 0 ? 0.0 : w == 1 ? 6.0 : w == 2 ? 9.3 : 4.45 * (double)w;
                 };
-                const double t = (190.0 + 42.0 * m) * blocks *
+                const double t = ((a + b * m) * blocks + once) *
                                  ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
                 if (t < 0.98 * best) {
                     best = t;
@@ -267,16 +295,16 @@ void default_shape(HostInst &h, int gmax)
 }
 
 // The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
-// With +-1 couplings the options keep the ranges documented for them: quads
-// of replicas in byte planes, tiles that fit the workgroup's LDS at one byte
-// per spin (and, L = 8 and 16, whole passes of 8 and 2 rows; group_replicas
-// is ignored there and where a lattice has no quads).  The words of M
-// replicas then take as many of the group's replicas as they can.
+// For words the options keep the ranges documented for them: quads of
+// replicas in byte planes, tiles that fit the workgroup's LDS at one byte per
+// spin (and with +-1 couplings, L = 8 and 16, whole passes of 8 and 2 rows;
+// group_replicas is ignored there and where a lattice has no quads).  The
+// words of M replicas then take as many of the group's replicas as they can.
 // h holds the default shape on entry.
 bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why)
 {
     const char *w = nullptr;
-    if (!is_rb(h)) {
+    if (!is_words(h)) {
         const int rp = group_replicas > 0 ? group_replicas / 4 : h.rp;
         // without an explicit tile: the default number of passes per workgroup
         h.tile_rows = tile_rows > 0 ? tile_rows : h.tile_rows / h.rp * rp;
@@ -285,7 +313,7 @@ bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, co
     }
     int group = 0;
     const int rb = h.row_bytes;
-    if (h.L == 8 || h.L == 16) {
+    if (is_rb(h) && (h.L == 8 || h.L == 16)) {
         const int p = h.L == 8 ? 8 : 2;
         tile_rows = (tile_rows + p - 1) / p * p;
         if (tile_rows > 4096)
@@ -299,25 +327,31 @@ bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, co
         const int rp0 = cm_replicas_per_block(h.tpr), rp = group_replicas > 0 ? group_replicas / 4 : rp0;
         const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (512 * 4 * rp0)));
         if (tile_rows <= 0) tile_rows = (int)m * 4 * rp;
-        int64_t table = h.ncol == 3 ? 16 + 144 * h.tpr : h.tpr <= 128 ? 16 + 96 * h.tpr : 0;
-        const int64_t slot = cm_slot_bytes(rb, h.tpr, 8);
-        if (slot * rp0 + 32 + 4 * 64 + table > kMaxLds || 8 * (int64_t)cm_plane_bytes(rb) > 65536) table = 0;
+        const int64_t slot = cm_slot_bytes(rb, h.tpr, is_rb(h) ? 8 : 4);
+        int64_t table = 0;
+        if (is_rb(h)) {
+            table = h.ncol == 3 ? 16 + 144 * h.tpr : h.tpr <= 128 ? 16 + 96 * h.tpr : 0;
+            if (slot * rp0 + 32 + 4 * 64 + table > kMaxLds || 8 * (int64_t)cm_plane_bytes(rb) > 65536) table = 0;
+        }
         group = 4 * rp;
         if (tile_rows > 4096)
             w = "tile_rows must be in [1, 4096]";
         else if (rp < 1 || (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) || cm_launch_threads(h.tpr, rp) > 1024)
             w = "group_replicas must be a multiple of four giving at most 1024 threads (whole waves when a quad "
                 "takes at most 64)";
-        else if (slot * rp + 32 + 4 * (int64_t)tile_rows + table > kMaxLds)
+        else if (slot * rp + 32 + (is_rb(h) ? 4 : 8) * (int64_t)tile_rows + table > kMaxLds)
             w = "the workgroup's tile does not fit in LDS";
     }
     if (why) *why = w;
     if (w) return false;
     const int rows = group > 0 ? std::min(group, tile_rows) : tile_rows;
-    const int m = std::min(rows, kMaxWord), plane = rb_plane(rb);
-    set_rb(h, m, std::max(1, std::min(rb_sets(gmax, plane, 256), rows / m)), tile_rows);
+    const int m = std::min(rows, kMaxWord);
+    set_rb(h, m, std::max(1, std::min(words_sets(h, gmax, is_rb(h) ? 256 : 1024), rows / m)), tile_rows);
     return shape_valid(h, why);
 }
+
+// Replicas per word worth trying.
+constexpr int kWords[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
 
 static std::vector<HostInst> shape_candidates(const HostInst &h)
 {
@@ -331,11 +365,11 @@ static std::vector<HostInst> shape_candidates(const HostInst &h)
     t.row_bytes = h.row_bytes;
     t.real = h.real;
     t.tpr = h.tpr;
-    if (is_rb(h)) {
-        const int G = max_blocks(h), plane = rb_plane(h.row_bytes);
+    if (is_words(h)) {
+        const int G = max_blocks(h);
         int last = 0;
         for (int threads : {64, 128, 256, 512, 1024}) {
-            const int sets = rb_sets(G, plane, threads);
+            const int sets = words_sets(h, G, threads);
             if (sets == last) continue;
             last = sets;
             for (int m : kWords) {
@@ -458,6 +492,7 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
     h.rp = best.rp;
     h.mrep = best.mrep;
     h.sets = best.sets;
+    h.own_shape = true;
     if (ns_per_attempt) *ns_per_attempt = best.ns_per_attempt;
     return PAMC_OK;
 }
