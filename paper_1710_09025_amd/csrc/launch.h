@@ -127,6 +127,10 @@ void launch_post(const Inst *insts, const Work *work, int nwork, hipStream_t st)
 // copy map of the resampling just done
 void launch_expand(const Inst *insts, const Work *work, int nwork, hipStream_t st);
 void launch_gather(const Inst *insts, const Work *work, int nwork, hipStream_t st);
+// rows [row0, row0 + rows) of the current buffer as +-1 bytes in lexicographic
+// order (4-byte aligned `out`), and such rows into buffer 0
+void launch_export(const Inst *inst, int N, int8_t *out, int row0, int rows, hipStream_t st);
+void launch_import(const Inst *inst, int srow_bytes, const int8_t *in, int row0, int rows, hipStream_t st);
 void launch_flip(const Inst *insts, const uint32_t *list, int n, hipStream_t st);
 
 }  // namespace pamc

@@ -1218,6 +1218,21 @@ int Runner::materialise(int i)
     return PAMC_OK;
 }
 
+// Where rows of +-1 bytes pass between the caller and population buffer b
+// (idle): the buffer itself, or memory for one row where it does not hold one
+// (a few packed rows).
+Runner::StateStage Runner::state_stage(const HostInst &h, int b)
+{
+    StateStage s{(int8_t *)h.dev.spins[b], nullptr, h.Rcap * h.srow_bytes / h.N};
+    if (s.rows == 0) {
+        s.own = alloc_.get((size_t)h.N);
+        s.p = (int8_t *)s.own;
+        s.rows = 1;
+        if (!s.p) set_error("state staging allocation failed");
+    }
+    return s;
+}
+
 int Runner::get_state(int i, pamc_state *stt)
 {
     HostInst &h = inst_[i];
@@ -1249,17 +1264,20 @@ int Runner::get_state(int i, pamc_state *stt)
     }
     const int cur = ctl[1];
     if (stt->spins) {
-        std::vector<uint8_t> buf((size_t)Rk * h.srow_bytes);
-        HIPCHK(hipMemcpy(buf.data(), h.dev.spins[cur], buf.size(), hipMemcpyDeviceToHost), "read spins");
-        for (uint32_t r = 0; r < Rk; ++r) {
-            const uint8_t *row = buf.data() + (size_t)r * h.srow_bytes;
-            int8_t *o = stt->spins + (size_t)r * h.N;
-            for (int s = 0; s < h.N; ++s) {
-                const int p = h.lex_pos[s];
-                const int up = h.packed ? (row[p >> 3] >> (p & 7)) & 1 : row[p];
-                o[s] = up ? 1 : -1;
-            }
+        // through the idle buffer, as many rows at a time as it holds
+        const StateStage stage = state_stage(h, cur ^ 1);
+        if (!stage.p) return PAMC_ERR_NOMEM;
+        for (int64_t r = 0; st == PAMC_OK && r < (int64_t)Rk; r += stage.rows) {
+            const int n = (int)std::min<int64_t>(stage.rows, (int64_t)Rk - r);
+            launch_export(d_insts_ + i, h.N, stage.p, (int)r, n, stream_);
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(stt->spins + (size_t)r * h.N, stage.p, (size_t)n * h.N, hipMemcpyDeviceToHost, stream_);
+            if (e == hipSuccess) e = hipStreamSynchronize(stream_);
+            if (e != hipSuccess) st = dev_fail(e, "read spins");
         }
+        alloc_.put(stage.own);
+        if (st != PAMC_OK) return st;
     }
     if (h.real) {
         if (stt->E_fixed)
@@ -1280,21 +1298,13 @@ int Runner::set_state(int i, const pamc_state *st)
         return PAMC_ERR_INVALID;
     }
     const int64_t R = st->R;
-    std::vector<uint8_t> buf((size_t)R * h.srow_bytes, 0);
     for (int64_t r = 0; r < R; ++r) {
         const int8_t *in = st->spins + (size_t)r * h.N;
-        uint8_t *row = buf.data() + (size_t)r * h.srow_bytes;
-        for (int s = 0; s < h.N; ++s) {
-            if (in[s] != 1 && in[s] != -1) {
-                set_error("set_state: spins must be +-1");
-                return PAMC_ERR_INVALID;
-            }
-            const int p = h.lex_pos[s];
-            if (h.packed) {
-                if (in[s] > 0) row[p >> 3] |= (uint8_t)(1u << (p & 7));
-            } else {
-                row[p] = in[s] > 0 ? 1 : 0;
-            }
+        uint32_t bad = 0;
+        for (int s = 0; s < h.N; ++s) bad |= (uint32_t)(uint8_t)(in[s] + 1) & 0xFDu;
+        if (bad) {
+            set_error("set_state: spins must be +-1");
+            return PAMC_ERR_INVALID;
         }
         if ((int64_t)st->family[r] >= h.R) {
             set_error("set_state: family id out of range");
@@ -1306,7 +1316,20 @@ int Runner::set_state(int i, const pamc_state *st)
     const int32_t ctl[3] = {st->step, 0, 0};
     const uint32_t status[2] = {0, 0};
     const uint32_t Rk = (uint32_t)R;
-    HIPCHK(hipMemcpy(h.dev.spins[0], buf.data(), buf.size(), hipMemcpyHostToDevice), "write spins");
+    const StateStage stage = state_stage(h, 1);
+    if (!stage.p) return PAMC_ERR_NOMEM;
+    for (int64_t r = 0; stt == PAMC_OK && r < R; r += stage.rows) {
+        const int n = (int)std::min<int64_t>(stage.rows, R - r);
+        hipError_t e = hipMemcpyAsync(stage.p, st->spins + (size_t)r * h.N, (size_t)n * h.N, hipMemcpyHostToDevice, stream_);
+        if (e == hipSuccess) {
+            launch_import(d_insts_ + i, h.srow_bytes, stage.p, (int)r, n, stream_);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(stream_);
+        if (e != hipSuccess) stt = dev_fail(e, "write spins");
+    }
+    alloc_.put(stage.own);
+    if (stt != PAMC_OK) return stt;
     HIPCHK(hipMemcpy(h.dev.fam[0], st->family, (size_t)R * 4, hipMemcpyHostToDevice), "write family");
     HIPCHK(hipMemcpy(h.ctl, ctl, 12, hipMemcpyHostToDevice), "write ctl");
     HIPCHK(hipMemcpy(h.dev.status, status, 8, hipMemcpyHostToDevice), "write status");

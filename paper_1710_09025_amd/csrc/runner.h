@@ -124,6 +124,12 @@ public:
     int get_state(int i, pamc_state *st);
     int set_state(int i, const pamc_state *st);
     int thresholds(int i, uint32_t *out, uint8_t *acc);
+    struct StateStage {
+        int8_t *p;
+        void *own;     // to be released
+        int64_t rows;  // rows it holds
+    };
+    StateStage state_stage(const HostInst &h, int b);
     // Changes the sweep workgroup shape of slot i (between steps; results
     // do not depend on it) and rebuilds the work lists of the active set.
     int set_shape(int i, const HostInst &shape);

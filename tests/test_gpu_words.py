@@ -24,6 +24,8 @@ CASES = [
     ("pm", 3, 7, 130, 9, 3, 3.0, dict(tile_rows=63, group_replicas=32, packed=True)),
     ("pm", 3, 23, 5, 3, 2, 3.0, {}),
     ("pm", 3, 28, 3, 3, 2, 3.0, dict(packed=True)),
+    # (a population buffer that holds less than one exported row)
+    ("pm", 3, 28, 3, 3, 2, 0.01, dict(packed=True, capacity=6)),
     ("pm", 3, 4, 31300, 3, 1, 1.0, dict(capacity=32768)),
     ("pm", 3, 4, 31300, 3, 1, 1.0, dict(capacity=32769)),
     # real: few and many replicas a word, bond sums and thresholds, at the last
