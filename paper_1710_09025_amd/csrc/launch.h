@@ -27,6 +27,7 @@ struct SweepShape {
     int variant = 0, tile_rows = 0, row_bytes = 0;
     int tpr = 0, rp = 0;  // CQ: threads per replica quad, quads per workgroup
     int G = 0, plane = 0; // RB, RQ: Philox blocks of the largest colour, words per site plane
+    int ncol = 0;         // colours
     int M = 0, sets = 0;  // RB, RQ: replicas per word, sets (of M replicas) per pass of a workgroup
 };
 
@@ -75,6 +76,11 @@ inline int rb_plane(int row_bytes) { return row_bytes <= 128 ? row_bytes / 4 : (
 bool rb_uniform(int G);
 int rb_threads(int G, int sets);
 size_t rb_lds(int plane, int sets);
+// Its form for up to kSmallWord replicas a word (and at most 512 threads), in
+// the same workgroups of threads: whether a shape takes it, and its LDS.
+constexpr int kSmallWord = 4;
+bool rs_small(int G, int m, int sets);
+size_t rs_lds(int plane, int G, int sets);
 // The same with real couplings, the tables included (thresholds or bond sums
 // by the rows of a pass).  These kernels have
 // little LDS of their own.
@@ -112,6 +118,8 @@ void launch_energy(const Inst *insts, const Work *work, int nwork, const int8_t 
 void launch_sweep(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 void launch_sweep_rb(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 hipError_t sweep_rb_init();
+void launch_sweep_rs(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
+hipError_t sweep_rs_init();
 void launch_sweep_rq(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 hipError_t sweep_rq_init();
 // resampling weights and their normaliser (instances with real couplings;

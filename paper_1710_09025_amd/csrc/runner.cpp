@@ -779,6 +779,7 @@ int Runner::build_work(const std::vector<int> &active)
         sh.rp = h.rp;
         sh.G = h.dev.gmax;
         sh.plane = h.dev.rb_plane;
+        sh.ncol = h.ncol;
         sh.M = h.mrep;
         sh.sets = h.sets;
         if (h.icm > 0) {

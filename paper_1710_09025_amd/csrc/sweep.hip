@@ -425,6 +425,7 @@ __global__ __launch_bounds__(MAXT, 2) void k_sweep_cq(const Inst *insts, const W
 hipError_t sweep_kernels_init()
 {
     hipError_t r = sweep_rb_init();
+    if (r == hipSuccess) r = sweep_rs_init();
     if (r == hipSuccess) r = sweep_rq_init();
     if (r != hipSuccess) return r;
     const void *fns[] = {
@@ -484,7 +485,10 @@ void launch_sweep(const SweepShape &sh, const Inst *insts, const Work *work, int
     if (!nwork) return;
     const int variant = sh.variant, tile_rows = sh.tile_rows, row_bytes = sh.row_bytes, tpr = sh.tpr, rp = sh.rp;
     if (variant == kSweepRB) {
-        launch_sweep_rb(sh, insts, work, nwork, phase, st);
+        if (rs_small(sh.G, sh.M, sh.sets))
+            launch_sweep_rs(sh, insts, work, nwork, phase, st);
+        else
+            launch_sweep_rb(sh, insts, work, nwork, phase, st);
         return;
     }
     if (is_rq(variant)) {

@@ -55,16 +55,17 @@ bool is_words(const HostInst &h) { return is_rb(h) || is_rq(h.variant); }
 int max_blocks(const HostInst &h) { return layout_for(h.L, h.real != 0, h.dim).gmax; }
 
 // The word kernels' launch: threads and LDS of a workgroup of `sets` sets, the
-// waves a compute unit holds (80 or 128 registers a lane).
+// waves a compute unit holds (80 to 188 registers a lane).
 bool words_uniform(const HostInst &h, int G) { return is_rb(h) ? rb_uniform(G) : rq_uniform(G); }
 int words_threads(const HostInst &h, int G, int sets) { return is_rb(h) ? rb_threads(G, sets) : rq_threads(G, sets); }
 int64_t words_lds(const HostInst &h, int m, int sets)
 {
-    const int plane = rb_plane(h.row_bytes);
-    return is_rb(h) ? (int64_t)rb_lds(plane, sets) : rq_lds(h.variant, plane, m, sets);
+    const int plane = rb_plane(h.row_bytes), G = max_blocks(h);
+    if (!is_rb(h)) return rq_lds(h.variant, plane, m, sets);
+    return (int64_t)(rs_small(G, m, sets) ? rs_lds(plane, G, sets) : rb_lds(plane, sets));
 }
 int64_t words_max_lds(const HostInst &h) { return is_rb(h) ? kMaxLds : kMaxWordLds; }
-int words_cu_waves(const HostInst &h) { return is_rb(h) ? 24 : 16; }
+int words_cu_waves(const HostInst &h, bool small) { return !is_rb(h) ? 16 : !small ? 24 : h.ncol == 2 ? 12 : 8; }
 
 // Dynamic LDS of a sweep workgroup.
 int64_t sweep_lds(const HostInst &h)
@@ -226,21 +227,27 @@ static int words_sets(const HostInst &h, int G, int threads)
     return best;
 }
 
-// Workgroups of nt threads and lds bytes a compute unit holds at once.
+// Workgroups of nt threads and lds bytes a compute unit holds at once.  (At two
+// or three waves a SIMD, a workgroup whose waves do not divide among the four
+// SIMDs leaves room that the next one cannot take.)
 constexpr int kCU = 256;
-static int words_per_cu(const HostInst &h, int nt, int64_t lds)
+static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 {
-    return std::max<int>(1, (int)std::min<int64_t>(words_cu_waves(h) / (nt / 64), 160 * 1024 / (lds + 512)));
+    const int waves = nt / 64, most = words_cu_waves(h, small);
+    const int n = small && waves > 4 ? most / 4 / ((waves + 3) / 4) : most / waves;
+    return std::max<int>(1, (int)std::min<int64_t>(n, 160 * 1024 / (lds + 512)));
 }
+
 // The shape used without tuning.
 //   Words: the sets and the replicas per word m that give the shortest launch
 // by what a colour step of a lane issues, about a instructions for its fields
 // and b per draw of four sites, at 4.45 cycles an instruction for each of the
-// waves that share a SIMD (6 for one, 9.3 for two).  Large words save fields,
+// waves that share a SIMD (6 or 8 for one, 9.3 for two; the small words of
+// sweep_rs.hip 6.3, 8.2 and 3.6 each).  Large words save fields,
 // small ones fill the chip and its last round of workgroups.  The figures are
-// measured; over 28 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
-// R = 5 10^5 the shape chosen is within 10% of the best of all that can be
-// tried.
+// measured; over 36 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
+// R = 5 10^4 and L = 32, R = 50 the shape chosen is within 10% of the best of
+// all that can be tried.
 //   Quads (real couplings, L > 13): enough workgroups to fill the chip when
 // the population is small, up to four passes per workgroup when it is large.
 void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
@@ -259,10 +266,11 @@ void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
                 if (m > 4 && m * sets > most) break;
                 // (+-1 couplings: the table mode draws for four at a time)
                 if (is_rb(h) && m > 2 && m % 4 != 0) continue;
-                const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets));
+                const bool small = is_rb(h) && rs_small(gmax, m, sets);
+                const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
                 // instructions of a lane's colour step: fields, and draws
                 // and decisions of four sites; tables, once a launch
-                double a = 190.0, b = 42.0, once = 0.0;
+                double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
                 if (!is_rb(h)) {
                     const bool thr = rq_kind(h.variant, m * sets) == kRQThr;
                     a = m <= 4 ? 120.0 : 320.0;
@@ -276,7 +284,8 @@ void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
                 // workgroups on the chip, from the waves that share a SIMD
                 auto cycles = [&](int64_t n) {
                     const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
-                    return w == 0 ? 0.0 : w == 1 ? 6.0 : w == 2 ? 9.3 : 4.45 * (double)w;
+                    if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
+                    return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
                 };
                 const double t = ((a + b * m) * blocks + once) *
                                  ((double)(wgs / round) * cycles(round) + cycles(wgs % round));

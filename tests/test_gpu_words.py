@@ -2,7 +2,7 @@
 of their shapes: words of 1 to 32 replicas, full and partial sets, passes that
 end inside a word, site blocks that leave lanes idle, the largest lattices
 each table of site thresholds or bond sums fits, and populations around the
-size where energies are counted in a histogram.  Spins, energies, families and
+sizes where the statistics change their ways.  Spins, energies, families and
 integer records bit for bit, observables within 1e-12 (the oracle's
 arithmetic is the same up to the order of a few sums)."""
 import numpy as np
@@ -28,6 +28,16 @@ CASES = [
     ("pm", 3, 28, 3, 3, 2, 0.01, dict(packed=True, capacity=6)),
     ("pm", 3, 4, 31300, 3, 1, 1.0, dict(capacity=32768)),
     ("pm", 3, 4, 31300, 3, 1, 1.0, dict(capacity=32769)),
+    # +-1, few replicas: bytes of a word, two and three colours, one set a
+    # workgroup and several, bit rows with a ragged last word
+    ("pm", 3, 5, 50, 7, 3, 4.0, dict(tile_rows=3, group_replicas=16, packed=True)),
+    ("pm", 3, 11, 9, 5, 3, 4.0, dict(packed=True)),
+    ("pm", 3, 13, 9, 4, 2, 3.0, {}),
+    ("pm", 3, 16, 31, 4, 2, 3.0, dict(tile_rows=2)),
+    # the largest population whose map the statistics write, and the next
+    ("pm", 3, 4, 3600, 3, 1, 1.0, dict(capacity=4096)),
+    ("pm", 3, 4, 3600, 3, 1, 1.0, dict(capacity=4097)),
+    ("real", 3, 4, 3600, 3, 1, 1.0, dict(capacity=4096)),
     # real: few and many replicas a word, bond sums and thresholds, at the last
     # lattice of either and the first beyond
     ("real", 3, 8, 15, 6, 3, 20.0, dict(tile_rows=4, group_replicas=4)),
