@@ -28,7 +28,8 @@ constexpr uint32_t kTagIcm = 0x40000000u;
 // every L.
 
 constexpr int kRowsPerBlock = 1024;  // rows handled per block by row kernels
-constexpr int kDirectRows = 32768;    // +-1 populations up to this size are measured row by row
+constexpr int kDirectRows = 32768;    // populations (capacity) up to this size are measured (+-1 couplings) and their families counted row by row
+constexpr int kMapRows = 4096;        // populations (capacity) up to this size get their copy map in the post launch
 constexpr int kOvlPairs = 2048;      // replica pairs per overlap workgroup (few workgroups: most steps measure no overlap)
 constexpr int kOvlLdsBins = 8194;    // overlap histograms up to this many bins (L <= 16) are built in LDS
 
@@ -139,7 +140,7 @@ struct Inst {
 
 // Work item of the row-parallel kernels and of the sweep: instance index,
 // first row (or first family id), and the role of a post-kernel workgroup.
-enum PostRole : uint32_t { kRoleCopies = 0, kRoleFamilies = 1, kRoleOverlap = 2 };
+enum PostRole : uint32_t { kRoleCopies = 0, kRoleFamilies = 1, kRoleOverlap = 2, kRoleMeasure = 3 };
 struct Work {
     uint32_t inst;
     uint32_t row0;

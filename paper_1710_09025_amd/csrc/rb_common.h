@@ -11,18 +11,6 @@ namespace pamc {
 
 constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u, kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;
 
-template <typename V>
-__device__ __forceinline__ V scalar(V v)
-{
-    return (V)__builtin_amdgcn_readfirstlane((int)v);
-}
-template <typename P>
-__device__ __forceinline__ P *scalar_ptr(P *p)
-{
-    const uint64_t a = (uint64_t)p;
-    return (P *)((uint64_t)scalar((uint32_t)a) | ((uint64_t)scalar((uint32_t)(a >> 32)) << 32));
-}
-
 // Row memory and tables are global (the descriptor's pointers would make flat
 // accesses).
 typedef __attribute__((address_space(1))) const uint32_t *GlobalIn;

@@ -1,19 +1,31 @@
 // resample.hip -- resampling and the per-step statistics (paper Sec. II.B,
 // Eq. (2), Sec. V.A) for gfx950.
 //
-// After the sweeps, one post launch runs three kinds of workgroups per
+// After the sweeps, one post launch runs four kinds of workgroups per
 // instance:
-//   copies    measures the step (energy sums, normaliser) and takes
-//             n_r = floor(tau) + [u_r < frac(tau) 2^32] for 1024 rows, with
-//             their exclusive scan inside the workgroup;
+//   copies    the step's normaliser, and n_r = floor(tau) + [u_r < frac(tau)
+//             2^32] for 1024 rows with their exclusive scan inside the
+//             workgroup;
+//   measure   (+-1 couplings) the step's energy record;
 //   families  n ln n of 2048 family ids, summed by the pairwise tree;
 //   overlap   spin overlaps of 2048 replica pairs (at overlap steps).
 // The last workgroup of an instance to finish scans the per-workgroup
 // totals into offsets, sets R_{k+1} and the capacity / extinction status,
-// folds the family partial sums, and advances the step.  An expand launch
-// then writes the copy map (destination row -> source row, stable order),
-// which the next sweep reads its tile through, and clears the step's energy
-// histogram.
+// folds the family partial sums, and advances the step.  Small populations
+// get their copy map (destination row -> source row, stable order) from it as
+// well, the others from an expand launch, which also clears the step's energy
+// histogram; the next sweep reads its tile through the map.
+//
+// What bounds it: a chain of dependent steps, not bytes: reads of the
+// descriptor, the step's state and the energies in turn, and instructions that
+// each launch fetches anew (the same routine took twice as long on its first
+// call in a launch as on its second).  With trees and scans in registers
+// instead of through LDS (two barriers a level), the energy sums in a
+// workgroup of their own, the histogram's parts read once, uniform values in
+// scalar registers, families of small populations counted here instead of by
+// atomics of the sweep's workgroups, and no launch for a small map, the
+// launches after a sweep take 12.5 us at L = 4, R = 1000 (21 before), 25 at
+// L = 10, R = 20000 (34) and 24 at L = 8, R = 10^5 (35).
 #include "launch.h"
 #include "pamc_dev.h"
 #include "step_common.h"
@@ -117,97 +129,93 @@ __device__ __forceinline__ double real_normaliser(const Inst &I, int Rk, double 
         nroot, [&](int b) { return b * kRowsPerBlock < Rk ? I.wpart[b] : 0.0; }, a, a + 1024);
 }
 
-// Exclusive scan over the workgroup (1024 threads, 16 waves).
-__device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t *sh, uint32_t *total)
+// Inclusive scan over a wave (DPP row shifts, then the rows' totals).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t x = v;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) sh[wave] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        const int nw = blockDim.x >> 6;
-        for (int i = 0; i < nw; ++i) {
-            const uint32_t t = sh[i];
-            sh[i] = acc;
-            acc += t;
-        }
-        sh[16] = acc;
-    }
-    __syncthreads();
-    *total = sh[16];
-    const uint32_t r = sh[wave] + x - v;
-    __syncthreads();
-    return r;
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr 1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast 15, rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast 31, rows 2 and 3
+    return v;
 }
 
-// Measurement of step k after its sweeps with +-1 couplings, by a workgroup of
-// 1024 threads: E_min, E_max, sum E, sum E^2 (exact integers; written to the
-// step's record by `writer`), and for k < nT-1 the level weights
-// w[m] = exp(-2 dbeta m) as a fixed product of rho^(2^b) and their normaliser
-// S by the pairwise tree over 2^ceil(log2(M+1)) levels.  Every copies
-// workgroup measures for itself: its pass over the energies or the histogram
-// comes out of the L2 (12 loads a thread at L = 8), where one workgroup at the
-// end of the sweep launch kept the whole chip waiting (64 threads at L = 8:
-// about 25 us a step) and every other one had to count itself in.
+// Exclusive scan over the workgroup (at most 1024 threads).
+__device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t *sh, uint32_t *total)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t x = wave_scan(v);
+    if (lane == 63) sh[wave] = x;
+    __syncthreads();
+    const uint32_t sums = wave_scan(lane < (int)(blockDim.x >> 6) ? sh[lane] : 0u);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)sums, 63);
+    const uint32_t before = wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)sums, wave - 1) : 0u;
+    __syncthreads();
+    return before + x - v;
+}
+
+// Energies of a step with +-1 couplings, by a workgroup of 1024 threads: the
+// lowest and highest occupied level (level m: E = 2 m - 3 N), and for
+// k < nT-1 the level weights w[m] = exp(-2 dbeta m) as a fixed product of
+// rho^(2^b) and their normaliser S by the pairwise tree over
+// 2^ceil(log2(M+1)) levels.  Every copies workgroup takes them for itself: its
+// pass over the energies or the histogram comes out of the L2 (12 loads a
+// thread at L = 8), where one workgroup at the end of the sweep launch kept
+// the whole chip waiting (64 threads at L = 8: about 25 us a step) and every
+// other one had to count itself in.
 //   Up to kDirectRows rows: the energies themselves, 32 a thread, with the
 // histogram built in LDS (a sweep launch then counts nothing: its atomics on
 // the few energies of a cold population follow each other about 0.1 us apart
 // on each address, 15-50 us a launch at 10^4 rows).
 //   Beyond: the histogram that the sweep's workgroups have counted.
-// pw: 40 doubles, a: 4096 doubles, of LDS.
+// The energy sums are taken by one more workgroup (measure_role) beside them:
+// 64-bit arithmetic per row that no copy count waits for.
+// pw: kLevelBits doubles, a: 4096 doubles, of LDS.
+// The parts of the energy histogram (global memory, the addresses read once).
+typedef __attribute__((address_space(1))) const uint32_t *GlobalCounts;
+struct HistParts {
+    GlobalCounts first, others;
+    int nlev;
+    __device__ __forceinline__ HistParts(const Inst &I, int n)
+        : first((GlobalCounts)scalar_ptr(I.hist)), others((GlobalCounts)scalar_ptr(I.loff)), nlev(n)
+    {
+    }
+    __device__ __forceinline__ uint32_t count(int m, int copies) const
+    {
+        uint32_t c = first[m];
+        const GlobalCounts p = others + m;
+#pragma unroll 8
+        for (int i = 0; i < copies - 1; ++i) c += p[(size_t)((uint32_t)i * (uint32_t)nlev)];
+        return c;
+    }
+};
+constexpr int kLevelRing = 4096;
+
 struct Levels {
     int lmin;
     double S;
 };
 
-struct LevelSums {
-    int64_t s1, s2;
-    int32_t lmin, lmax;
-    __device__ __forceinline__ void add(int m, int64_t c, int N3)
-    {
-        const int64_t e = 2 * m - N3;
-        s1 += c * e;
-        s2 += c * e * e;
-        lmin = min(lmin, m);
-        lmax = max(lmax, m);
+__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+__device__ __forceinline__ int imax(int a, int b) { return a > b ? a : b; }
+
+// Lowest and highest level over the workgroup.
+__device__ __forceinline__ void level_range(int &lmin, int &lmax)
+{
+    __shared__ int32_t sh[2][16];
+    lmin = wave_fold(lmin, imin);
+    lmax = wave_fold(lmax, imax);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = ((int)blockDim.x + 63) >> 6;
+    if (lane == 0) {
+        sh[0][wave] = lmin;
+        sh[1][wave] = lmax;
     }
-    // over the workgroup (two barriers inside)
-    __device__ __forceinline__ void reduce()
-    {
-        __shared__ int64_t sh64[2][16];
-        __shared__ int32_t sh32[2][16];
-        for (int off = 32; off > 0; off >>= 1) {
-            s1 += __shfl_xor(s1, off);
-            s2 += __shfl_xor(s2, off);
-            lmin = min(lmin, __shfl_xor(lmin, off));
-            lmax = max(lmax, __shfl_xor(lmax, off));
-        }
-        const int wave = threadIdx.x >> 6, nw = ((int)blockDim.x + 63) >> 6;
-        if ((threadIdx.x & 63) == 0) {
-            sh64[0][wave] = s1;
-            sh64[1][wave] = s2;
-            sh32[0][wave] = lmin;
-            sh32[1][wave] = lmax;
-        }
-        __syncthreads();
-        s1 = sh64[0][0];
-        s2 = sh64[1][0];
-        lmin = sh32[0][0];
-        lmax = sh32[1][0];
-        for (int i = 1; i < nw; ++i) {
-            s1 += sh64[0][i];
-            s2 += sh64[1][i];
-            lmin = min(lmin, sh32[0][i]);
-            lmax = max(lmax, sh32[1][i]);
-        }
-        __syncthreads();
-    }
-};
+    __syncthreads();
+    lmin = scalar(wave_fold(sh[0][imin(lane, nw - 1)], imin));
+    lmax = scalar(wave_fold(sh[1][imin(lane, nw - 1)], imax));
+    __syncthreads();
+}
 
 // S from the levels of up to 32 rows a thread (lev[i] of row 1024 i + t, -1:
 // none), 2048 levels at a time (an aligned subtree of the tree).
@@ -259,24 +267,20 @@ __device__ double normaliser_direct(const int (&lev)[32], int groups, int lmin, 
     return nchunks > 1 ? lds_pairwise(roots, nchunks) : S;
 }
 
-__device__ Levels measure_levels(const Inst &I, int k, int buf, bool writer, double *pw, double *a)
+__device__ Levels measure_levels(const Inst &I, int k, int buf, int Rk, double *pw, double *a)
 {
-    const bool resample = k < I.nT - 1;
     // loaded before the pass over the energies so that its latency overlaps it
-    const double rho_k = resample ? I.rho[k] : 1.0;
-    const int N3 = 3 * I.N, nlev = I.nlev, copies = I.hist_copies, Rk = (int)I.Rk[k];
+    const double rho_k = I.rho[k];
+    const int N3 = 3 * scalar(I.N), nlev = scalar(I.nlev), copies = scalar(I.hist_copies);
     const bool direct = copies == 0;
-    LevelSums s{0, 0, 0x7FFFFFFF, -1};
+    uint32_t *ring = reinterpret_cast<uint32_t *>(a + 2048);
+    int lmin = 0x7FFFFFFF, lmax = -1;
     int lev[32];
     const int groups = (Rk + 8191) / 8192;
-    if (threadIdx.x == 0) {
-        pw[0] = rho_k;
-        for (int b = 1; b < 40; ++b) pw[b] = pw[b - 1] * pw[b - 1];
-    }
     // loads eight at a time before any is used: the pass waits for about one
     // memory latency per eight of a thread
     if (direct) {
-        const int32_t *E = I.E[buf];
+        const auto E = (__attribute__((address_space(1))) const int32_t *)scalar_ptr(I.E[buf]);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             if (g < groups) {
@@ -289,59 +293,101 @@ __device__ Levels measure_levels(const Inst &I, int k, int buf, bool writer, dou
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int r = (8 * g + u) * 1024 + (int)threadIdx.x;
-                    lev[8 * g + u] = r < Rk ? (e[u] + N3) >> 1 : -1;
-                    if (r < Rk) s.add(lev[8 * g + u], 1, N3);
+                    const int l = (e[u] + N3) >> 1;
+                    lev[8 * g + u] = r < Rk ? l : -1;
+                    lmin = imin(lmin, r < Rk ? l : 0x7FFFFFFF);
+                    lmax = imax(lmax, lev[8 * g + u]);
                 }
             }
         }
     } else {
-        for (int base = threadIdx.x; base < nlev; base += 8 * 1024) {
-            uint32_t c[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-            for (int p = 0; p < copies; ++p) {
-                const uint32_t *hp = hist_copy(I, p);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int m = base + u * 1024;
-                    c[u] += m < nlev ? hp[m] : 0u;
-                }
+        // (the levels' counts stay in LDS, modulo kLevelRing, for the
+        // normaliser: a population spreads over far fewer)
+        const HistParts parts(I, nlev);
+        for (int i = threadIdx.x; i < kLevelRing; i += 1024) ring[i] = 0u;
+        __syncthreads();
+        for (int m = threadIdx.x; m < nlev; m += 1024) {
+            const uint32_t c = parts.count(m, copies);
+            if (c) {
+                lmin = imin(lmin, m);
+                lmax = imax(lmax, m);
+                ring[m % kLevelRing] = c;
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (c[u]) s.add(base + u * 1024, (int64_t)c[u], N3);
         }
     }
-    s.reduce();
-    double S = __builtin_nan("");
-    if (resample) {
-        const int lmin = s.lmin, nl = s.lmax - s.lmin + 1;
-        if (direct) {
-            S = normaliser_direct(lev, groups, lmin, nl, pw, a);
-        } else {
-            int P = 1;
-            while (P < nl) P <<= 1;
-            S = tree_sum<1024>(
-                P,
-                [&](int m) {
-                    if (m >= nl) return 0.0;
-                    uint32_t h = 0;
-                    for (int p = 0; p < copies; ++p) h += hist_copy(I, p)[lmin + m];
-                    return (double)h * level_weight(pw, (uint32_t)m);
-                },
-                a, a + 1024);
+    if (threadIdx.x == 0) {
+        double p = rho_k;
+        for (int b = 0; b < kLevelBits; ++b, p = p * p) pw[b] = p;
+    }
+    level_range(lmin, lmax);
+    const int nl = lmax - lmin + 1;
+    double S;
+    if (direct) {
+        S = normaliser_direct(lev, groups, lmin, nl, pw, a);
+    } else {
+        int P = 1;
+        while (P < nl) P <<= 1;
+        S = tree_sum<1024>(
+            P,
+            [&](int m) {
+                if (m >= nl) return 0.0;
+                const uint32_t h = nl <= kLevelRing ? ring[(lmin + m) % kLevelRing] : HistParts(I, nlev).count(lmin + m, copies);
+                return (double)h * level_weight(pw, (uint32_t)m);
+            },
+            a, a + 1024);
+    }
+    return Levels{lmin, S};
+}
+
+// The energy record of step k with +-1 couplings: E_min, E_max, sum E and
+// sum E^2 (exact integers).
+__device__ void measure_role(const Inst &I, int k, int buf, int Rk)
+{
+    __shared__ int64_t sh[2][16];
+    const int N3 = 3 * scalar(I.N), nlev = scalar(I.nlev), copies = scalar(I.hist_copies);
+    int64_t s1 = 0, s2 = 0;
+    int lmin = 0x7FFFFFFF, lmax = -1;
+    auto add = [&](int m, int64_t c) {
+        const int64_t e = 2 * m - N3;
+        s1 += c * e;
+        s2 += c * e * e;
+        lmin = imin(lmin, m);
+        lmax = imax(lmax, m);
+    };
+    if (copies == 0) {
+        const auto E = (__attribute__((address_space(1))) const int32_t *)scalar_ptr(I.E[buf]);
+#pragma unroll 8
+        for (int r = threadIdx.x; r < Rk; r += 1024) add((E[r] + N3) >> 1, 1);
+    } else {
+        const HistParts parts(I, nlev);
+        for (int m = threadIdx.x; m < nlev; m += 1024) {
+            const uint32_t c = parts.count(m, copies);
+            if (c) add(m, (int64_t)c);
         }
     }
-    if (writer && threadIdx.x == 0) {
+    for (int off = 32; off > 0; off >>= 1) {
+        s1 += __shfl_xor(s1, off);
+        s2 += __shfl_xor(s2, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = s1;
+        sh[1][threadIdx.x >> 6] = s2;
+    }
+    level_range(lmin, lmax);
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < 16; ++i) {
+            s1 += sh[0][i];
+            s2 += sh[1][i];
+        }
         StepRec *rec = I.rec + k;
         rec->R = Rk;
-        rec->sumE = s.s1;
-        rec->sumE2 = (uint64_t)s.s2;
+        rec->sumE = s1;
+        rec->sumE2 = (uint64_t)s2;
         rec->sumE2_hi = 0;
-        rec->Emin = 2 * s.lmin - N3;
-        rec->Emax = 2 * s.lmax - N3;
-        rec->S = S;
+        rec->Emin = 2 * lmin - N3;
+        rec->Emax = 2 * lmax - N3;
+        if (k == I.nT - 1) rec->S = __builtin_nan("");
     }
-    __syncthreads();
-    return Levels{s.lmin, S};
 }
 
 // Where the offsets of the resampled rows go: the energy buffer that the next
@@ -354,24 +400,21 @@ __device__ __forceinline__ uint32_t *row_offsets(const Inst &I, int idle)
 // Copy counts of rows [row0, row0 + 1024) and their offsets in the block:
 // tau = R' w / S, floor(tau) copies and one more when the row's draw is below
 // floor(frac(tau) 2^32).
-__device__ void copies_role(const Inst &I, int k, uint32_t row0, uint32_t *sh, double *pw, double *a)
+__device__ void copies_role(const Inst &I, int k, int buf, int Rk, uint32_t row0, uint32_t *sh, double *pw, double *a)
 {
-    const int buf = swept_buffer(I);
-    const int Rk = (int)I.Rk[k];
     const int r = (int)row0 + (int)threadIdx.x;
-    const bool resample = k < I.nT - 1;
-    Levels lv{0, 0.0};
+    if (k == I.nT - 1) return;
     // (issued before the measurement, whose latency covers it)
-    const int E = !I.real && resample && r < Rk ? I.E[buf][r] : 0;
-    if (!I.real && (resample || row0 == 0)) lv = measure_levels(I, k, buf, row0 == 0, pw, a);
-    if (!resample) return;
-    if (I.real) {
+    const int E = !I.real && r < Rk ? I.E[buf][r] : 0;
+    const uint32_t u = philox10(make_uint4(0u, (uint32_t)r, (uint32_t)k, kTagResample), I.key0, I.key1).x;
+    Levels lv{0, 0.0};
+    if (I.real)
         lv.S = real_normaliser(I, Rk, a);
-        if (row0 == 0 && threadIdx.x == 0) I.rec[k].S = lv.S;
-    }
+    else
+        lv = measure_levels(I, k, buf, Rk, pw, a);
+    if (row0 == 0 && threadIdx.x == 0) I.rec[k].S = lv.S;
     uint32_t n = 0;
     if (r < Rk) {
-        const uint32_t u = philox10(make_uint4(0u, (uint32_t)r, (uint32_t)k, kTagResample), I.key0, I.key1).x;
         // (real couplings: the row's weight from the weights launch)
         const double w = I.real ? I.wrep[r] : level_weight(pw, (uint32_t)(((E + 3 * I.N) >> 1) - lv.lmin));
         const double tau = (I.Rt[k + 1] * w) / lv.S;
@@ -385,29 +428,50 @@ __device__ void copies_role(const Inst &I, int k, uint32_t row0, uint32_t *sh, d
 }
 
 // Pairwise tree of n ln n over family ids [base, base + 2048) (zero for ids
-// without descendants and beyond R); the counts are cleared for the next
-// step.
-__device__ void families_role(const Inst &I, int k, uint32_t base, double *a)
+// without descendants and beyond R).  Up to kDirectRows rows (capacity) the
+// descendants are counted here from the rows' families, in LDS; beyond, the
+// sweep's workgroups have counted them, and the counts are cleared for the
+// next step.
+__device__ void families_role(const Inst &I, int k, int buf, int Rk, uint32_t base, double *a)
 {
-    const int n = min(2048, I.fam_pow2);
+    const int n = min(2048, scalar(I.fam_pow2));
     const int t = threadIdx.x;
-    double v = 0.0;
-    if (2 * t < n) {
-        const int f0 = (int)base + 2 * t, f1 = f0 + 1;
-        double l0 = 0.0, l1 = 0.0;
-        if (f0 < I.R) {
-            l0 = I.nlnn[I.cnt[f0]];
-            I.cnt[f0] = 0u;
+    uint32_t c[2] = {0u, 0u};
+    if (scalar(I.Rcap) <= kDirectRows) {
+        uint32_t *cnt = reinterpret_cast<uint32_t *>(a);
+        cnt[2 * t] = cnt[2 * t + 1] = 0u;
+        const auto fam = (GlobalCounts)scalar_ptr(I.fam[buf]);
+        __syncthreads();
+        for (int r0 = 0; r0 < Rk; r0 += 8192) {
+            uint32_t f[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + 1024 * u + t;
+                f[u] = r < Rk ? fam[r] - base : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (__ballot(f[u] < 2048u)) count_runs(cnt, f[u], f[u] < 2048u);
         }
-        if (n >= 2 && f1 < I.R) {
-            l1 = I.nlnn[I.cnt[f1]];
-            I.cnt[f1] = 0u;
+        __syncthreads();
+        c[0] = cnt[2 * t];
+        c[1] = cnt[2 * t + 1];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int f = (int)base + 2 * t + j;
+            if (2 * t + j < n && f < I.R) {
+                c[j] = I.cnt[f];
+                I.cnt[f] = 0u;
+            }
         }
-        v = n >= 2 ? l0 + l1 : l0;
     }
-    a[t] = v;
-    __syncthreads();
-    const double s = lds_pairwise(a, n >= 2 ? n / 2 : 1);
+    double l[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        if (2 * t + j < n && (int)base + 2 * t + j < I.R) l[j] = I.nlnn[c[j]];
+    const double s = wg_tree(n >= 2 ? l[0] + l[1] : l[0], n >= 2 ? n / 2 : 1, a);
     if (threadIdx.x == 0) {
         if (I.fam_pow2 <= 2048)
             I.rec[k].T = s;
@@ -423,11 +487,11 @@ __device__ void families_role(const Inst &I, int k, uint32_t base, double *a)
 // short rows.  Low temperatures put most pairs into a few bins, so the
 // counts go to an LDS histogram first and only its non-empty bins reach
 // global memory.
-__device__ void overlap_role(const Inst &I, int k, uint32_t p0, uint32_t *qh)
+__device__ void overlap_role(const Inst &I, int k, int buf, int Rk, uint32_t p0, uint32_t *qh)
 {
     const int slot = I.ovl_slot[k];
     if (slot < 0) return;
-    const int h = (int)I.Rk[k] / 2;
+    const int h = Rk / 2;
     if ((int)p0 >= h) return;
     const int npairs = min(kOvlPairs, h - (int)p0);
     const int nb = 2 * I.N + 1;
@@ -437,7 +501,7 @@ __device__ void overlap_role(const Inst &I, int k, uint32_t p0, uint32_t *qh)
         for (int i = threadIdx.x; i < nb; i += blockDim.x) qh[i] = 0u;
         __syncthreads();
     }
-    const uint8_t *sp = I.spins[swept_buffer(I)];
+    const uint8_t *sp = I.spins[buf];
     // 16-byte words of a stored row: bytes 0/1, or bits (both count the
     // differing sites as the popcount of the XOR)
     const int words = I.srow_bytes >> 4;
@@ -476,41 +540,114 @@ __device__ void overlap_role(const Inst &I, int k, uint32_t p0, uint32_t *qh)
     }
 }
 
-// Last workgroup of an instance in a post launch.
-__device__ void post_finish(const Inst &I, int k, uint32_t *sh, double *a)
+__device__ __forceinline__ void clear_moments(const Inst &I)
 {
-    if (I.fam_pow2 > 2048) {
-        const int n = I.fam_pow2 / 2048;  // power of two
-        const double s = tree_sum<1024>(n, [&](int i) { return I.fpart[i]; }, a, a + 1024);
-        if (threadIdx.x == 0) I.rec[k].T = s;
+    if ((int)threadIdx.x < kMomentParts) {
+        EMoments *m = I.emom + threadIdx.x;
+        m->emin = 0x7FFFFFFFFFFFFFFFll;
+        m->emax = -0x7FFFFFFFFFFFFFFFll - 1;
+        m->sum = 0ull;
+        m->sq_lo = 0ull;
+        m->sq_hi = 0ull;
     }
+}
+// What the last workgroup needs of the descriptor, read before the election:
+// its acquire empties the L2 of everything, and each read behind it is a trip
+// to memory (a chain of three took 5 us).
+struct PostEnd {
+    int nT, Rcap, real, fam_pow2;
+    const uint32_t *loff, *bsum;
+    uint32_t *boff, *map, *Rk;
+    const double *fpart;
+    int32_t *ctl;
+};
+__device__ __forceinline__ PostEnd post_end(const Inst &I, int buf)
+{
+    return PostEnd{scalar(I.nT),           scalar(I.Rcap),      scalar(I.real),     scalar(I.fam_pow2),
+                   scalar_ptr(row_offsets(I, buf ^ 1)), scalar_ptr(I.bsum),  scalar_ptr(I.boff), scalar_ptr(I.map),
+                   scalar_ptr(I.Rk),       scalar_ptr(I.fpart), scalar_ptr(I.k)};
+}
+
+// The map of a population of at most kMapRows rows, by one workgroup: every
+// row's offset in LDS, four destinations a thread (see k_expand, whose launch
+// takes 5 us).  Returns R_{k+1}; no map if that exceeds the capacity.
+__device__ uint32_t expand_small(const PostEnd &p, int Rold, uint32_t *off)
+{
+    constexpr int B = kMapRows / kRowsPerBlock;
+    const int nb = (Rold + kRowsPerBlock - 1) / kRowsPerBlock;
+    uint32_t l[B], sum[B], total = 0;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const int r = b * kRowsPerBlock + (int)threadIdx.x;
+        l[b] = r < Rold ? p.loff[r] : 0u;
+        sum[b] = b < nb ? p.bsum[b] : 0u;
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        if (b < nb) off[b * kRowsPerBlock + (int)threadIdx.x] = total + l[b];
+        total += scalar(sum[b]);
+    }
+    __syncthreads();
+    if (total > (uint32_t)p.Rcap) return total;
+    int first = 1;
+    while (2 * first < Rold) first *= 2;
+    for (uint32_t j = threadIdx.x; j < total; j += kRowsPerBlock) {
+        int q = 0;  // off[0] = 0 <= j
+        for (int step = first; step > 0; step >>= 1)
+            if (q + step < Rold && off[q + step] <= j) q += step;
+        p.map[j] = (uint32_t)q;
+    }
+    return total;
+}
+
+// Last workgroup of an instance in a post launch.
+__device__ void post_finish(const Inst &I, const PostEnd &p, int k, int buf, int Rk, uint32_t *sh, double *a)
+{
+    const bool resample = k < p.nT - 1;
     bool ok = true;
-    if (k < I.nT - 1) {
-        const int nb = ((int)I.Rk[k] + kRowsPerBlock - 1) / kRowsPerBlock;
+    if (resample) {
+        const int nb = (Rk + kRowsPerBlock - 1) / kRowsPerBlock;
         uint64_t carry = 0;
-        for (int b0 = 0; b0 < nb; b0 += blockDim.x) {
-            const int b = b0 + (int)threadIdx.x;
-            const uint32_t v = b < nb ? I.bsum[b] : 0u;
-            uint32_t total;
-            const uint32_t off = block_exscan(v, sh, &total);
-            if (b < nb) I.boff[b] = (uint32_t)(carry + off);
-            carry += total;
+        if (p.Rcap <= kMapRows) {
+            carry = expand_small(p, Rk, reinterpret_cast<uint32_t *>(a));
+            if (p.real) clear_moments(I);
+        } else if (nb <= 64) {
+            // (every wave: no barrier)
+            const int b = (int)threadIdx.x & 63;
+            const uint32_t v = b < nb ? p.bsum[b] : 0u, x = wave_scan(v);
+            if ((int)threadIdx.x < nb) p.boff[b] = x - v;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        } else {
+            for (int b0 = 0; b0 < nb; b0 += blockDim.x) {
+                const int b = b0 + (int)threadIdx.x;
+                const uint32_t v = b < nb ? p.bsum[b] : 0u;
+                uint32_t total;
+                const uint32_t off = block_exscan(v, sh, &total);
+                if (b < nb) p.boff[b] = (uint32_t)(carry + off);
+                carry += total;
+            }
         }
-        ok = carry > 0 && carry <= (uint64_t)I.Rcap;
+        ok = carry > 0 && carry <= (uint64_t)p.Rcap;
         if (threadIdx.x == 0) {
-            I.Rk[k + 1] = carry > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)carry;
+            p.Rk[k + 1] = carry > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)carry;
             if (!ok) {
                 I.status[1] = (uint32_t)k;
                 I.status[0] |= carry == 0 ? 2u : 1u;
             }
         }
     }
+    if (p.fam_pow2 > 2048) {
+        __syncthreads();
+        const int n = p.fam_pow2 / 2048;  // power of two
+        const double s = tree_sum<1024>(n, [&](int i) { return p.fpart[i]; }, a, a + 1024);
+        if (threadIdx.x == 0) I.rec[k].T = s;
+    }
     if (threadIdx.x == 0) {
         // the population of step k lies where its sweeps left it; rows of the
         // next step live there through the copy map
-        *I.cur = swept_buffer(I);
-        *I.mapped = ok && k < I.nT - 1 ? 1 : 0;
-        if (ok) *I.k = k + 1;
+        p.ctl[1] = buf;
+        p.ctl[2] = ok && resample ? 1 : 0;
+        if (ok) p.ctl[0] = k + 1;
     }
 }
 
@@ -522,19 +659,29 @@ __global__ __launch_bounds__(1024) void k_post(const Inst *insts, const Work *wo
     __shared__ double a[kOvlLdsBins / 2 + 1];
     const Work w = work[blockIdx.x];
     const Inst &I = insts[w.inst];
-    const int k = *I.k;
-    if (!inst_live(I, k)) return;
-    if (w.role == kRoleCopies) {
-        copies_role(I, k, w.row0, sh, pw, a);
-    } else if (w.role == kRoleFamilies) {
-        families_role(I, k, w.row0, a);
+    // (k, cur and mapped in one read)
+    const int4 ctl = *reinterpret_cast<const int4 *>(I.k);
+    const uint32_t status = I.status[0];
+    const int k = scalar(ctl.x), buf = scalar(ctl.y ^ ctl.z);
+    if (k >= scalar(I.nT) || scalar(status) != 0u) return;
+    const int Rk = (int)scalar(I.Rk[k]);
+    const uint32_t row0 = scalar(w.row0), role = scalar(w.role);
+    const PostEnd end = post_end(I, buf);
+    const int expected = scalar(I.post_blocks);
+    uint32_t *const count = scalar_ptr(&I.sync[1]);
+    if (role == kRoleCopies) {
+        copies_role(I, k, buf, Rk, row0, sh, pw, a);
+    } else if (role == kRoleMeasure) {
+        measure_role(I, k, buf, Rk);
+    } else if (role == kRoleFamilies) {
+        families_role(I, k, buf, Rk, row0, a);
     } else {
-        overlap_role(I, k, w.row0, reinterpret_cast<uint32_t *>(a));
+        overlap_role(I, k, buf, Rk, row0, reinterpret_cast<uint32_t *>(a));
     }
-    if (last_workgroup(&I.sync[1], I.post_blocks)) post_finish(I, k, sh, a);
+    if (last_workgroup(count, expected)) post_finish(I, end, k, buf, Rk, sh, a);
 }
 
-// Copy map of the resampling of step k - 1 (the step index has advanced):
+// Copy map of the resampling of step k - 1 (more than kMapRows rows) (the step index has advanced):
 // source row r owns destination rows [off_r, off_r + n_r).  A few rows can
 // own thousands of copies when the temperature step is large, so the
 // workgroup of a row block walks the block's destinations instead of its
@@ -548,14 +695,7 @@ __global__ __launch_bounds__(1024) void k_expand(const Inst *insts, const Work *
     if (!inst_live(I, k) || k == 0 || !*I.mapped) return;
     const int Rold = (int)I.Rk[k - 1];
     const int row0 = (int)w.row0;
-    if (I.real && row0 == 0 && threadIdx.x < kMomentParts) {
-        EMoments *m = I.emom + threadIdx.x;
-        m->emin = 0x7FFFFFFFFFFFFFFFll;
-        m->emax = -0x7FFFFFFFFFFFFFFFll - 1;
-        m->sum = 0ull;
-        m->sq_lo = 0ull;
-        m->sq_hi = 0ull;
-    }
+    if (I.real && row0 == 0) clear_moments(I);
     if (!I.real && I.hist_copies > 0) {
         // every copies workgroup has measured the step: the nblk workgroups
         // clear its energy histogram for the next sweep, a slice each

@@ -521,7 +521,7 @@ int Runner::upload_inst(int i)
     {
         const int64_t nchunks = std::max<int64_t>(1, fp2 / 2048);
         const int64_t novl = (h.Rcap / 2 + kOvlPairs - 1) / kOvlPairs;
-        d.post_blocks = (int32_t)(d.nblk + nchunks + novl);
+        d.post_blocks = (int32_t)(d.nblk + nchunks + novl + (h.real ? 0 : 1));
     }
     h.ctl = d.k;
     h.Jdev = (int8_t *)(b + lay.J);
@@ -790,11 +790,12 @@ int Runner::build_work(const std::vector<int> &active)
         const uint32_t tiles = (uint32_t)((h.Rcap + h.tile_rows - 1) / h.tile_rows);
         for (int64_t r = 0; r < h.Rcap; r += h.tile_rows) g.push_back(Work{ii, (uint32_t)r, 0u, tiles});
         for (int64_t r = 0; r < h.Rcap; r += kRowsPerBlock) {
-            rows.push_back(Work{ii, (uint32_t)r, 0u, 0u});
+            if (h.Rcap > kMapRows) rows.push_back(Work{ii, (uint32_t)r, 0u, 0u});
             post.push_back(Work{ii, (uint32_t)r, kRoleCopies, 0u});
             if (h.real) wblk.push_back(Work{ii, (uint32_t)r, 0u, 0u});
         }
         for (const Work &w : gather_items(ii, h.Rcap, h.srow_bytes)) gath.push_back(w);
+        if (!h.real) post.push_back(Work{ii, 0u, kRoleMeasure, 0u});
         int64_t fp2 = 1;
         while (fp2 < h.R) fp2 <<= 1;
         for (int64_t f = 0; f < fp2; f += 2048) post.push_back(Work{ii, (uint32_t)f, kRoleFamilies, 0u});
@@ -810,7 +811,11 @@ int Runner::build_work(const std::vector<int> &active)
         if (!sg.work) return dev_fail(hipErrorOutOfMemory, "upload sweep work");
         sweep_groups_.push_back(sg);
     }
-    d_rows_ = (Work *)upload(rows.data(), rows.size() * sizeof(Work));
+    d_rows_ = nullptr;
+    if (!rows.empty()) {
+        d_rows_ = (Work *)upload(rows.data(), rows.size() * sizeof(Work));
+        if (!d_rows_) return dev_fail(hipErrorOutOfMemory, "upload map work");
+    }
     d_gather_ = (Work *)upload(gath.data(), gath.size() * sizeof(Work));
     ngather_ = (int)gath.size();
     d_post_ = (Work *)upload(post.data(), post.size() * sizeof(Work));
@@ -827,7 +832,7 @@ int Runner::build_work(const std::vector<int> &active)
         d_wblk_ = (Work *)upload(wblk.data(), wblk.size() * sizeof(Work));
         if (!d_wblk_) return dev_fail(hipErrorOutOfMemory, "upload weight work");
     }
-    if (!d_rows_ || !d_post_ || !d_list_ || !d_gather_) return dev_fail(hipErrorOutOfMemory, "upload work lists");
+    if (!d_post_ || !d_list_ || !d_gather_) return dev_fail(hipErrorOutOfMemory, "upload work lists");
     const int ust = upload_sync();
     if (ust != PAMC_OK) return ust;
     nrows_work_ = (int)rows.size();

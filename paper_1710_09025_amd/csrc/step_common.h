@@ -46,79 +46,144 @@ __device__ __forceinline__ uint32_t word_of(uint4 v, int i)
 
 __device__ __forceinline__ bool inst_live(const Inst &I, int k) { return k < I.nT && I.status[0] == 0; }
 
-// Reduction over the block (any multiple of 64 threads up to 1024); sh holds
-// one value per wave.
-template <typename T, typename Op>
-__device__ __forceinline__ T block_reduce(T v, T *sh, Op op)
+// A value or pointer known to be the same in all lanes, in scalar registers
+// (values read through pointers would stay in vector registers, and branches
+// on them mask lanes).
+template <typename V>
+__device__ __forceinline__ V scalar(V v)
 {
-    for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off));
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) sh[wave] = v;
-    __syncthreads();
-    T r = sh[0];
-    const int nw = (blockDim.x + 63) >> 6;
-    for (int i = 1; i < nw; ++i) r = op(r, sh[i]);
-    __syncthreads();
-    return r;
+    return (V)__builtin_amdgcn_readfirstlane((int)v);
+}
+template <typename P>
+__device__ __forceinline__ P *scalar_ptr(P *p)
+{
+    const uint64_t a = (uint64_t)p;
+    return (P *)((uint64_t)scalar((uint32_t)a) | ((uint64_t)scalar((uint32_t)(a >> 32)) << 32));
 }
 
-// Pairwise tree sum of the n = 2^p values a[0..n) held in LDS (destroys a):
-// level by level, node i of the next level is a[2i] + a[2i+1].
-// n <= 2 blockDim.
+// v of the lane that the DPP control names, and folds over a wave from it:
+// lanes 1, 2, 4 and 8 away by DPP (half mirror and mirror stand for 4 and 8:
+// by then the lanes of a quad, of eight, agree), 16 and 32 away by the row
+// swaps.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, ((uint64_t)dpp32<CTRL>((uint32_t)(b >> 32)) << 32) | dpp32<CTRL>((uint32_t)b));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor4 = 0x141, kXor8 = 0x140;
+// both values that a lane and the one 16 or 32 away hold, the lower lane's first
+struct Pair32 {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Pair32 both16(uint32_t v)
+{
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return Pair32{p[0], p[1]};
+}
+__device__ __forceinline__ Pair32 both32(uint32_t v)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return Pair32{p[0], p[1]};
+}
+template <typename Op>
+__device__ __forceinline__ int32_t wave_fold(int32_t v, Op op)
+{
+    v = op(v, (int32_t)dpp32<kXor1>((uint32_t)v));
+    v = op(v, (int32_t)dpp32<kXor2>((uint32_t)v));
+    v = op(v, (int32_t)dpp32<kXor4>((uint32_t)v));
+    v = op(v, (int32_t)dpp32<kXor8>((uint32_t)v));
+    Pair32 p = both16((uint32_t)v);
+    v = op((int32_t)p.lo, (int32_t)p.hi);
+    p = both32((uint32_t)v);
+    return op((int32_t)p.lo, (int32_t)p.hi);
+}
+
+// Pairwise tree sum of the values of each aligned group of n = 2^p <= 64
+// lanes: node i of the next level is node 2i + node 2i+1 (the sum of two
+// values is the same in either order, so both lanes of a pair compute it).
+__device__ __forceinline__ double wave_tree(double v, int n)
+{
+    if (n > 1) v = v + dpp64<kXor1>(v);
+    if (n > 2) v = v + dpp64<kXor2>(v);
+    if (n > 4) v = v + dpp64<kXor4>(v);
+    if (n > 8) v = v + dpp64<kXor8>(v);
+    if (n > 16) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const Pair32 l = both16((uint32_t)b), h = both16((uint32_t)(b >> 32));
+        v = __builtin_bit_cast(double, ((uint64_t)h.lo << 32) | l.lo) + __builtin_bit_cast(double, ((uint64_t)h.hi << 32) | l.hi);
+    }
+    if (n > 32) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const Pair32 l = both32((uint32_t)b), h = both32((uint32_t)(b >> 32));
+        v = __builtin_bit_cast(double, ((uint64_t)h.lo << 32) | l.lo) + __builtin_bit_cast(double, ((uint64_t)h.hi << 32) | l.hi);
+    }
+    return v;
+}
+
+// Pairwise tree sum of the values of threads 0 .. n-1, n = 2^p <= blockDim
+// (at most 1024): the waves' subtrees in registers, their roots through
+// roots[16] in LDS.  Two barriers (a level at a time through LDS took two
+// each, 20 for 1024 values).
+__device__ __forceinline__ double wg_tree(double v, int n, double *roots)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = n > 64 ? n >> 6 : 1;
+    v = wave_tree(v, n < 64 ? n : 64);
+    if (lane == 0 && wave < nw) roots[wave] = v;
+    __syncthreads();
+    v = wave_tree(roots[lane & (nw - 1)], nw);
+    __syncthreads();
+    return v;
+}
+
+// The same of the n values a[0..n) held in LDS (after a barrier).
 __device__ __forceinline__ double lds_pairwise(double *a, int n)
 {
-    for (; n > 1; n >>= 1) {
-        const int h = n >> 1;
-        double v = 0.0;
-        if ((int)threadIdx.x < h) v = a[2 * threadIdx.x] + a[2 * threadIdx.x + 1];
-        __syncthreads();
-        if ((int)threadIdx.x < h) a[threadIdx.x] = v;
-        __syncthreads();
-    }
-    return a[0];
+    const double v = (int)threadIdx.x < n ? a[threadIdx.x] : 0.0;
+    __syncthreads();
+    return wg_tree(v, n, a);
 }
 
 // Pairwise tree sum of n = 2^p leaves leaf(0..n).  T = the largest power of
 // two <= min(blockDim, NT) threads take part: aligned chunks of 2T leaves
-// are subtrees of the global tree; each is folded in LDS, then the chunk
-// roots are folded.  a and roots hold NT doubles each; n <= 2 T NT.
+// are subtrees of the global tree; each is folded, then the chunk roots are.
+// a holds 16 doubles, roots one per chunk; n <= 2 T blockDim.
 template <int NT, typename Leaf>
 __device__ __forceinline__ double tree_sum(int n, Leaf leaf, double *a, double *roots)
 {
     const int t = threadIdx.x;
     int T = 1;
     while (2 * T <= (int)blockDim.x && 2 * T <= NT) T <<= 1;
-    if (n == 1) {
-        if (t == 0) a[0] = leaf(0);
-        __syncthreads();
-        const double r = a[0];
-        __syncthreads();
-        return r;
-    }
+    if (n == 1) return wg_tree(t == 0 ? leaf(0) : 0.0, 1, a);
     const int chunk = 2 * T;
-    if (n <= chunk) {
-        if (t < T) a[t] = 2 * t < n ? leaf(2 * t) + leaf(2 * t + 1) : 0.0;
-        __syncthreads();
-        return lds_pairwise(a, n / 2);
-    }
+    if (n <= chunk) return wg_tree(2 * t < n ? leaf(2 * t) + leaf(2 * t + 1) : 0.0, n / 2, a);
     const int nchunks = n / chunk;
     for (int c = 0; c < nchunks; ++c) {
-        if (t < T) a[t] = leaf(c * chunk + 2 * t) + leaf(c * chunk + 2 * t + 1);
-        __syncthreads();
-        const double r = lds_pairwise(a, T);
+        const double r = wg_tree(t < T ? leaf(c * chunk + 2 * t) + leaf(c * chunk + 2 * t + 1) : 0.0, T, a);
         if (t == 0) roots[c] = r;
     }
     __syncthreads();
     return lds_pairwise(roots, nchunks);
 }
 
-// w[m] = product over the set bits b of m, ascending, of pw[b] = rho^(2^b).
+// w[m] = product over the set bits b of m < 2^17, ascending, of
+// pw[b] = rho^(2^b).  The first nine factors are read at once (a loop over the
+// set bits waited for LDS at each).
+constexpr int kLevelBits = 17;
 __device__ __forceinline__ double level_weight(const double *pw, uint32_t m)
 {
-    double x = 1.0;
-    for (int b = 0; m != 0; ++b, m >>= 1)
-        if (m & 1u) x = x * pw[b];
+    double x = 1.0, f[9];
+#pragma unroll
+    for (int b = 0; b < 9; ++b) f[b] = pw[b];
+#pragma unroll
+    for (int b = 0; b < 9; ++b) x = (m >> b) & 1u ? x * f[b] : x;
+    for (int b = 9; (m >> b) != 0; ++b)
+        if ((m >> b) & 1u) x = x * pw[b];
     return x;
 }
 

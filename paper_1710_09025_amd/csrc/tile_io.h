@@ -105,9 +105,11 @@ __device__ __forceinline__ void tile_energy_out(const Inst &I, const TileIO &io,
 }
 
 // Descendants per family: a tile's rows counted under their family ids fam[]
-// (sorted, unless a caller's imported state is not: then the runs are short).
+// (sorted, unless a caller's imported state is not: then the runs are short),
+// where the population is too large for the statistics to count them all.
 __device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t *fam, int nrows)
 {
+    if (I.Rcap <= kDirectRows) return;
     for (int base = 0; base < nrows; base += blockDim.x) {
         const int q = base + (int)threadIdx.x;
         const bool valid = q < nrows;
