@@ -26,6 +26,8 @@
 //              words is compared once and the exact decision made only where
 //              a lane of the wave needs it, 0.6 per attempt; kMid compares
 //              every draw with the threshold for dE = 4 besides (2).
+#include <algorithm>
+
 #include "launch.h"
 #include "pamc_dev.h"
 #include "rb_common.h"
@@ -188,7 +190,7 @@ __device__ __forceinline__ void rb_block(const RBInst &X, uint32_t *lds, const u
 // blocks of all sets are dealt out to the threads in order.
 template <bool UNI, int MODE>
 __device__ __forceinline__ void rb_sweeps(const RBInst &X, int k, uint32_t *lds, const uint32_t *tab, uint4 th, int r0,
-                                          int m, int sets, int t0, int t1, int tid)
+                                          int m, int sets, int t0, int t1, int tid, bool even)
 {
     const bool local = UNI && blockDim.x == 64;
     int set = 0, g0 = tid, step = (int)blockDim.x;
@@ -202,7 +204,8 @@ __device__ __forceinline__ void rb_sweeps(const RBInst &X, int k, uint32_t *lds,
     const uint32_t rb = (uint32_t)(UNI ? r0 : r0 + set * m);
     const int last = X.gmax - 1;  // (records past a colour's blocks are zeros)
     Record rec = load_record(X, 0, min(g0, last));
-    for (int t = t0; t < t1; ++t)
+    for (int t = t0; t < t1; ++t) {
+        if (even) even_progress(t, t0, t1);
         for (int c = 0; c < X.ncol; ++c) {
             const int nc = c + 1 < X.ncol ? c + 1 : 0;
             for (int first = 0; first <= last; first += step) {
@@ -213,6 +216,8 @@ __device__ __forceinline__ void rb_sweeps(const RBInst &X, int k, uint32_t *lds,
             }
             set_barrier(local);
         }
+    }
+    if (even) __builtin_amdgcn_s_setprio(3);
 }
 
 // Sum over each row of 16 lanes, in every lane of the row.
@@ -318,7 +323,8 @@ __device__ __forceinline__ void rb_energy(const RBInst &X, const uint32_t *lds, 
 // The workgroup's LDS: the sets' words, then the pass's source rows, their
 // families and their unsatisfied-bond counts (32 of each a set).
 template <bool UNI>
-__device__ __forceinline__ void rb_tile(const Inst &I, int k, uint32_t *lds, int r0, int nrows, int m, int sets, int phase)
+__device__ __forceinline__ void rb_tile(const Inst &I, int k, uint32_t *lds, int r0, int nrows, int m, int sets, int phase,
+                                        bool even)
 {
     // thresholds by n: T(dE = 12, 8, 4) for n = 0, 1, 2; n = 3 flips whatever
     // the entry
@@ -353,13 +359,13 @@ __device__ __forceinline__ void rb_tile(const Inst &I, int k, uint32_t *lds, int
         __syncthreads();
         // (the checks take two draws at a time)
         if (th.w)
-            rb_sweeps<UNI, kAll>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid);
+            rb_sweeps<UNI, kAll>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid, even);
         else if (th.x <= kRareT && m > 1)
-            rb_sweeps<UNI, kRare>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid);
+            rb_sweeps<UNI, kRare>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid, even);
         else if (th.y <= kRareT && m > 1)
-            rb_sweeps<UNI, kMid>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid);
+            rb_sweeps<UNI, kMid>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid, even);
         else
-            rb_sweeps<UNI, kTable>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid);
+            rb_sweeps<UNI, kTable>(X, k, lds, tab, th, row0, m, sets, t0, t1, tid, even);
         __syncthreads();
         if (phase != 1) rb_energy<UNI>(X, lds, unsat, m, sets, tid);
         rb_store<UNI>(X, lds, row0, nr, m, sets, tid);
@@ -380,8 +386,8 @@ __device__ __forceinline__ void rb_tile(const Inst &I, int k, uint32_t *lds, int
 }  // namespace
 
 template <bool UNI>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_sweep_rb(const Inst *insts, const Work *work, int tile_rows, int m,
-                                                    int sets, int phase)
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void k_sweep_rb(
+    const Inst *insts, const Work *work, int tile_rows, int m, int sets, int phase, bool even)
 {
     extern __shared__ __align__(16) uint8_t lds[];
     const Work w = work[blockIdx.x];
@@ -391,7 +397,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     const int Rk = (int)I.Rk[k];
     const int r0 = scalar((int)w.row0);
     const int nrows = scalar(min(tile_rows, Rk - r0));
-    if (nrows > 0) rb_tile<UNI>(I, k, reinterpret_cast<uint32_t *>(lds), r0, nrows, m, sets, phase);
+    if (nrows > 0) rb_tile<UNI>(I, k, reinterpret_cast<uint32_t *>(lds), r0, nrows, m, sets, phase, even);
     if (phase == 1) phase1_done(I, w.n);
 }
 
@@ -433,10 +439,15 @@ void launch_sweep_rb(const SweepShape &sh, const Inst *insts, const Work *work, 
 {
     const int nt = rb_threads(sh.G, sh.sets);
     const size_t lds = rb_lds(sh.plane, sh.sets);
+    // all workgroups on the chip at once (256 compute units, 24 waves each):
+    // then even progress takes 3-9% off (L = 8, R = 10^5: 255 -> 232 us); in a
+    // launch of several rounds it would bring the loads of the later ones
+    // together (L = 12, R = 10^5: 725 -> 766 us)
+    const bool even = nwork <= 256 * (int)std::min<size_t>(24 / (nt / 64), 160 * 1024 / (lds + 512));
     if (rb_uniform(sh.G))
-        k_sweep_rb<true><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase);
+        k_sweep_rb<true><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase, even);
     else
-        k_sweep_rb<false><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase);
+        k_sweep_rb<false><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase, even);
 }
 
 }  // namespace pamc

@@ -372,7 +372,10 @@ __device__ __forceinline__ void rq_sweeps(const RBInst &X, const RQInst &Q, int 
     if constexpr (UNI) rb = scalar(rb);
     const int last = X.gmax - 1;  // (records past a colour's blocks are zeros)
     Record rec = load_record(X, 0, min(p.g0, last));
-    for (int t = t0; t < t1; ++t)
+    for (int t = t0; t < t1; ++t) {
+        // (waves of their own sets: the workgroup is done when the last is;
+        // L = 8, R = 10^5: 395 -> 375 us)
+        if (local) even_progress(t, t0, t1);
         for (int c = 0; c < X.ncol; ++c) {
             const int nc = c + 1 < X.ncol ? c + 1 : 0;
             for (int first = 0; first <= last; first += p.step) {
@@ -383,6 +386,8 @@ __device__ __forceinline__ void rq_sweeps(const RBInst &X, const RQInst &Q, int 
             }
             set_barrier(local);
         }
+    }
+    if (local) __builtin_amdgcn_s_setprio(3);
 }
 
 // Energies E = -sum_b J S S from the sites' bond sums h = sum_d J_d (1 - 2 x_d):
