@@ -45,16 +45,15 @@ struct StepRec {
     double T;         // family term sum n ln n
 };
 
-// Energy moments of a step's population with real couplings, accumulated
-// with atomics by the sweep workgroups (one update per pass, in kMomentParts
-// parts), read by the weights launch and reset by k_expand.  Sums are exact: E^2 as a 128-bit integer.
-constexpr int kMomentParts = 64;
-struct EMoments {
-    long long emin, emax;
-    unsigned long long sum;      // sum of E, two's complement
-    unsigned long long sq_lo;    // sum of E^2, low 64 bits
-    unsigned long long sq_hi;    //   high 64 bits (carries added)
-    unsigned long long pad[3];
+// Real couplings: the lowest energy of the step being swept, in kMinParts
+// parts (one atomic of a sweep wave each; atomics on one address follow each
+// other about 0.1 us apart), and the other moments of a block of 1024 rows
+// (the squares' sum as two 64-bit halves).
+constexpr int kMinParts = 64;
+constexpr long long kNoEnergy = 0x7FFFFFFFFFFFFFFFll;
+struct BlockMoments {
+    long long emax;
+    unsigned long long sum, sq_lo, sq_hi;
 };
 
 struct Inst {
@@ -121,7 +120,7 @@ struct Inst {
     int64_t *Eq[2];     // energies, units of 2^-20
     double *wrep;       // [Rcap] resampling weight of each row
     double *wpart;      // [nblk] pairwise-tree roots of the 1024-row blocks
-    EMoments *emom;     // [kMomentParts] energy moments of the step being swept
+    long long *emin;    // [kMinParts], lowest energies of the step being swept
     const int32_t *cmj; // [ncol][gmax][24] coupling of each neighbour bond, in cmdesc order
     const float *bq;    // [nT] beta_k 2^-20 rounded to binary32
     const double *gpw;  // [nT][40] exp(-(beta_{k+1} - beta_k) 2^(b-20)), host libm

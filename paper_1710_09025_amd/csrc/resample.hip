@@ -6,7 +6,7 @@
 //   copies    the step's normaliser, and n_r = floor(tau) + [u_r < frac(tau)
 //             2^32] for 1024 rows with their exclusive scan inside the
 //             workgroup;
-//   measure   (+-1 couplings) the step's energy record;
+//   measure   the step's energy record;
 //   families  n ln n of 2048 family ids, summed by the pairwise tree;
 //   overlap   spin overlaps of 2048 replica pairs (at overlap steps).
 // The last workgroup of an instance to finish scans the per-workgroup
@@ -32,29 +32,46 @@
 
 namespace pamc {
 
-// The moments of a step with real couplings from their parts, by a wave
-// (lane = part); every lane returns them.
-struct Moments {
-    long long emin, emax;
-    unsigned long long sum, lo, hi;
-};
-__device__ __forceinline__ Moments fold_moments(const EMoments *parts)
+// Lowest energy of the step, from its parts (every lane returns it).
+__device__ __forceinline__ long long lowest_energy(const Inst &I)
 {
-    static_assert(kMomentParts == 64, "one part per lane");
-    const EMoments &p = parts[threadIdx.x & 63];
-    Moments m{p.emin, p.emax, p.sum, p.sq_lo, p.sq_hi};
+    static_assert(kMinParts == 64, "one part per lane");
+    long long e = I.emin[threadIdx.x & 63];
     for (int off = 32; off > 0; off >>= 1) {
-        const long long a = __shfl_xor(m.emin, off), b = __shfl_xor(m.emax, off);
-        const unsigned long long s = __shfl_xor(m.sum, off), l = __shfl_xor(m.lo, off), h = __shfl_xor(m.hi, off);
-        m.emin = a < m.emin ? a : m.emin;
-        m.emax = b > m.emax ? b : m.emax;
-        m.sum += s;
-        const unsigned long long nl = m.lo + l;
-        m.hi += h + (nl < m.lo ? 1ull : 0ull);
-        m.lo = nl;
+        const long long o = __shfl_xor(e, off);
+        e = o < e ? o : e;
     }
-    return m;
+    return e;
 }
+
+struct MomentSum {
+    long long emax;
+    unsigned long long sum, lo, hi;
+    __device__ __forceinline__ void add(const MomentSum &o)
+    {
+        emax = o.emax > emax ? o.emax : emax;
+        sum += o.sum;
+        const unsigned long long l = lo + o.lo;
+        hi += o.hi + (l < lo ? 1ull : 0ull);
+        lo = l;
+    }
+    // over the workgroup, into thread 0 (one barrier)
+    __device__ __forceinline__ void reduce(MomentSum *sh)
+    {
+        for (int off = 32; off > 0; off >>= 1) {
+            MomentSum o{__shfl_xor(emax, off), __shfl_xor(sum, off), __shfl_xor(lo, off), __shfl_xor(hi, off)};
+            add(o);
+        }
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = *this;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int w = 1; w < (int)(blockDim.x >> 6); ++w) add(sh[w]);
+    }
+};
+
+// Where the blocks' moments wait between the weights launch and the next one:
+// the copy map, which the sweeps have consumed and the next expand writes.
+__device__ __forceinline__ BlockMoments *block_moments(const Inst &I) { return reinterpret_cast<BlockMoments *>(I.map); }
 
 // Resampling weights with real couplings (Sec. II.B), for rows
 // [row0, row0 + 1024) of one instance after the sweeps of step k:
@@ -64,58 +81,54 @@ __device__ __forceinline__ Moments fold_moments(const EMoments *parts)
 // pairwise tree over rows 0 .. P-1 (P the smallest power of two >= R_k); the
 // copies workgroups fold the block roots (real_normaliser).  For P < 1024 the
 // block tree adds only zeros above the P-leaf subtree, which leaves its sum
-// unchanged.  The instance's first workgroup writes the step's energy record.
+// unchanged.  The block's moments go to measure_role.
 __global__ __launch_bounds__(512) void k_weights(const Inst *insts, const Work *work)
 {
     __shared__ double pw[40];
     __shared__ double a[512];
-    __shared__ Moments sh;
+    __shared__ MomentSum sh[8];
     const Work w = work[blockIdx.x];
     const Inst &I = insts[w.inst];
-    const int k = *I.k;
+    const int4 ctl = *reinterpret_cast<const int4 *>(I.k);
+    const int k = scalar(ctl.x), row0 = scalar((int)w.row0);
     if (!inst_live(I, k)) return;
-    const bool resample = k < I.nT - 1;
-    if (!resample && w.row0 != 0) return;
-    const int Rk = (int)I.Rk[k];
+    const bool resample = k < scalar(I.nT) - 1;
+    const int Rk = (int)scalar(I.Rk[k]);
+    if (row0 >= Rk && !resample) return;
     const int t = threadIdx.x;
     if (resample && t < 40) pw[t] = I.gpw[(size_t)k * 40 + t];
-    if (t < 64) {
-        const Moments m = fold_moments(I.emom);
-        if (t == 0) sh = m;
-    }
-    const int64_t *E = I.Eq[swept_buffer(I)];
+    const long long emin = lowest_energy(I);
+    const int64_t *E = I.Eq[scalar(ctl.y ^ ctl.z)];
     int64_t e[2] = {0, 0};
+    MomentSum m{-kNoEnergy - 1, 0ull, 0ull, 0ull};
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int r = (int)w.row0 + 2 * t + j;
-        if (resample && r < Rk) e[j] = E[r];
+        const int r = row0 + 2 * t + j;
+        if (r < Rk) e[j] = E[r];
     }
-    __syncthreads();
-    if (w.row0 == 0 && t == 0) {
-        StepRec *rec = I.rec + k;
-        rec->R = Rk;
-        rec->sumE = (int64_t)sh.sum;
-        rec->sumE2 = sh.lo;
-        rec->sumE2_hi = (int64_t)sh.hi;
-        rec->Emin = sh.emin;
-        rec->Emax = sh.emax;
-        rec->S = __builtin_nan("");
-    }
-    if (!resample) return;
-    double l[2] = {0.0, 0.0};
+    if (resample) {
+        __syncthreads();
+        double l[2] = {0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int r = (int)w.row0 + 2 * t + j;
-        if (r < Rk) {
-            const double x = weight64(pw, (uint64_t)(e[j] - sh.emin));
-            I.wrep[r] = x;
-            l[j] = x;
+        for (int j = 0; j < 2; ++j) {
+            const int r = row0 + 2 * t + j;
+            if (r < Rk) {
+                const double x = weight64(pw, (uint64_t)(e[j] - emin));
+                I.wrep[r] = x;
+                l[j] = x;
+            }
         }
+        const double root = wg_tree(l[0] + l[1], 512, a);
+        if (t == 0) I.wpart[row0 / kRowsPerBlock] = root;
     }
-    a[t] = l[0] + l[1];
-    __syncthreads();
-    const double root = lds_pairwise(a, 512);
-    if (t == 0) I.wpart[w.row0 / kRowsPerBlock] = root;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        if (row0 + 2 * t + j < Rk) {
+            const unsigned __int128 e2 = (unsigned __int128)((__int128)e[j] * (__int128)e[j]);
+            m.add(MomentSum{e[j], (unsigned long long)e[j], (unsigned long long)e2, (unsigned long long)(e2 >> 64)});
+        }
+    m.reduce(sh);
+    if (t == 0) block_moments(I)[row0 / kRowsPerBlock] = BlockMoments{m.emax, m.sum, m.lo, m.hi};
 }
 
 // The normaliser of a step with real couplings: the pairwise tree over the
@@ -339,11 +352,35 @@ __device__ Levels measure_levels(const Inst &I, int k, int buf, int Rk, double *
     return Levels{lmin, S};
 }
 
-// The energy record of step k with +-1 couplings: E_min, E_max, sum E and
-// sum E^2 (exact integers).
+// The energy record of step k: E_min, E_max, sum E and sum E^2 (exact
+// integers; with real couplings sum E^2 in 128 bits).
+__device__ void measure_real(const Inst &I, int k, int Rk)
+{
+    __shared__ MomentSum sh[16];
+    MomentSum m{-kNoEnergy - 1, 0ull, 0ull, 0ull};
+    const BlockMoments *b = block_moments(I);
+    for (int i = threadIdx.x; i < (Rk + kRowsPerBlock - 1) / kRowsPerBlock; i += blockDim.x)
+        m.add(MomentSum{b[i].emax, b[i].sum, b[i].sq_lo, b[i].sq_hi});
+    const long long emin = lowest_energy(I);
+    m.reduce(sh);
+    if (threadIdx.x == 0) {
+        StepRec *rec = I.rec + k;
+        rec->R = Rk;
+        rec->sumE = (int64_t)m.sum;
+        rec->sumE2 = m.lo;
+        rec->sumE2_hi = (int64_t)m.hi;
+        rec->Emin = emin;
+        rec->Emax = m.emax;
+        if (k == I.nT - 1) rec->S = __builtin_nan("");
+    }
+}
 __device__ void measure_role(const Inst &I, int k, int buf, int Rk)
 {
     __shared__ int64_t sh[2][16];
+    if (scalar(I.real)) {
+        measure_real(I, k, Rk);
+        return;
+    }
     const int N3 = 3 * scalar(I.N), nlev = scalar(I.nlev), copies = scalar(I.hist_copies);
     int64_t s1 = 0, s2 = 0;
     int lmin = 0x7FFFFFFF, lmax = -1;
@@ -540,16 +577,9 @@ __device__ void overlap_role(const Inst &I, int k, int buf, int Rk, uint32_t p0,
     }
 }
 
-__device__ __forceinline__ void clear_moments(const Inst &I)
+__device__ __forceinline__ void clear_lowest(const Inst &I)
 {
-    if ((int)threadIdx.x < kMomentParts) {
-        EMoments *m = I.emom + threadIdx.x;
-        m->emin = 0x7FFFFFFFFFFFFFFFll;
-        m->emax = -0x7FFFFFFFFFFFFFFFll - 1;
-        m->sum = 0ull;
-        m->sq_lo = 0ull;
-        m->sq_hi = 0ull;
-    }
+    if ((int)threadIdx.x < kMinParts) I.emin[threadIdx.x] = kNoEnergy;
 }
 // What the last workgroup needs of the descriptor, read before the election:
 // its acquire empties the L2 of everything, and each read behind it is a trip
@@ -610,7 +640,7 @@ __device__ void post_finish(const Inst &I, const PostEnd &p, int k, int buf, int
         uint64_t carry = 0;
         if (p.Rcap <= kMapRows) {
             carry = expand_small(p, Rk, reinterpret_cast<uint32_t *>(a));
-            if (p.real) clear_moments(I);
+            if (p.real) clear_lowest(I);
         } else if (nb <= 64) {
             // (every wave: no barrier)
             const int b = (int)threadIdx.x & 63;
@@ -695,7 +725,7 @@ __global__ __launch_bounds__(1024) void k_expand(const Inst *insts, const Work *
     if (!inst_live(I, k) || k == 0 || !*I.mapped) return;
     const int Rold = (int)I.Rk[k - 1];
     const int row0 = (int)w.row0;
-    if (I.real && row0 == 0) clear_moments(I);
+    if (I.real && row0 == 0) clear_lowest(I);
     if (!I.real && I.hist_copies > 0) {
         // every copies workgroup has measured the step: the nblk workgroups
         // clear its energy histogram for the next sweep, a slice each

@@ -112,7 +112,7 @@ struct Carve {
 
 struct InstLayout {
     size_t ctl, status, sync, spins0, spins1, E0, E1, f0, f1, map, loff, bsum, boff, hist, cnt, fpart, thr,
-        beta, rho, Rt, rbtab, J, pos, lexof, cmdesc, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emom, cmj,
+        beta, rho, Rt, rbtab, J, pos, lexof, cmdesc, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emin, cmj,
         bq, gpw, total;
 };
 
@@ -165,7 +165,7 @@ InstLayout layout_of(int L, int64_t R, int64_t Rcap, int nT, int n_ovl, bool pac
     l.Eq1 = c.take(real ? (size_t)Rcap * 8 : 16);
     l.wrep = c.take(real ? (size_t)Rcap * 8 : 16);
     l.wpart = c.take(real ? (size_t)nblk * 8 : 16);
-    l.emom = c.take(real ? kMomentParts * sizeof(EMoments) : 16);
+    l.emin = c.take(real ? kMinParts * 8 : 16);
     l.cmj = c.take(real ? (size_t)ncol * gmax * 24 * 4 : 16);
     l.bq = c.take((size_t)nT * 4);
     l.gpw = c.take(real ? (size_t)nT * 40 * 8 : 16);
@@ -426,14 +426,6 @@ void Runner::remove_instance(int slot)
     used_[slot] = 0;
 }
 
-static EMoments no_moments()
-{
-    EMoments m{};
-    m.emin = std::numeric_limits<long long>::max();
-    m.emax = std::numeric_limits<long long>::min();
-    return m;
-}
-
 int Runner::upload_inst(int i)
 {
     HostInst &h = inst_[i];
@@ -512,7 +504,7 @@ int Runner::upload_inst(int i)
     d.Eq[1] = (int64_t *)(b + lay.Eq1);
     d.wrep = (double *)(b + lay.wrep);
     d.wpart = (double *)(b + lay.wpart);
-    d.emom = (EMoments *)(b + lay.emom);
+    d.emin = (long long *)(b + lay.emin);
     d.cmj = (const int32_t *)(b + lay.cmj);
     d.bq = (const float *)(b + lay.bq);
     d.gpw = (const double *)(b + lay.gpw);
@@ -521,7 +513,7 @@ int Runner::upload_inst(int i)
     {
         const int64_t nchunks = std::max<int64_t>(1, fp2 / 2048);
         const int64_t novl = (h.Rcap / 2 + kOvlPairs - 1) / kOvlPairs;
-        d.post_blocks = (int32_t)(d.nblk + nchunks + novl + (h.real ? 0 : 1));
+        d.post_blocks = (int32_t)(d.nblk + nchunks + novl + 1);
     }
     h.ctl = d.k;
     h.Jdev = (int8_t *)(b + lay.J);
@@ -653,7 +645,7 @@ int Runner::upload_inst(int i)
             for (int bb = 0; bb < 40; ++bb) gpw[(size_t)k * 40 + bb] = std::exp(-db * std::ldexp(1.0, bb - 20));
         }
     }
-    const std::vector<EMoments> em(h.real ? kMomentParts : 0, no_moments());
+    const std::vector<long long> emin(h.real ? kMinParts : 0, kNoEnergy);
     std::vector<uint32_t> Rk0((size_t)h.nT + 1, 0u);
     Rk0[0] = (uint32_t)h.R;
     int32_t ctl[4] = {0, 0, 0, 0};
@@ -672,7 +664,7 @@ int Runner::upload_inst(int i)
     else
         put(lay.J, h.J.data(), h.J.size());
     put(lay.bq, bq.data(), bq.size() * 4);
-    if (!em.empty()) put(lay.emom, em.data(), em.size() * sizeof(EMoments));
+    if (!emin.empty()) put(lay.emin, emin.data(), emin.size() * 8);
     if (!gpw.empty()) put(lay.gpw, gpw.data(), gpw.size() * 8);
     if (!cmj.empty()) put(lay.cmj, cmj.data(), cmj.size() * 4);
     put(lay.pos, pos16.data(), pos16.size() * 2);
@@ -795,7 +787,7 @@ int Runner::build_work(const std::vector<int> &active)
             if (h.real) wblk.push_back(Work{ii, (uint32_t)r, 0u, 0u});
         }
         for (const Work &w : gather_items(ii, h.Rcap, h.srow_bytes)) gath.push_back(w);
-        if (!h.real) post.push_back(Work{ii, 0u, kRoleMeasure, 0u});
+        post.push_back(Work{ii, 0u, kRoleMeasure, 0u});
         int64_t fp2 = 1;
         while (fp2 < h.R) fp2 <<= 1;
         for (int64_t f = 0; f < fp2; f += 2048) post.push_back(Work{ii, (uint32_t)f, kRoleFamilies, 0u});
@@ -1340,11 +1332,11 @@ int Runner::set_state(int i, const pamc_state *st)
     HIPCHK(hipMemcpy(h.ctl, ctl, 12, hipMemcpyHostToDevice), "write ctl");
     HIPCHK(hipMemcpy(h.dev.status, status, 8, hipMemcpyHostToDevice), "write status");
     HIPCHK(hipMemcpy(h.dev.Rk + st->step, &Rk, 4, hipMemcpyHostToDevice), "write Rk");
-    // parts of the energy histogram or moments, which a step that failed in
+    // parts of the energy histogram or minimum, which a step that failed in
     // its resampling or the last step left behind
     if (h.real) {
-        const std::vector<EMoments> em(kMomentParts, no_moments());
-        HIPCHK(hipMemcpy(h.dev.emom, em.data(), em.size() * sizeof(EMoments), hipMemcpyHostToDevice), "clear the moments");
+        const std::vector<long long> emin(kMinParts, kNoEnergy);
+        HIPCHK(hipMemcpy(h.dev.emin, emin.data(), emin.size() * 8, hipMemcpyHostToDevice), "clear the lowest energies");
     } else {
         HIPCHK(hipMemset(h.dev.hist, 0, (size_t)h.dev.nlev * 4), "clear the histogram");
         HIPCHK(hipMemset(h.dev.loff, 0, (size_t)h.Rcap * 4), "clear the histogram");

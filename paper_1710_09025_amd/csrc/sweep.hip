@@ -396,7 +396,7 @@ __device__ __forceinline__ void sweep_tile_cq(const Inst &I, int k, uint8_t *lds
     if (io.map)
         for (int q = threadIdx.x; q < nrows; q += blockDim.x) io.fdst[r0 + q] = io.fsrc[io.map[r0 + q]];
     if (phase == 1) return;
-    tile_moments_real(I, io, eacc, r0, nrows, I.Jtot);
+    tile_energies_real(I, io, eacc, r0, nrows, I.Jtot);
     __syncthreads();
     uint32_t *fam = reinterpret_cast<uint32_t *>(eacc);  // (the energies are out)
     for (int q = threadIdx.x; q < nrows; q += blockDim.x) fam[q] = io.fsrc[io.map ? io.map[r0 + q] : r0 + q];

@@ -94,24 +94,33 @@ __device__ __forceinline__ void build_table(const RBInst &X, const RQInst &Q, ui
 {
     constexpr int H = NB / 2, P = 1 << H;
     const int entry = 4 * X.plane, sites = 4 * X.gmax * X.ncol;
-    // kThr: pattern and complement have opposite dE: 2^(NB-1) pairs a site,
-    // eight pairs an item
-    const int items = KIND == kRQThr && !fields && NB == 6 ? 4 : 1;
-    for (int it = tid; it < sites * items; it += blockDim.x) {
+    // kThr: pattern and complement have opposite dE, 2^(NB-1) pairs a site in
+    // rows of eight; several threads a site where there are more threads
+    constexpr int kRows = NB == 6 ? 4 : 1;
+    const int parts = KIND == kRQThr && !fields ? max(1, min(kRows, (int)blockDim.x / sites)) : 1;
+    for (int it = tid; it < sites * parts; it += blockDim.x) {
         const int part = it / sites, site = it - part * sites;
         const int ci = site / X.gmax, g = site - ci * X.gmax, c = ci >> 2, i = ci & 3;
         if (g >= pick3(X.gcs, c)) continue;
-        int32_t J[NB];
+        int32_t J[NB], lo[8];
 #pragma unroll
         for (int d = 0; d < NB; ++d) J[d] = coupling(X, Q, c, g, d, i);
         uint32_t *t = table + i * X.plane + pick3(X.base, c) + g;
         if (KIND == kRQThr && !fields) {
-#pragma unroll 2
-            for (int p = 8 * part; p < 8 * part + 8; ++p) {
-                const int32_t dE = 2 * bond_sum<NB>(J, 0, NB, (uint32_t)p);
-                const uint32_t T = threshold(Q.bq, abs(dE));
-                t[p * entry] = dE > 0 ? T : 0xFFFFFFFFu;
-                t[((1 << NB) - 1 - p) * entry] = dE < 0 ? T : 0xFFFFFFFFu;
+            // (the first three bonds' sums of every pattern)
+#pragma unroll
+            for (int p = 0; p < 8; ++p) lo[p] = bond_sum<NB>(J, 0, 3, (uint32_t)p);
+#pragma unroll 1
+            for (int row = part; row < kRows; row += parts) {
+                const int32_t hi = bond_sum<NB>(J, 3, NB, (uint32_t)row);
+                uint32_t *tp = t + 8 * row * entry, *tc = t + ((1 << NB) - 1 - 8 * row) * entry;
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const int32_t dE = 2 * (lo[p] + hi);
+                    const uint32_t T = threshold(Q.bq, abs(dE));
+                    tp[p * entry] = dE > 0 ? T : 0xFFFFFFFFu;
+                    tc[-p * entry] = dE < 0 ? T : 0xFFFFFFFFu;
+                }
             }
         } else {
 #pragma unroll
@@ -504,7 +513,7 @@ __device__ __forceinline__ void rq_tile(const Inst &I, int k, uint32_t *table, i
                 eacc[q] = (unsigned long long)(X.ncol == 2 ? -h : -(h / 2));
             }
             __syncthreads();
-            tile_moments_real(I, io, eacc, row0, nr, 0);
+            tile_energies_real(I, io, eacc, row0, nr, 0);
             tile_family_count(I, fam, nr);
             __syncthreads();
         }

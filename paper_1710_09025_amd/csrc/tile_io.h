@@ -117,65 +117,25 @@ __device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t 
     }
 }
 
-// Energies of the tile's rows (real couplings; E = the accumulated sums - base) and
-// their moments, added to the step's accumulators once per workgroup: min,
-// max, sum E (two's complement) and sum E^2 as an exact 128-bit integer
-// (low word added first; its carry goes into the high word).  The workgroups
-// add to kMomentParts accumulators in turn (atomics on one address follow each
-// other about 0.1 us apart).
-__device__ __forceinline__ void tile_moments_real(const Inst &I, const TileIO &io, const unsigned long long *eacc,
-                                                  int r0, int nrows, long long base)
+// Energies of the tile's rows (real couplings; E = the accumulated sums -
+// base), and the lowest of them; the other moments are taken with the weights.
+// (All of them here, with 128-bit sums through LDS and five atomics a
+// workgroup, took 7 us of a workgroup's 170 at L = 8, R = 10^5.)
+__device__ __forceinline__ void tile_energies_real(const Inst &I, const TileIO &io, const unsigned long long *eacc,
+                                                   int r0, int nrows, long long base)
 {
-    __shared__ long long smin[16], smax[16];
-    __shared__ unsigned long long ssum[16], slo[16], shi[16];
-    long long lmin = 0x7FFFFFFFFFFFFFFFll, lmax = -0x7FFFFFFFFFFFFFFFll - 1;
-    unsigned long long s1 = 0ull, lo = 0ull, hi = 0ull;
-    for (int q = threadIdx.x; q < nrows; q += blockDim.x) {
-        const long long E = (long long)eacc[q] - base;
-        io.Eqdst[r0 + q] = E;
-        lmin = E < lmin ? E : lmin;
-        lmax = E > lmax ? E : lmax;
-        s1 += (unsigned long long)E;
-        const unsigned __int128 e2 = (unsigned __int128)((__int128)E * (__int128)E);
-        const unsigned long long l2 = (unsigned long long)e2;
-        const unsigned long long nl = lo + l2;
-        hi += (unsigned long long)(e2 >> 64) + (nl < lo ? 1ull : 0ull);
-        lo = nl;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        const long long omin = __shfl_xor(lmin, off), omax = __shfl_xor(lmax, off);
-        const unsigned long long os = __shfl_xor(s1, off), ol = __shfl_xor(lo, off), oh = __shfl_xor(hi, off);
-        lmin = omin < lmin ? omin : lmin;
-        lmax = omax > lmax ? omax : lmax;
-        s1 += os;
-        const unsigned long long nl = lo + ol;
-        hi += oh + (nl < lo ? 1ull : 0ull);
-        lo = nl;
-    }
-    const int wave = threadIdx.x >> 6, nw = ((int)blockDim.x + 63) >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        smin[wave] = lmin;
-        smax[wave] = lmax;
-        ssum[wave] = s1;
-        slo[wave] = lo;
-        shi[wave] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < nw; ++v) {
-            lmin = smin[v] < lmin ? smin[v] : lmin;
-            lmax = smax[v] > lmax ? smax[v] : lmax;
-            s1 += ssum[v];
-            const unsigned long long nl = lo + slo[v];
-            hi += shi[v] + (nl < lo ? 1ull : 0ull);
-            lo = nl;
+    for (int q0 = (int)(threadIdx.x & ~63u); q0 < nrows; q0 += blockDim.x) {
+        const int q = q0 + (int)(threadIdx.x & 63u);
+        long long e = kNoEnergy;
+        if (q < nrows) {
+            e = (long long)eacc[q] - base;
+            io.Eqdst[r0 + q] = e;
         }
-        EMoments *m = I.emom + blockIdx.x % kMomentParts;
-        atomicMin(&m->emin, lmin);
-        atomicMax(&m->emax, lmax);
-        atomicAdd(&m->sum, s1);
-        const unsigned long long old = atomicAdd(&m->sq_lo, lo);
-        atomicAdd(&m->sq_hi, hi + (old + lo < old ? 1ull : 0ull));
+        for (int off = 32; off > 0; off >>= 1) {
+            const long long o = __shfl_xor(e, off);
+            e = o < e ? o : e;
+        }
+        if (q == q0) atomicMin(I.emin + blockIdx.x % kMinParts, e);
     }
 }
 
