@@ -53,8 +53,9 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // 1024 threads (even L up to 20, odd L up to 21); no kernel beyond it.  The
 // square lattice (dim = 2) runs only with real couplings.  The replica-word
 // kernels sweep what their tables of the sites' thresholds or bond sums leave
-// LDS for (cubic: L <= 8 and L <= 13, square: L <= 48 and all); the quad
-// kernel the rest (L = 14 ... 21).
+// LDS for (cubic: L <= 8 and L <= 13, square: L <= 45 and all; thresholds that
+// leave room for one set only are slower than bond sums, 879 attempts per ns
+// against 1017 at L = 48); the quad kernel the rest (L = 14 ... 21).
 LayoutInfo layout_for(int L, bool real, int dim)
 {
     LayoutInfo li{};
@@ -89,7 +90,7 @@ LayoutInfo layout_for(int L, bool real, int dim)
                (size_t)cm_slot_bytes(li.row_bytes, li.tpr, 4) * cm_replicas_per_block(li.tpr) + 32 + 8 * 64 <= kMaxSweepLds) {
         const int thr = dim == 3 ? kSweepRQ3Thr : kSweepRQ2Thr, field = dim == 3 ? kSweepRQ3Field : kSweepRQ2Field;
         const int plane = rb_plane(li.row_bytes);
-        li.variant = rq_lds(thr, plane, 32, 1) <= kMaxWordLds     ? thr
+        li.variant = rq_lds(thr, plane, 32, 2) <= kMaxWordLds     ? thr
                      : rq_lds(field, plane, 32, 1) <= kMaxWordLds ? field
                      : li.ncol == 2                               ? kSweepCQ2
                                                                   : kSweepCQ3;

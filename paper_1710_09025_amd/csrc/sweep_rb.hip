@@ -403,15 +403,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
 
 // ---------------------------------------------------------------------------
 // Workgroup form of the lattice whose largest colour has G blocks: one set
-// whose waves waste few lanes (G close to a multiple of 64, or beyond 1024
-// threads, when each thread takes several blocks in turn), else several sets
-// with their blocks side by side.
+// whose waves waste few lanes (up to a quarter, or beyond 1024 threads, when
+// each thread takes several blocks in turn), else several sets with their
+// blocks side by side.  (L = 13, G = 194, R = 10^5: one set in four waves 1072
+// us a launch, five sets in 16 waves 1274: a barrier for 16 waves after every
+// colour, and the replica's part of the draws per lane.)
 // ---------------------------------------------------------------------------
 bool rb_uniform(int G)
 {
     if (G > 1024) return true;
     const int waves = (G + 63) / 64;
-    return G >= 48 && 100 * G >= 84 * 64 * waves;
+    return G >= 48 && 100 * G >= 75 * 64 * waves;
 }
 
 int rb_threads(int G, int sets)

@@ -11,7 +11,7 @@
 //   kThr   the threshold itself, one entry for each of the 2^NB patterns
 //          (the recipe of step_common.h, evaluated once per site and pattern):
 //          an attempt is its draw, one LDS read and a compare.  256 bytes a
-//          site on the cubic lattice (L <= 8), 64 on the square one (L <= 48);
+//          site on the cubic lattice (L <= 8), 64 on the square one (L <= 45);
 //   kField the bond sums of two halves of the bonds, 64 bytes a site (L <= 13),
 //          32 on the square lattice (all L).  The decision compares log2 of
 //          the draw with the move's exponent and takes the exact recipe where

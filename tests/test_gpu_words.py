@@ -46,6 +46,8 @@ CASES = [
     ("real", 3, 13, 40, 4, 2, 6.0, {}),
     ("real", 3, 14, 9, 4, 2, 6.0, {}),
     ("real", 2, 5, 500, 8, 3, 20.0, dict(tile_rows=6, group_replicas=64)),
+    ("real", 2, 45, 60, 4, 2, 6.0, {}),
+    ("real", 2, 46, 60, 4, 2, 6.0, {}),
     ("real", 2, 48, 60, 4, 2, 6.0, {}),
     ("real", 2, 49, 60, 4, 2, 6.0, {}),
     ("real", 2, 64, 33, 4, 2, 6.0, dict(tile_rows=8, group_replicas=8)),
