@@ -203,14 +203,16 @@ __device__ __forceinline__ void rb_sweeps(const RBInst &X, int k, uint32_t *lds,
     uint32_t *sp = UNI ? lds : lds + (act ? set : 0) * 4 * X.plane;
     const uint32_t rb = (uint32_t)(UNI ? r0 : r0 + set * m);
     const int last = X.gmax - 1;  // (records past a colour's blocks are zeros)
+    const int wave0 = UNI ? scalar(tid & ~63) : 0;
     Record rec = load_record(X, 0, min(g0, last));
     for (int t = t0; t < t1; ++t) {
         if (even) even_progress(t, t0, t1);
         for (int c = 0; c < X.ncol; ++c) {
             const int nc = c + 1 < X.ncol ? c + 1 : 0;
-            for (int first = 0; first <= last; first += step) {
+            // (UNI: a wave past the last block draws nothing)
+            for (int first = 0; wave0 + first <= last; first += step) {
                 const int g = g0 + first;
-                const bool more = first + step <= last;
+                const bool more = wave0 + first + step <= last;
                 rb_block<UNI, MODE>(X, sp, tab, th, c, min(g, last), act && g < pick3(X.gcs, c), rb, m, k, t, rec, more ? c : nc,
                                     min(more ? g + step : g0, last));
             }
@@ -418,10 +420,11 @@ bool rb_uniform(int G)
 
 int rb_threads(int G, int sets)
 {
-    if (G > 1024) {
-        const int n = (G + 1023) / 1024;  // blocks per thread
-        return (((G + n - 1) / n) + 63) / 64 * 64;
-    }
+    // beyond 1024 blocks 16 waves, four a SIMD, of which the first take one
+    // block more than the last: the SIMDs' shares differ by one (L = 24,
+    // G = 1728: 7 at most, R = 4000 in 267 us; two blocks for each of 14 waves
+    // were 8 and 308 us)
+    if (G > 1024) return 1024;
     return (G * sets + 63) / 64 * 64;
 }
 
