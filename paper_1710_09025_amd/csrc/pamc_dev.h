@@ -108,11 +108,7 @@ struct Inst {
     // real couplings: per colour and Philox block, the 24 storage positions
     // of the 6 neighbours of its 4 sites; word 24 is the mask of real
     // (non-padding) sites, one 0x01 per byte.
-    const uint16_t *cmdesc;  // [ncol][gmax][32]
     int32_t cbase[3];   // first storage position of each colour
-    int32_t tpr;        // real couplings: threads per replica quad
-    int32_t plane_bytes;// real couplings: LDS stride of a replica quad's byte planes (>= row_bytes)
-    int32_t slot_bytes; // real couplings: LDS stride of the replica quads' slots (bank-skewed)
     int32_t ncs[3];     // sites per colour
     int32_t gcs[3];     // Philox blocks per colour, ceil(ncs / 4)
     int32_t gmax;
@@ -121,10 +117,9 @@ struct Inst {
     double *wrep;       // [Rcap] resampling weight of each row
     double *wpart;      // [nblk] pairwise-tree roots of the 1024-row blocks
     long long *emin;    // [kMinParts], lowest energies of the step being swept
-    const int32_t *cmj; // [ncol][gmax][24] coupling of each neighbour bond, in cmdesc order
+    const int32_t *cmj; // [ncol][gmax][24] couplings of a block's bonds, [direction][site]
     const float *bq;    // [nT] beta_k 2^-20 rounded to binary32
     const double *gpw;  // [nT][40] exp(-(beta_{k+1} - beta_k) 2^(b-20)), host libm
-    int64_t Jtot;       // sum of all couplings
     // progress and records
     int32_t *k;         // current step (device scalar)
     int32_t *cur;       // buffer holding the current population (0/1)

@@ -53,9 +53,11 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // 1024 threads (even L up to 20, odd L up to 21); no kernel beyond it.  The
 // square lattice (dim = 2) runs only with real couplings.  The replica-word
 // kernels sweep what their tables of the sites' thresholds or bond sums leave
-// LDS for (cubic: L <= 8 and L <= 13, square: L <= 45 and all; thresholds that
-// leave room for one set only are slower than bond sums, 879 attempts per ns
-// against 1017 at L = 48); the quad kernel the rest (L = 14 ... 21).
+// LDS for: thresholds on cubic lattices up to L = 8 and square ones up to 45,
+// bond sums up to L = 12 and on all other square ones, couplings beyond.
+// (Thresholds that leave room for one set only are slower than bond sums, 879
+// attempts per ns against 1017 at L = 48 on the square lattice, and bond sums
+// than couplings, 490 against 783 at L = 13.)
 LayoutInfo layout_for(int L, bool real, int dim)
 {
     LayoutInfo li{};
@@ -91,9 +93,8 @@ LayoutInfo layout_for(int L, bool real, int dim)
         const int thr = dim == 3 ? kSweepRQ3Thr : kSweepRQ2Thr, field = dim == 3 ? kSweepRQ3Field : kSweepRQ2Field;
         const int plane = rb_plane(li.row_bytes);
         li.variant = rq_lds(thr, plane, 32, 2) <= kMaxWordLds     ? thr
-                     : rq_lds(field, plane, 32, 1) <= kMaxWordLds ? field
-                     : li.ncol == 2                               ? kSweepCQ2
-                                                                  : kSweepCQ3;
+                     : rq_lds(field, plane, 32, dim == 3 ? 4 : 1) <= kMaxWordLds ? field
+                     : kSweepRQ3Bonds;
     } else {
         li.valid = false;
     }
@@ -113,7 +114,7 @@ struct Carve {
 
 struct InstLayout {
     size_t ctl, status, sync, spins0, spins1, E0, E1, f0, f1, map, loff, bsum, boff, hist, cnt, fpart, thr,
-        beta, rho, Rt, rbtab, J, pos, lexof, cmdesc, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emin, cmj,
+        beta, rho, Rt, rbtab, J, pos, lexof, Rk, rec, ovl_slot, qhist, Eq0, Eq1, wrep, wpart, emin, cmj,
         bq, gpw, total;
 };
 
@@ -150,12 +151,10 @@ InstLayout layout_of(int L, int64_t R, int64_t Rcap, int nT, int n_ovl, bool pac
     l.beta = c.take((size_t)nT * 8);
     l.rho = c.take((size_t)nT * 8);
     l.Rt = c.take((size_t)nT * 8);
-    const bool cq = li.variant == kSweepCQ2 || li.variant == kSweepCQ3;
-    l.rbtab = c.take(cq ? 16 : (size_t)ncol * gmax * 64);
+    l.rbtab = c.take((size_t)ncol * gmax * 64);
     l.J = c.take((size_t)dim * N * (real ? 4 : 1));
     l.pos = c.take((size_t)N * 2);
     l.lexof = c.take((size_t)li.row_bytes * 2);
-    l.cmdesc = c.take(cq ? (size_t)ncol * gmax * 32 * 2 : 16);
     l.Rk = c.take((size_t)(nT + 1) * 4);
     l.rec = c.take((size_t)nT * sizeof(StepRec));
     l.ovl_slot = c.take((size_t)nT * 4);
@@ -488,7 +487,6 @@ int Runner::upload_inst(int i)
     d.rb_plane = rb_plane(h.row_bytes);
     d.pos = (const uint16_t *)(b + lay.pos);
     d.lexof = (const uint16_t *)(b + lay.lexof);
-    d.cmdesc = (const uint16_t *)(b + lay.cmdesc);
     d.k = (int32_t *)(b + lay.ctl);
     d.cur = d.k + 1;
     d.mapped = d.k + 2;
@@ -509,8 +507,6 @@ int Runner::upload_inst(int i)
     d.cmj = (const int32_t *)(b + lay.cmj);
     d.bq = (const float *)(b + lay.bq);
     d.gpw = (const double *)(b + lay.gpw);
-    d.Jtot = 0;
-    for (int32_t v : h.Jq) d.Jtot += v;
     {
         const int64_t nchunks = std::max<int64_t>(1, fp2 / 2048);
         const int64_t novl = (h.Rcap / 2 + kOvlPairs - 1) / kOvlPairs;
@@ -560,9 +556,6 @@ int Runner::upload_inst(int i)
     };
     const LayoutInfo li = layout_for(L, h.real != 0, h.dim);
     for (int c = 0; c < 3; ++c) d.cbase[c] = li.cbase[c];
-    d.tpr = li.tpr;
-    d.plane_bytes = cm_plane_bytes(h.row_bytes);
-    d.slot_bytes = cm_slot_bytes(h.row_bytes, li.tpr, h.real ? 4 : 8);
     // storage position of each site
     h.lex_pos.resize(N);
     std::vector<uint16_t> pos16((size_t)N);
@@ -578,16 +571,11 @@ int Runner::upload_inst(int i)
     // On the square lattice the two z entries of a site point at the site
     // itself with coupling 0 and are not read.  Padding sites point at
     // themselves.
-    std::vector<uint16_t> cmdesc;
     std::vector<int32_t> cmj;
     std::vector<uint32_t> rbtab;
     std::vector<int> site_at((size_t)3 * N, -1);
     for (int s = 0; s < N; ++s) site_at[(size_t)col[s] * N + rank[s]] = s;
-    const bool cq = li.variant == kSweepCQ2 || li.variant == kSweepCQ3;
-    if (cq)
-        cmdesc.assign((size_t)h.ncol * d.gmax * 32, 0);
-    else
-        rbtab.assign((size_t)h.ncol * d.gmax * 16, 0u);
+    rbtab.assign((size_t)h.ncol * d.gmax * 16, 0u);
     if (h.real) cmj.assign((size_t)h.ncol * d.gmax * 24, 0);
     const bool sq = h.dim == 2;
     for (int c = 0; c < h.ncol; ++c)
@@ -614,25 +602,16 @@ int Runner::upload_inst(int i)
                 }
                 for (int dd = 0; dd < 6; ++dd) {
                     const int e = 4 * dd + bb;
-                    if (cq) {
-                        cmdesc[blk * 32 + e] = (uint16_t)nbp[dd];
-                    } else {
-                        const uint32_t word = (uint32_t)((nbp[dd] & 3) * d.rb_plane + (nbp[dd] >> 2));
-                        rbtab[blk * 16 + (e >> 1)] |= word << (16 * (e & 1));
-                    }
+                    const uint32_t word = (uint32_t)((nbp[dd] & 3) * d.rb_plane + (nbp[dd] >> 2));
+                    rbtab[blk * 16 + (e >> 1)] |= word << (16 * (e & 1));
                     if (h.real)
                         cmj[blk * 24 + e] = jv[dd];
                     else if (jv[dd] < 0)
                         rbtab[blk * 16 + 12] |= 1u << e;
                 }
             }
-            if (cq) {
-                cmdesc[blk * 32 + 24] = (uint16_t)(vmask & 0xFFFFu);
-                cmdesc[blk * 32 + 25] = (uint16_t)(vmask >> 16);
-            } else {
-                for (int bb = 0; bb < 4; ++bb)
-                    if ((vmask >> (8 * bb)) & 1u) rbtab[blk * 16 + 13] |= 1u << bb;
-            }
+            for (int bb = 0; bb < 4; ++bb)
+                if ((vmask >> (8 * bb)) & 1u) rbtab[blk * 16 + 13] |= 1u << bb;
         }
     // real couplings: beta_k 2^-20 in binary32 and the weight factors
     // exp(-(beta_{k+1} - beta_k) 2^(b-20)), b < 40, host libm
@@ -659,7 +638,7 @@ int Runner::upload_inst(int i)
     put(lay.beta, h.beta.data(), h.beta.size() * 8);
     put(lay.rho, rho.data(), rho.size() * 8);
     put(lay.Rt, h.pop.data(), h.pop.size() * 8);
-    if (!rbtab.empty()) put(lay.rbtab, rbtab.data(), rbtab.size() * 4);
+    put(lay.rbtab, rbtab.data(), rbtab.size() * 4);
     if (h.real)
         put(lay.J, h.Jq.data(), h.Jq.size() * 4);
     else
@@ -670,7 +649,6 @@ int Runner::upload_inst(int i)
     if (!cmj.empty()) put(lay.cmj, cmj.data(), cmj.size() * 4);
     put(lay.pos, pos16.data(), pos16.size() * 2);
     put(lay.lexof, lexof16.data(), lexof16.size() * 2);
-    if (!cmdesc.empty()) put(lay.cmdesc, cmdesc.data(), cmdesc.size() * 2);
     put(lay.Rk, Rk0.data(), Rk0.size() * 4);
     put(lay.ovl_slot, h.ovl_slot.data(), h.ovl_slot.size() * 4);
     // host vectors must outlive the async copies
@@ -768,8 +746,6 @@ int Runner::build_work(const std::vector<int> &active)
         sh.variant = h.variant;
         sh.tile_rows = h.tile_rows;
         sh.row_bytes = h.row_bytes;
-        sh.tpr = h.tpr;
-        sh.rp = h.rp;
         sh.G = h.dev.gmax;
         sh.plane = h.dev.rb_plane;
         sh.ncol = h.ncol;

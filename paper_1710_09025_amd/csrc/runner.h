@@ -28,8 +28,8 @@ struct HostInst {
     int icm = 0;                       // cluster-move rounds per step
     double icm_bmin = 0.0;             // ... at steps with beta_k >= icm_bmin
     int srow_bytes = 0;                // bytes per stored spin row
-    int tpr = 0;                       // real couplings: threads per replica quad
-    int rp = 0;                        // replica quads a sweep workgroup holds at once
+    int tpr = 0;                       // threads of a replica quad (what the shape options may ask for)
+    int rp = 0;                        // quads of replicas a sweep workgroup holds at once
     int mrep = 0, sets = 0;            // replicas per word, sets of them per pass of a workgroup
     bool own_shape = false;            // the shape was asked for or measured: launches keep it
     int64_t R = 0, Rcap = 0;
@@ -90,7 +90,7 @@ struct LayoutInfo {
     int cbase[3];     // first storage position of each colour
     int row_bytes;    // bytes per replica row (multiple of 16)
     int gmax;         // Philox blocks of the largest colour
-    int tpr;          // threads per replica quad (real couplings)
+    int tpr;          // threads of a replica quad (what the shape options may ask for)
 };
 LayoutInfo layout_for(int L, bool real = false, int dim = 3);
 

@@ -12,22 +12,26 @@
 //          (the recipe of step_common.h, evaluated once per site and pattern):
 //          an attempt is its draw, one LDS read and a compare.  256 bytes a
 //          site on the cubic lattice (L <= 8), 64 on the square one (L <= 45);
-//   kField the bond sums of two halves of the bonds, 64 bytes a site (L <= 13),
-//          32 on the square lattice (all L).  The decision compares log2 of
-//          the draw with the move's exponent and takes the exact recipe where
-//          the two are closer than the error of either.
+//   kField the bond sums of two halves of the bonds, 64 bytes a site
+//          (L <= 12), 32 on the square lattice (all L).  The decision compares
+//          log2 of the draw with the move's exponent and takes the exact
+//          recipe where the two are closer than the error of either;
+//   kBonds (cubic, L >= 13) the three couplings that start at the site, 12
+//          bytes; a lane keeps its block's in registers through a colour step
+//          and sums them for each replica.  The decision as in kField.
 // Entry e of all sites is one array, so that a lane's bank follows from its
 // site alone (site planes are multiples of 64 words): no entry chosen by any
 // lane conflicts with another's.
 //
-// What bounds it: instruction issue, 16 instructions an attempt (kThr) or 28
-// (kField) with two to four waves a SIMD; the tables fill the LDS.  Attempts
-// per ns at 10 sweeps a step, beta = 1.5, against a form that swept replica
-// quads with neighbours and couplings in registers (53 instructions an
-// attempt, two waves a SIMD): cubic L = 8, R = 10^5: 542 -> 1312; L = 10,
-// R = 5 10^4: 527 -> 1098; L = 12, R = 3 10^4: 459 -> 992; square L = 32,
-// R = 5 10^4: 595 -> 1725; L = 64, R = 2 10^4: 648 -> 998.  That form
-// (sweep.hip) stays where the tables do not fit: cubic L >= 14.
+// What bounds it: instruction issue, 16 instructions an attempt (kThr), 28
+// (kField) or 32 (kBonds) with two to four waves a SIMD; the tables fill the
+// LDS.  Attempts per ns at 10 sweeps a step, beta = 1.5, against a form that
+// swept replica quads with neighbours and couplings in registers (53
+// instructions an attempt, two waves a SIMD and spills beyond L = 17): cubic
+// L = 8, R = 10^5: 542 -> 1448; L = 10, R = 5 10^4: 527 -> 1098; L = 12,
+// R = 3 10^4: 459 -> 978; L = 13, R = 2 10^4: 308 -> 783; L = 16, R = 2 10^4:
+// 584 -> 1010; L = 20, R = 10^4: 263 -> 926; square L = 32, R = 5 10^4: 595 ->
+// 1740; L = 64, R = 2 10^4: 648 -> 1003.
 #include <algorithm>
 
 #include "launch.h"
@@ -106,7 +110,10 @@ __device__ __forceinline__ void build_table(const RBInst &X, const RQInst &Q, ui
 #pragma unroll
         for (int d = 0; d < NB; ++d) J[d] = coupling(X, Q, c, g, d, i);
         uint32_t *t = table + i * X.plane + pick3(X.base, c) + g;
-        if (KIND == kRQThr && !fields) {
+        if (KIND == kRQBonds) {
+#pragma unroll
+            for (int d = 0; d < NB; d += 2) t[(d >> 1) * entry] = (uint32_t)J[d];
+        } else if (KIND == kRQThr && !fields) {
             // (the first three bonds' sums of every pattern)
 #pragma unroll
             for (int p = 0; p < 8; ++p) lo[p] = bond_sum<NB>(J, 0, 3, (uint32_t)p);
@@ -155,6 +162,41 @@ __device__ __forceinline__ void block_bonds(const uint32_t *lds, const Record &r
 #pragma unroll
         for (int d = 0; d < NB; ++d) f.x[i][d] ^= f.own[i];
     }
+}
+
+// Couplings of a block's bonds (kRQBonds): the one to s + e_d is entry d of
+// the site, the one to s - e_d entry d of that neighbour.
+template <int NB>
+__device__ __forceinline__ void block_couplings(const uint32_t *table, const Record &rec, int own, int plane, int32_t (&J)[4][NB],
+                                                int32_t (&sum)[4])
+{
+    const u32x4 q0 = rec.q[0], q1 = rec.q[1], q2 = rec.q[2];
+    const uint32_t e[12] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y, q2.z, q2.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sum[i] = 0;
+#pragma unroll
+        for (int d = 0; d < NB; ++d) {
+            const uint32_t w = e[2 * d + (i >> 1)];
+            const uint32_t at = d & 1 ? ((i & 1) ? w >> 16 : w & 0xFFFFu) : (uint32_t)(own + i * plane);
+            J[i][d] = (int32_t)table[(d >> 1) * 4 * plane + at];
+            sum[i] += J[i][d];
+        }
+    }
+}
+// acc += a b, factors of 24 bits
+__device__ __forceinline__ void mad24(int32_t &acc, int32_t a, int32_t b)
+{
+    asm("v_mad_i32_i24 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+// Bond sum of a site in replica r: sum J_d (1 - 2 x_d), |J_d| < 2^23.
+template <int NB>
+__device__ __forceinline__ int32_t field_from_bonds(const uint32_t (&x)[NB], const int32_t (&J)[NB], int32_t sum, int r)
+{
+    int32_t a = 0;
+#pragma unroll
+    for (int d = 0; d < NB; ++d) mad24(a, __builtin_amdgcn_sbfe((int)x[d], (uint32_t)r, 1u), J[d]);
+    return sum + 2 * a;
 }
 
 // Within each byte, bit j of a[i] <-> bit i of a[j]: afterwards byte b of a[k]
@@ -253,6 +295,8 @@ __device__ __forceinline__ void rq_block(const RBInst &X, const RQInst &Q, uint3
         rec = load_record(X, next_c, next_g);
     } else {
         block_bonds<NB>(lds, rec, own, plane, f);
+        [[maybe_unused]] int32_t J[4][NB], Jsum[4];
+        if constexpr (KIND == kRQBonds) block_couplings<NB>(table, rec, own, plane, J, Jsum);
         // the next block's record is on its way while this one draws
         rec = load_record(X, next_c, next_g);
         const LaneDraw d = lane_draw(ctr, k, t, k0, k1);
@@ -273,8 +317,9 @@ __device__ __forceinline__ void rq_block(const RBInst &X, const RQInst &Q, uint3
             uint32_t e[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                e[i] = KIND == kRQThr ? entry_of<NB>(tab[i], stride, w[i], at)
-                                      : (uint32_t)field_of<NB>(tab[i], tab2[i], stride, w[i], at);
+                e[i] = KIND == kRQThr     ? entry_of<NB>(tab[i], stride, w[i], at)
+                       : KIND == kRQField ? (uint32_t)field_of<NB>(tab[i], tab2[i], stride, w[i], at)
+                                          : (uint32_t)field_from_bonds<NB>(f.x[i], J[i], Jsum[i], r);
             const uint4 u = replica_draw<UNI>(d, rb + (uint32_t)r, k, k0, k1);
             if constexpr (KIND == kRQThr) {
 #pragma unroll
@@ -298,23 +343,25 @@ __device__ __forceinline__ void rq_block(const RBInst &X, const RQInst &Q, uint3
             for (int r = m - 1; r >= 0; --r) {
                 uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < (KIND == kRQBonds ? 0 : 4); ++i)
 #pragma unroll
                     for (int dd = 0; dd < NB; ++dd) w[i] |= __builtin_amdgcn_ubfe(f.x[i][dd], (uint32_t)r, 1u) << dd;
                 attempt(r, w, 0, acc[0]);
             }
-            if constexpr (KIND == kRQField) again = __builtin_amdgcn_ballot_w64(near < kNear) != 0ull ? 0xFFu : 0u;
+            if constexpr (KIND != kRQThr) again = __builtin_amdgcn_ballot_w64(near < kNear) != 0ull ? 0xFFu : 0u;
         } else {
             uint32_t w[4][8];
-            patterns<NB>(f, w);
+            if constexpr (KIND != kRQBonds) patterns<NB>(f, w);
 #pragma unroll
             for (int kk = 7; kk >= 0; --kk) {
                 near = 1.0f;
-                const uint32_t wk[4] = {w[0][kk], w[1][kk], w[2][kk], w[3][kk]};
+                uint32_t wk[4];
+                if constexpr (KIND != kRQBonds)
+                    for (int i = 0; i < 4; ++i) wk[i] = w[i][kk];
 #pragma unroll
                 for (int b = 3; b >= 0; --b)
                     if (8 * b + kk < m) attempt(8 * b + kk, wk, 8 * b, acc[b]);
-                if constexpr (KIND == kRQField)
+                if constexpr (KIND != kRQThr)
                     again |= __builtin_amdgcn_ballot_w64(near < kNear) != 0ull ? 1u << kk : 0u;
             }
         }
@@ -424,8 +471,12 @@ __device__ __forceinline__ void rq_energy(const RBInst &X, const RQInst &Q, cons
             const int own = pick3(X.base, c) + g;
             Bonds<NB> f;
             block_bonds<NB>(sp, rec, own, X.plane, f);
+            [[maybe_unused]] int32_t J[4][NB], Jsum[4];
             uint32_t w[4][8];
-            patterns<NB>(f, w);
+            if constexpr (KIND == kRQBonds)
+                block_couplings<NB>(table, rec, own, X.plane, J, Jsum);
+            else
+                patterns<NB>(f, w);
             int n = m;  // (opaque, as in rq_block)
             asm volatile("" : "+s"(n));
 #pragma unroll
@@ -438,8 +489,11 @@ __device__ __forceinline__ void rq_energy(const RBInst &X, const RQInst &Q, cons
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const uint32_t *t = table + own + i * X.plane;
-                        const int32_t s =
-                            field_of<NB>(t, t + (4 * X.plane << (NB / 2)), 16u * (uint32_t)X.plane, w[i][kk], 8 * b);
+                        int32_t s;
+                        if constexpr (KIND == kRQBonds)
+                            s = field_from_bonds<NB>(f.x[i], J[i], Jsum[i], r);
+                        else
+                            s = field_of<NB>(t, t + (4 * X.plane << (NB / 2)), 16u * (uint32_t)X.plane, w[i][kk], 8 * b);
                         h += (valid >> i) & 1u ? s : 0;
                     }
                     if constexpr (UNI) {
@@ -460,7 +514,7 @@ template <int NB, int KIND, bool UNI>
 __device__ __forceinline__ void rq_tile(const Inst &I, int k, uint32_t *table, int r0, int nrows, int m, int sets,
                                         int phase)
 {
-    constexpr int words = KIND == kRQThr ? 1 << NB : 2 << (NB / 2);
+    constexpr int words = KIND == kRQThr ? 1 << NB : KIND == kRQField ? 2 << (NB / 2) : NB / 2;
     const int pass = m * sets;
     const TileIO io = tile_io(I);
     const RBInst X = rb_inst(I, io);
@@ -486,7 +540,7 @@ __device__ __forceinline__ void rq_tile(const Inst &I, int k, uint32_t *table, i
             src[q] = r;
             eacc[q] = 0ull;
         }
-        if (KIND == kRQField ? q0 == 0 : !all) build_table<NB, KIND>(X, Q, table, false, tid);
+        if (KIND != kRQThr ? q0 == 0 : !all) build_table<NB, KIND>(X, Q, table, false, tid);
         __syncthreads();
         rb_load<false>(X, lds, src, m, sets, tid);
         for (int q = tid; q < nr; q += blockDim.x) fam[q] = io.fsrc[src[q]];
@@ -544,12 +598,15 @@ __global__ __launch_bounds__(1024) void k_sweep_rq(const Inst *insts, const Work
 // sweeps a step.
 int rq_kind(int variant, int rows)
 {
+    if (variant == kSweepRQ3Bonds) return kRQBonds;
     return (variant == kSweepRQ3Thr && rows >= 16) || (variant == kSweepRQ2Thr && rows >= 4) ? kRQThr : kRQField;
 }
 int64_t rq_lds(int variant, int plane, int m, int sets)
 {
     const bool cubic = variant == kSweepRQ3Thr || variant == kSweepRQ3Field;
-    const int words = rq_kind(variant, m * sets) == kRQThr ? (cubic ? 64 : 16) : (cubic ? 16 : 8);
+    const int words = variant == kSweepRQ3Bonds                  ? 3
+                      : rq_kind(variant, m * sets) == kRQThr ? (cubic ? 64 : 16)
+                                                             : (cubic ? 16 : 8);
     return (int64_t)16 * plane * words + (int64_t)(16 * plane + 512) * sets;
 }
 
@@ -566,6 +623,7 @@ hipError_t sweep_rq_init()
     const void *fns[] = {
         (const void *)&k_sweep_rq<6, kRQThr, true>,   (const void *)&k_sweep_rq<6, kRQThr, false>,
         (const void *)&k_sweep_rq<6, kRQField, true>, (const void *)&k_sweep_rq<6, kRQField, false>,
+        (const void *)&k_sweep_rq<6, kRQBonds, true>, (const void *)&k_sweep_rq<6, kRQBonds, false>,
         (const void *)&k_sweep_rq<4, kRQThr, true>,   (const void *)&k_sweep_rq<4, kRQThr, false>,
         (const void *)&k_sweep_rq<4, kRQField, true>, (const void *)&k_sweep_rq<4, kRQField, false>,
     };
@@ -580,7 +638,7 @@ void launch_sweep_rq(const SweepShape &sh, const Inst *insts, const Work *work, 
 {
     const bool uni = rq_uniform(sh.G);
     const int nt = rq_threads(sh.G, sh.sets);
-    const int nb = sh.variant == kSweepRQ3Thr || sh.variant == kSweepRQ3Field ? 6 : 4;
+    const int nb = sh.variant == kSweepRQ2Thr || sh.variant == kSweepRQ2Field ? 4 : 6;
     const int kind = rq_kind(sh.variant, sh.M * sh.sets);
     const size_t lds = (size_t)rq_lds(sh.variant, sh.plane, sh.M, sh.sets);
 #define PAMC_RQ(NB, KIND)                                                                                             \
@@ -592,6 +650,7 @@ void launch_sweep_rq(const SweepShape &sh, const Inst *insts, const Work *work, 
     }
     PAMC_RQ(6, kRQThr)
     PAMC_RQ(6, kRQField)
+    PAMC_RQ(6, kRQBonds)
     PAMC_RQ(4, kRQThr)
     PAMC_RQ(4, kRQField)
 #undef PAMC_RQ

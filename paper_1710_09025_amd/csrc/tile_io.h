@@ -1,7 +1,7 @@
 // tile_io.h -- device routines shared by the sweep kernels: the rows of a tile
 // (through the copy map or in place, one byte or one bit per spin), the byte
 // transpose between rows and replica words, and the end of a sweep workgroup
-// (energies, family counts, the election of the measuring workgroup).
+// (energies, family counts).
 #pragma once
 #include "pamc_dev.h"
 #include "step_common.h"
@@ -9,18 +9,7 @@
 namespace pamc {
 
 // Packed spin rows: bit p of a row (bit p & 7 of byte p >> 3) is the spin at
-// storage position p.  Kernels work on one byte per position in LDS; 16
-// stored bits are one 16-byte LDS vector.
-__device__ __forceinline__ uint32_t bits_to_bytes4(uint32_t nib)
-{
-    // bit i of the nibble lands on bit 8 i: nib + (nib << 7) + (nib << 14) + (nib << 21)
-    return (nib * 0x00204081u) & 0x01010101u;
-}
-__device__ __forceinline__ uint4 bits_to_bytes16(uint32_t b)
-{
-    return make_uint4(bits_to_bytes4(b & 15u), bits_to_bytes4((b >> 4) & 15u), bits_to_bytes4((b >> 8) & 15u),
-                      bits_to_bytes4((b >> 12) & 15u));
-}
+// storage position p.
 __device__ __forceinline__ uint32_t bytes_to_bits4(uint32_t w)
 {
     // byte i (0 or 1) lands on bit 24 + i of w * (2^24 + 2^17 + 2^10 + 2^3)
@@ -67,21 +56,6 @@ __device__ __forceinline__ TileIO tile_io(const Inst &I)
     io.Edst = out ? e1 : e0;
     io.Eqdst = out ? q1 : q0;
     return io;
-}
-
-// 16-byte LDS vector c of stored row `row`: a copy, or 16 stored bits
-// expanded to bytes.
-__device__ __forceinline__ uint4 stored_vec(const TileIO &io, const uint8_t *row, int c)
-{
-    if (io.packed) return bits_to_bytes16(reinterpret_cast<const uint16_t *>(row)[c]);
-    return reinterpret_cast<const uint4 *>(row)[c];
-}
-__device__ __forceinline__ void store_vec(const TileIO &io, uint8_t *row, int c, uint4 v)
-{
-    if (io.packed)
-        reinterpret_cast<uint16_t *>(row)[c] = (uint16_t)bytes_to_bits16(v);
-    else
-        reinterpret_cast<uint4 *>(row)[c] = v;
 }
 
 // Energies of the tile's rows, stored and (populations too large for the
@@ -143,8 +117,6 @@ __device__ __forceinline__ void tile_energies_real(const Inst &I, const TileIO &
 // moves, the first floor(N_S/2) sweeps (phase 1: through the copy map, no
 // energies) and later the remaining ones (phase 2: in place, with energies
 // and the measurement).
-__device__ __forceinline__ int phase_t0(const Inst &I, int phase) { return phase == 2 ? I.NS / 2 : 0; }
-__device__ __forceinline__ int phase_t1(const Inst &I, int phase) { return phase == 1 ? I.NS / 2 : I.NS; }
 
 // End of phase 1 in the last workgroup: the population now lives in the
 // buffer the tiles were written to.

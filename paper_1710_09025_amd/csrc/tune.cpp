@@ -1,10 +1,9 @@
 // tune.cpp -- sweep workgroup shapes chosen by measurement.
 //
-// How fast the sweep runs depends on how many replica rows one workgroup
-// holds (tile_rows) and, for the colour-major kernel, on how many replica
-// quads it sweeps at once: a small population needs small
-// tiles to spread over the 256 compute units, a large one amortises the tile
-// load, the energy epilogue and the measurement tail over more rows.  The
+// How fast the sweep runs depends on how many replicas share a word and how
+// many sets of them a workgroup holds: a small population needs few to spread
+// over the 256 compute units, a large one shares each block's fields and
+// tables among many.  The
 // tuner runs each candidate shape on a throw-away run of the instance (its
 // couplings, L, R, capacity and sweeps per step) at a constant beta = 2
 // after the beta = 0 start, where every replica gets one copy on average
@@ -48,8 +47,6 @@ constexpr double kTuneBeta = 2.0;   // inside the low-temperature part where an 
 constexpr int kMaxWord = 32;        // replicas per word
 
 bool is_rb(const HostInst &h) { return h.variant == kSweepRB; }
-// replicas as bits of a word, +-1 or real couplings
-bool is_words(const HostInst &h) { return is_rb(h) || is_rq(h.variant); }
 
 // Philox blocks of the largest colour.
 int max_blocks(const HostInst &h) { return layout_for(h.L, h.real != 0, h.dim).gmax; }
@@ -66,13 +63,6 @@ int64_t words_lds(const HostInst &h, int m, int sets)
 }
 int64_t words_max_lds(const HostInst &h) { return is_rb(h) ? kMaxLds : kMaxWordLds; }
 int words_cu_waves(const HostInst &h, bool small) { return !is_rb(h) ? 16 : !small ? 24 : h.ncol == 2 ? 12 : 8; }
-
-// Dynamic LDS of a sweep workgroup.
-int64_t sweep_lds(const HostInst &h)
-{
-    if (is_words(h)) return words_lds(h, h.mrep, h.sets);
-    return (int64_t)cm_slot_bytes(h.row_bytes, h.tpr, 4) * h.rp + 32 + 8 * (int64_t)h.tile_rows;
-}
 
 // A shape of words: m replicas per word, `sets` sets per pass, tile_rows rows
 // per workgroup.  rp, reported as group_replicas = 4 rp, is 0 where the caller
@@ -194,18 +184,37 @@ bool shape_valid(const HostInst &h, const char **why)
     const char *w = nullptr;
     if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
-    } else if (is_words(h)) {
+    } else {
         const int G = max_blocks(h);
         if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (is_rb(h) && rb_uniform(G) && h.sets != 1) ||
             words_threads(h, G, h.sets) > 1024)
             w = "no such grouping of replicas";
-    } else if (h.rp < 1 || (h.tpr <= 64 && (h.tpr * h.rp) % 64 != 0) || cm_launch_threads(h.tpr, h.rp) > 1024) {
-        w = "group_replicas must be a multiple of four giving at most 1024 threads (whole waves when a quad "
-            "takes at most 64)";
+        else if (words_lds(h, h.mrep, h.sets) > words_max_lds(h))
+            w = "the workgroup's tile does not fit in LDS";
     }
-    if (!w && sweep_lds(h) > (is_words(h) ? words_max_lds(h) : kMaxLds)) w = "the workgroup's tile does not fit in LDS";
     if (why) *why = w;
     return w == nullptr;
+}
+
+// Quads of a workgroup whose caller asks for none: 256 / tpr of at most 64
+// threads; above, the number of quads (of at most 512 threads together) that
+// leaves the fewest idle lanes in the last wave, the one nearest 256 threads
+// among equals.
+int cm_replicas_per_block(int tpr)
+{
+    if (tpr <= 64) return 256 / tpr;
+    int best = 1;
+    double best_use = 0.0;
+    for (int rp = 1; rp * tpr <= 512 || rp == 1; ++rp) {
+        const int nt = rp * tpr;
+        const double use = (double)nt / (double)cm_launch_threads(tpr, rp);
+        const bool nearer = std::abs(nt - 256) < std::abs(best * tpr - 256);
+        if (use > best_use + 1e-9 || (use > best_use - 1e-9 && nearer)) {
+            best = rp;
+            best_use = use;
+        }
+    }
+    return best;
 }
 
 // Sets of a workgroup of about `threads` threads: with +-1 couplings one where
@@ -239,8 +248,7 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 }
 
 // The shape used without tuning.
-//   Words: the sets and the replicas per word m that give the shortest launch
-// by what a colour step of a lane issues, about a instructions for its fields
+// The sets and the replicas per word m that give the shortest launch by what a colour step of a lane issues, about a instructions for its fields
 // and b per draw of four sites, at 4.45 cycles an instruction for each of the
 // waves that share a SIMD (6 or 8 for one, 9.3 for two; the small words of
 // sweep_rs.hip 6.3, 8.2 and 3.6 each).  Large words save fields,
@@ -248,78 +256,66 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 // measured; over 36 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
 // R = 5 10^4 and L = 32, R = 50 the shape chosen is within 10% of the best of
 // all that can be tried.
-//   Quads (real couplings, L > 13): enough workgroups to fill the chip when
-// the population is small, up to four passes per workgroup when it is large.
 void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
 {
-    if (is_words(h)) {
-        const int64_t most = *std::max_element(rows.begin(), rows.end());
-        double best = INFINITY;
-        int last = 0;
-        for (int threads : {64, 256, 512, 1024}) {
-            if (is_rb(h) && threads == 512) continue;
-            const int sets = words_sets(h, gmax, threads);
-            if (sets == last) continue;
-            last = sets;
-            const int nt = words_threads(h, gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
-            for (int m = 1; m <= kMaxWord; ++m) {
-                if (m > 4 && m * sets > most) break;
-                // (+-1 couplings: the table mode draws for four at a time)
-                if (is_rb(h) && m > 2 && m % 4 != 0) continue;
-                const bool small = is_rb(h) && rs_small(gmax, m, sets);
-                const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
-                // instructions of a lane's colour step: fields, and draws
-                // and decisions of four sites; tables, once a launch
-                double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
-                if (!is_rb(h)) {
-                    const bool thr = rq_kind(h.variant, m * sets) == kRQThr;
+    const int64_t most = *std::max_element(rows.begin(), rows.end());
+    double best = INFINITY;
+    int last = 0;
+    for (int threads : {64, 256, 512, 1024}) {
+        if (is_rb(h) && threads == 512) continue;
+        const int sets = words_sets(h, gmax, threads);
+        if (sets == last) continue;
+        last = sets;
+        const int nt = words_threads(h, gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
+        for (int m = 1; m <= kMaxWord; ++m) {
+            if (m > 4 && m * sets > most) break;
+            // (+-1 couplings: the table mode draws for four at a time)
+            if (is_rb(h) && m > 2 && m % 4 != 0) continue;
+            const bool small = is_rb(h) && rs_small(gmax, m, sets);
+            const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
+            // instructions of a lane's colour step: fields, and draws
+            // and decisions of four sites; tables, once a launch
+            double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
+            if (!is_rb(h)) {
+                const int kind = rq_kind(h.variant, m * sets);
+                if (kind == kRQBonds) {
+                    a = 180.0;
+                    b = 130.0;
+                } else {
                     a = m <= 4 ? 120.0 : 320.0;
-                    b = (thr ? 62.0 : 105.0) + (m <= 4 ? 48.0 : 0.0);
-                    once = (double)h.N / nt * (thr ? h.dim == 3 ? 1400.0 : 400.0 : 150.0) / (h.NS * h.ncol);
+                    b = (kind == kRQThr ? 62.0 : 105.0) + (m <= 4 ? 48.0 : 0.0);
                 }
-                const int64_t round = (int64_t)kCU * per_cu;
-                int64_t wgs = 0;
-                for (int64_t r : rows) wgs += (r + m * sets - 1) / (m * sets);
-                // cycles per instruction of a lane's colour step with n
-                // workgroups on the chip, from the waves that share a SIMD
-                auto cycles = [&](int64_t n) {
-                    const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
-                    if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
-                    return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
-                };
-                const double t = ((a + b * m) * blocks + once) *
-                                 ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
-                if (t < 0.98 * best) {
-                    best = t;
-                    set_rb(h, m, sets, m * sets);
-                }
+                once = (double)h.N / nt * (kind == kRQThr ? h.dim == 3 ? 1400.0 : 400.0 : 150.0) / (h.NS * h.ncol);
+            }
+            const int64_t round = (int64_t)kCU * per_cu;
+            int64_t wgs = 0;
+            for (int64_t r : rows) wgs += (r + m * sets - 1) / (m * sets);
+            // cycles per instruction of a lane's colour step with n
+            // workgroups on the chip, from the waves that share a SIMD
+            auto cycles = [&](int64_t n) {
+                const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
+                if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
+                return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
+            };
+            const double t = ((a + b * m) * blocks + once) *
+                             ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
+            if (t < 0.98 * best) {
+                best = t;
+                set_rb(h, m, sets, m * sets);
             }
         }
-        return;
     }
-    const int64_t target = 512;  // workgroups: two per compute unit
-    h.rp = cm_replicas_per_block(h.tpr);
-    const int64_t m = std::max<int64_t>(1, std::min<int64_t>(4, h.Rcap / (target * 4 * h.rp)));
-    h.tile_rows = (int)(m * 4 * h.rp);
 }
 
 // The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
-// For words the options keep the ranges documented for them: quads of
-// replicas in byte planes, tiles that fit the workgroup's LDS at one byte per
-// spin (and with +-1 couplings, L = 8 and 16, whole passes of 8 and 2 rows;
+// The options keep the ranges documented for them: quads of replicas in byte
+// planes, tiles that fit the workgroup's LDS at one byte per spin (and with +-1 couplings, L = 8 and 16, whole passes of 8 and 2 rows;
 // group_replicas is ignored there and where a lattice has no quads).  The
 // words of M replicas then take as many of the group's replicas as they can.
 // h holds the default shape on entry.
 bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why)
 {
     const char *w = nullptr;
-    if (!is_words(h)) {
-        const int rp = group_replicas > 0 ? group_replicas / 4 : h.rp;
-        // without an explicit tile: the default number of passes per workgroup
-        h.tile_rows = tile_rows > 0 ? tile_rows : h.tile_rows / h.rp * rp;
-        h.rp = rp;
-        return shape_valid(h, why);
-    }
     int group = 0;
     const int rb = h.row_bytes;
     if (is_rb(h) && (h.L == 8 || h.L == 16)) {
@@ -374,33 +370,15 @@ static std::vector<HostInst> shape_candidates(const HostInst &h)
     t.row_bytes = h.row_bytes;
     t.real = h.real;
     t.tpr = h.tpr;
-    if (is_words(h)) {
-        const int G = max_blocks(h);
-        int last = 0;
-        for (int threads : {64, 128, 256, 512, 1024}) {
-            const int sets = words_sets(h, G, threads);
-            if (sets == last) continue;
-            last = sets;
-            for (int m : kWords) {
-                set_rb(t, m, sets, m * sets);
-                if ((m == 1 || m * sets <= 2 * h.Rcap) && shape_valid(t, nullptr)) c.push_back(t);
-            }
-        }
-        return c;
-    }
-    // tile sizes between the powers of two matter: the number of tiles
-    // against the number of resident workgroups decides how full the last
-    // round of workgroups is
-    static const int kPasses[] = {1, 2, 3, 4, 6, 8};
-    // quads of up to 64 threads: groups of whole waves; wider quads: any
-    // count whose last wave is at least 80% used
-    for (int rp = 1; cm_launch_threads(h.tpr, rp) <= 1024; rp = h.tpr <= 64 ? 2 * rp : rp + 1) {
-        if (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) continue;
-        if (h.tpr > 64 && rp > 1 && 5 * h.tpr * rp < 4 * cm_launch_threads(h.tpr, rp)) continue;
-        for (int m : kPasses) {
-            t.tile_rows = 4 * m * rp;
-            t.rp = rp;
-            if (shape_valid(t, nullptr) && 4 * m * rp <= 2 * h.Rcap) c.push_back(t);
+    const int G = max_blocks(h);
+    int last = 0;
+    for (int threads : {64, 128, 256, 512, 1024}) {
+        const int sets = words_sets(h, G, threads);
+        if (sets == last) continue;
+        last = sets;
+        for (int m : kWords) {
+            set_rb(t, m, sets, m * sets);
+            if ((m == 1 || m * sets <= 2 * h.Rcap) && shape_valid(t, nullptr)) c.push_back(t);
         }
     }
     return c;

@@ -44,7 +44,11 @@ CASES = [
     ("real", 3, 8, 401, 6, 3, 20.0, dict(tile_rows=100, group_replicas=64)),
     ("real", 3, 9, 70, 5, 2, 6.0, dict(packed=True)),
     ("real", 3, 13, 40, 4, 2, 6.0, {}),
+    ("real", 3, 12, 40, 4, 2, 6.0, {}),
     ("real", 3, 14, 9, 4, 2, 6.0, {}),
+    ("real", 3, 16, 70, 4, 2, 20.0, dict(tile_rows=32, group_replicas=8, packed=True)),
+    ("real", 3, 20, 5, 3, 2, 6.0, {}),
+    ("real", 3, 21, 4, 3, 2, 6.0, {}),
     ("real", 2, 5, 500, 8, 3, 20.0, dict(tile_rows=6, group_replicas=64)),
     ("real", 2, 45, 60, 4, 2, 6.0, {}),
     ("real", 2, 46, 60, 4, 2, 6.0, {}),
