@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
+#include <set>
 
 namespace pamc {
 
@@ -714,8 +715,12 @@ int Runner::build_work(const std::vector<int> &active)
     std::map<std::tuple<int, int, int>, std::vector<int64_t>> pops;
     std::map<std::tuple<int, int, int>, HostInst> joint;
     auto lattice = [](const HostInst &h) { return std::make_tuple(h.icm > 0 ? 1 : 0, h.variant, h.L); };
-    for (int i : active)
+    std::set<std::tuple<int, int, int>> launches;
+    for (int i : active) {
         if (!inst_[i].own_shape) pops[lattice(inst_[i])].push_back(inst_[i].R);
+        launches.insert(lattice(inst_[i]));
+    }
+    const int beside = (int)std::min(launches.size(), aux_.size() + 1);
     for (int i : active) {
         HostInst &h = inst_[i];
         const uint32_t ii = (uint32_t)i;
@@ -732,7 +737,7 @@ int Runner::build_work(const std::vector<int> &active)
                 s.real = h.real;
                 s.tpr = h.tpr;
                 s.Rcap = h.Rcap;
-                default_shape(s, h.dev.gmax, pops[lattice(h)]);
+                default_shape(s, h.dev.gmax, pops[lattice(h)], beside);
             }
             h.tile_rows = s.tile_rows;
             h.rp = s.rp;

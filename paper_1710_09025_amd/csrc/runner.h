@@ -65,8 +65,8 @@ inline void take_shape(HostInst &h, const HostInst &from)
 }
 
 // Sweep workgroup shape for instances of h's lattice with these populations
-// swept as one launch (tune.cpp).
-void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows);
+// swept as one launch, `beside` launches at once (tune.cpp).
+void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows, int beside = 1);
 
 struct Allocator {
     void *(*alloc)(size_t, void *) = nullptr;

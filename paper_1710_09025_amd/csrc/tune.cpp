@@ -248,6 +248,10 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 }
 
 // The shape used without tuning.
+// Launches beside others (a batch of several lattices) also count the issue
+// time they take of the chip, at 0.3 of it: nine instances of L = 4 ... 11 with
+// 3528 rows each ran 59 ms with every launch the shortest by itself, 51 so, 59
+// with all of it; real couplings gain nothing from it.
 // The sets and the replicas per word m that give the shortest launch by what a colour step of a lane issues, about a instructions for its fields
 // and b per draw of four sites, at 4.45 cycles an instruction for each of the
 // waves that share a SIMD (6 or 8 for one, 9.3 for two; the small words of
@@ -256,7 +260,7 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 // measured; over 36 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
 // R = 5 10^4 and L = 32, R = 50 the shape chosen is within 10% of the best of
 // all that can be tried.
-void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
+void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows, int beside)
 {
     const int64_t most = *std::max_element(rows.begin(), rows.end());
     double best = INFINITY;
@@ -297,8 +301,10 @@ void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows)
                 if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
                 return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
             };
-            const double t = ((a + b * m) * blocks + once) *
-                             ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
+            const double step = (a + b * m) * blocks + once;
+            double t = step * ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
+            if (is_rb(h) && beside > 1)
+                t = t / beside + 0.3 * step * 4.45 * (double)(wgs * (nt / 64)) / (4.0 * kCU);
             if (t < 0.98 * best) {
                 best = t;
                 set_rb(h, m, sets, m * sets);
