@@ -75,7 +75,8 @@ ALU_OPS_PER_ATTEMPT_REAL = 47.5
 
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "sweep_counters.json")
 SWEEP_SOURCES = [os.path.join(ROOT, "paper_1710_09025_amd", "csrc", f)
-                 for f in ("sweep.hip", "step_common.h", "pamc_dev.h")]
+                 for f in ("sweep_rb.hip", "sweep_rs.hip", "sweep_rq.hip", "rb_common.h", "tile_io.h",
+                           "step_common.h", "pamc_dev.h")]
 
 
 def log(msg: str):
@@ -227,10 +228,8 @@ def gather_bench(name, n_steps, packed=False):
             "sweep_ms_per_step": round(sweep_ms / nsteps, 4)}
 
 
-def sweep_kernel_name(L, real):
-    if real:
-        return f"k_sweep_cq<{2 if L % 2 == 0 else 3}, 512>"
-    return f"k_sweep_eo<{L}>" if L in (8, 16) else "k_sweep_cm / k_sweep_lex"
+def sweep_kernel_name(real):
+    return "k_sweep_rq" if real else "k_sweep_rb"
 
 
 def roofline(res, calib=None):
@@ -256,7 +255,7 @@ def roofline(res, calib=None):
     alg_bytes = 2.0 * res["mean_R"] * rb + (20.0 if real else 16.0) * res["mean_R"]
     out = {"bound": "alu", "achieved": round(achieved, 3), "peak": round(ALU_PEAK_TOPS, 3),
             "unit": "Tops/s (int32 VALU)", "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": traffic,
-            "kernel": sweep_kernel_name(res["cfg"]["L"], real) + " (N_S sweeps of every replica at one temperature)",
+            "kernel": sweep_kernel_name(real) + " (N_S sweeps of every replica at one temperature)",
             "ops_per_attempt": opa,
             "sweep_shape": {"tile_rows": res["shape"][0], "group_replicas": res["shape"][1]},
             "avg_launch_ms": round(res["sweep_ms"] / max(1, res["nsteps"]), 4),

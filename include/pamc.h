@@ -95,15 +95,17 @@ typedef struct pamc_options {
     int timing;              /* 1: record HIP events around the sweep and the
                                 resampling kernels of every step (see
                                 pamc_phase_times); 0 (default): no events   */
-    int group_replicas;      /* L other than 8 and 16 (colour-major sweep):
-                                replicas one sweep workgroup holds at once,
-                                a multiple of four (they are swept in
-                                fours); 0 = the library's choice.  A quad
-                                takes one thread per Philox block of the
-                                largest colour (a power of two up to 64);
-                                the workgroup, rounded up to whole 64-lane
-                                waves, has at most 1024 threads, and quads
-                                of at most 64 threads must fill its waves  */
+    int group_replicas;      /* L other than 8 and 16 (to L = 20, odd L to
+                                21): replicas one sweep workgroup holds at
+                                once, a multiple of four; 0 = the library's
+                                choice.  Limits, counted in fours of one
+                                thread per Philox block of the largest
+                                colour (a power of two up to 64): all fours
+                                together, rounded up to whole 64-lane waves,
+                                at most 1024 threads, and fours of at most
+                                64 threads must fill their waves.  The
+                                library sweeps the replicas in words of up
+                                to 32                                      */
     int autotune;            /* 1: when tile_rows and group_replicas are 0,
                                 pick them by timing the candidate shapes on
                                 a throw-away run first (see pamc_autotune);
@@ -191,7 +193,7 @@ int pamc_create(int L, const int8_t *couplings, int64_t R, const double *beta, i
  *   couplings  int32 [D][N], J = couplings[d*N + s] * 2^-20 with
  *              |couplings| < 2^23 (|J| < 8), same bond order as pamc_create
  *              (D = opt->dim: [3][L^3], or [2][L^2] on the square lattice);
- *   L          3D: even L <= 20 or odd L <= 21 (the colour-major sweep);
+ *   L          3D: even L <= 20 or odd L <= 21;
  *              2D: 2 <= L <= 64;
  *   capacity   at most 2^29, and times the sum of |couplings| below 2^62.
  * Energies are exact integers in units of 2^-20 (the E_min, E_max, sum_E,
