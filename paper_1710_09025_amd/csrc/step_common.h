@@ -233,6 +233,16 @@ __device__ __forceinline__ bool real_accept(float bq, int32_t dE, uint32_t u)
     return x >= -23.0f && (e >= 1.0f || u < T);
 }
 
+// threadIdx.x for the end of a sweep workgroup, opaque: lane masks and
+// addresses that follow from it are made there, not hoisted before the sweeps
+// and spilled for them.
+__device__ __forceinline__ int late_thread()
+{
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // Adds one count per valid lane to arr[idx]: at low temperature most replicas
 // share a few energies, and per-lane atomics on one address would serialise,
 // so the first kShared distinct indices found in the wave get one atomic
@@ -243,7 +253,7 @@ __device__ __forceinline__ bool real_accept(float bq, int32_t dE, uint32_t u)
 __device__ __forceinline__ void count_wave(uint32_t *arr, uint32_t idx, bool valid)
 {
     constexpr int kShared = 64;
-    const int lane = threadIdx.x & 63;
+    const int lane = late_thread() & 63;
     uint64_t pending = __ballot(valid);
     for (int i = 0; i < kShared && pending; ++i) {
         const int leader = __builtin_ctzll(pending);
@@ -259,8 +269,8 @@ __device__ __forceinline__ void count_wave(uint32_t *arr, uint32_t idx, bool val
 // per run, all in one instruction.
 __device__ __forceinline__ void count_runs(uint32_t *arr, uint32_t idx, bool valid)
 {
-    const int lane = threadIdx.x & 63;
-    const uint32_t left = __shfl_up(idx, 1);
+    const int lane = late_thread() & 63;
+    const uint32_t left = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (lane - 1), (int)idx);
     const uint64_t on = __ballot(valid);
     const bool head = valid && (lane == 0 || !((on >> (lane - 1)) & 1u) || left != idx);
     // a run ends at the next head or the next lane without a row

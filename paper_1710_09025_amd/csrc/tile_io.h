@@ -48,13 +48,17 @@ __device__ __forceinline__ TileIO tile_io(const Inst &I)
     io.packed = I.packed;
     io.srow = I.srow_bytes;
     const int cur = *I.cur, mapped = *I.mapped, out = cur ^ mapped;
-    io.src = cur ? s1 : s0;
-    io.dst = out ? s1 : s0;
-    io.map = mapped ? map : nullptr;
-    io.fsrc = cur ? f1 : f0;
-    io.fdst = mapped ? (out ? f1 : f0) : nullptr;
-    io.Edst = out ? e1 : e0;
-    io.Eqdst = out ? q1 : q0;
+    // (uniform, but the compiler cannot know: as lane values the pointers were
+    // spilled to memory for the sweeps.  With late_thread at the workgroup's
+    // end 20 bytes a thread instead of 76, 0.5 GB a launch at L = 16,
+    // R = 5 10^5; L = 8, R = 10^5, 201 temperatures 47.1 -> 46.3 ms)
+    io.src = scalar_ptr(cur ? s1 : s0);
+    io.dst = scalar_ptr(out ? s1 : s0);
+    io.map = scalar_ptr(mapped ? map : nullptr);
+    io.fsrc = scalar_ptr(cur ? f1 : f0);
+    io.fdst = scalar_ptr(mapped ? (out ? f1 : f0) : nullptr);
+    io.Edst = scalar_ptr(out ? e1 : e0);
+    io.Eqdst = scalar_ptr(out ? q1 : q0);
     return io;
 }
 
@@ -67,7 +71,7 @@ __device__ __forceinline__ void tile_energy_out(const Inst &I, const TileIO &io,
     const int copies = I.hist_copies;
     uint32_t *hist = copies > 0 ? hist_copy(I, (int)blockIdx.x % copies) : nullptr;
     for (int base = 0; base < nrows; base += blockDim.x) {
-        const int q = base + (int)threadIdx.x;
+        const int q = base + late_thread();
         const bool valid = q < nrows;
         int E = 0;
         if (valid) {
@@ -85,7 +89,7 @@ __device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t 
 {
     if (I.Rcap <= kDirectRows) return;
     for (int base = 0; base < nrows; base += blockDim.x) {
-        const int q = base + (int)threadIdx.x;
+        const int q = base + late_thread();
         const bool valid = q < nrows;
         count_runs(I.cnt, valid ? fam[q] : 0u, valid);
     }
@@ -98,8 +102,9 @@ __device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t 
 __device__ __forceinline__ void tile_energies_real(const Inst &I, const TileIO &io, const unsigned long long *eacc,
                                                    int r0, int nrows, long long base)
 {
-    for (int q0 = (int)(threadIdx.x & ~63u); q0 < nrows; q0 += blockDim.x) {
-        const int q = q0 + (int)(threadIdx.x & 63u);
+    const int t = late_thread();
+    for (int q0 = scalar(t & ~63); q0 < nrows; q0 += blockDim.x) {
+        const int q = q0 + (t & 63);
         long long e = kNoEnergy;
         if (q < nrows) {
             e = (long long)eacc[q] - base;
