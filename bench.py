@@ -61,7 +61,8 @@ HBM_PEAK_GBS = 8000.0
 #   acceptance: 4 x (threshold index + compare + select into the flip mask)
 #     + downhill mask (add, shift, and) + 2 merges of the partial masks = 17;
 #   the flip applied to the word: 1;
-# 63 / 4 = 15.75.  The compiled kernels issue 16.5 lane instructions per
+# 63 / 4 = 15.75, counted one replica at a time.  The compiled kernel, whose
+# field words serve up to 32 replicas, issues 11.8 lane instructions per
 # attempt (profiles/sweep_L16_R500000_valu_counters.md).
 ALU_OPS_PER_ATTEMPT = 15.75
 # The same with real (Gaussian, fixed-point) couplings, per attempt: Philox
