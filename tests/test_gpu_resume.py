@@ -1,0 +1,59 @@
+"""Overlaps of runs whose population passed through the host: read half-way
+and annealed on in the same handle, and taken into a fresh one.  Bit-packed
+rows keep their padding bits equal in every replica, whatever the buffers held
+in between: every histogram and moment equals that of an uninterrupted run
+with a byte per spin, which equals the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+import pamc_inputs as pi
+from parity import THREADS, compare_run
+
+pytestmark = pytest.mark.gpu
+
+Q_KEYS = ("q_abs", "q2", "q4", "g_SG")
+
+
+def make(model, dim, L, R, beta, **kw):
+    from paper_1710_09025_amd import Pamc
+
+    J = pi.pm_j_couplings(L, 300 + L) if model == "pm" else pi.gaussian_couplings(L, 300 + L, dim=dim)
+    return Pamc(L, J, R, beta, 3, 400 + L, overlap_steps=list(range(len(beta))), **kw), J
+
+
+def same_overlaps(got, want, steps, what):
+    go, wo = got.observables(), want.observables()
+    for k in steps:
+        np.testing.assert_array_equal(got.overlap_hist(k), want.overlap_hist(k), err_msg=f"{what}: step {k}")
+    for key in Q_KEYS + ("sum_E", "R"):
+        np.testing.assert_array_equal(go[key][steps], wo[key][steps], err_msg=f"{what}: {key}")
+
+
+# rows whose last stored word(s) hold no site, with words of many replicas and
+# of few, one set a workgroup and several; a row without such words (L = 8)
+@pytest.mark.parametrize("model,dim,L,R,opts", [
+    ("pm", 3, 6, 40_000, {}), ("pm", 3, 6, 50, {}), ("pm", 3, 8, 200, {}),
+    ("pm", 3, 12, 300, dict(tile_rows=32, group_replicas=16)), ("pm", 3, 13, 200, dict(tile_rows=32, group_replicas=16)),
+    ("pm", 3, 18, 40, {}), ("pm", 3, 23, 20, {}),
+    ("real", 3, 5, 400, {}), ("real", 3, 9, 150, {}), ("real", 3, 14, 30, {}),
+    ("real", 2, 10, 300, {}), ("real", 2, 47, 40, {}),
+])
+def test_packed_overlaps_after_a_stored_state(model, dim, L, R, opts):
+    beta, half = pi.linear_beta(4.0, 9), 4
+    what = f"{model} {dim}D L={L} R={R}"
+    plain, J = make(model, dim, L, R, beta)
+    assert plain.anneal() == 0
+    if R <= 1000:
+        o = oracle.Oracle(L, J, R, beta, 3, 400 + L, overlap_steps=list(range(len(beta))), threads=THREADS)
+        assert o.run() == 0
+        compare_run(plain.observables(), plain.step_sums(), o, what=what)
+    went_on, _ = make(model, dim, L, R, beta, packed=True, **opts)
+    assert went_on.anneal(half) == 0
+    st = went_on.get_state()
+    assert went_on.anneal() == 0
+    same_overlaps(went_on, plain, list(range(len(beta))), what + " read half-way")
+    resumed, _ = make(model, dim, L, R, beta, packed=True, **opts)
+    resumed.set_state(st["step"], st["spins"], st["family"], st["lnZ"])
+    assert resumed.anneal() == 0
+    same_overlaps(resumed, plain, list(range(half, len(beta))), what + " resumed")
