@@ -282,7 +282,8 @@ int pamc_get_state(pamc_ctx *ctx, pamc_state *st);
 
 /* Replaces the population (checkpoint resume, step-wise checks): step in
  * [0, n_temps), 1 <= R <= capacity, spins +-1, family < R (nominal).
- * Energies are recomputed from the spins; st->E is ignored. */
+ * Energies are recomputed from the spins; st->E is ignored.  Overlap
+ * histograms of steps from st->step on start at zero again. */
 int pamc_set_state(pamc_ctx *ctx, const pamc_state *st);
 
 /* Metropolis thresholds of every step: out[k][0..2] for dE = 4, 8, 12,

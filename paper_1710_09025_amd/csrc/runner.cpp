@@ -1323,6 +1323,12 @@ int Runner::set_state(int i, const pamc_state *st)
         HIPCHK(hipMemset(h.dev.hist, 0, (size_t)h.dev.nlev * 4), "clear the histogram");
         HIPCHK(hipMemset(h.dev.loff, 0, (size_t)h.Rcap * 4), "clear the histogram");
     }
+    // overlaps of the steps that run again are counted anew (slots follow the
+    // order in which the steps were asked for)
+    const size_t bins = 2 * (size_t)h.N + 1;
+    for (int k = st->step; k < h.nT; ++k)
+        if (h.ovl_slot[k] >= 0)
+            HIPCHK(hipMemset(h.dev.qhist + (size_t)h.ovl_slot[k] * bins, 0, bins * 4), "clear the overlaps");
     // energies from the spins (Eq. (1)) for the imported rows
     std::vector<Work> rows;
     for (int64_t r = 0; r < R; r += kRowsPerBlock) rows.push_back(Work{(uint32_t)i, (uint32_t)r, 0u, 0u});

@@ -57,3 +57,27 @@ def test_packed_overlaps_after_a_stored_state(model, dim, L, R, opts):
     resumed.set_state(st["step"], st["spins"], st["family"], st["lnZ"])
     assert resumed.anneal() == 0
     same_overlaps(resumed, plain, list(range(half, len(beta))), what + " resumed")
+
+
+@pytest.mark.parametrize("model,dim,L,R", [("pm", 3, 4, 300), ("real", 2, 12, 100), ("pm", 3, 17, 12)])
+def test_overlaps_of_steps_that_run_again_are_counted_anew(model, dim, L, R):
+    """A state taken back into a finished run: the steps after it have the
+    histograms of the first pass, not the sum of both; those before it keep
+    theirs."""
+    from paper_1710_09025_amd import Pamc
+
+    beta, half = pi.linear_beta(4.0, 9), 4
+    J = pi.pm_j_couplings(L, 300 + L) if model == "pm" else pi.gaussian_couplings(L, 300 + L, dim=dim)
+    steps = [8, 1, 4, 3, 6, 5]  # in no order
+    p = Pamc(L, J, R, beta, 3, 400 + L, overlap_steps=steps)
+    assert p.anneal(half) == 0
+    st = p.get_state()
+    assert p.anneal() == 0
+    first, obs = {k: p.overlap_hist(k) for k in steps}, p.observables()
+    p.set_state(st["step"], st["spins"], st["family"], st["lnZ"])
+    assert p.anneal() == 0
+    for k in steps:
+        np.testing.assert_array_equal(p.overlap_hist(k), first[k], err_msg=f"step {k}")
+    again = p.observables()
+    for key in Q_KEYS:
+        np.testing.assert_array_equal(again[key][half:], obs[key][half:], err_msg=key)
