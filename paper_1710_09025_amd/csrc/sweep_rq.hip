@@ -59,6 +59,7 @@ typedef __attribute__((address_space(1))) const int32_t *GlobalInt;
 struct RQInst {
     GlobalInt J;  // [ncol][gmax][24], [direction][site]
     float bq;     // beta 2^-20
+    float scale;  // -2 log2(e) bq, finite (see kNear)
 };
 __device__ __forceinline__ int32_t coupling(const RBInst &X, const RQInst &Q, int c, int g, int d, int i)
 {
@@ -270,7 +271,10 @@ __device__ __forceinline__ int32_t field_of(const uint32_t *t, const uint32_t *t
 // recipe's argument, two roundings of at most 23 / ln 2 = 33 (4e-6), its
 // result, four ulps (7e-7), and the floor, which moves the boundary by less
 // than one draw, exact in u + 1.  Together below 2e-5; closer pairs than
-// kNear are decided by the recipe.
+// kNear are decided by the recipe.  The factor of h is held finite: from
+// beta = 1.2e44 on it would be infinite, and its product with h = 0 (dE = 0,
+// always accepted) not a number; any other h puts y beyond every draw either
+// way.
 constexpr float kNear = 4.0e-5f;
 
 // One colour step of block g for the m replicas from row rb on (see rb_block).
@@ -300,7 +304,6 @@ __device__ __forceinline__ void rq_block(const RBInst &X, const RQInst &Q, uint3
         // the next block's record is on its way while this one draws
         rec = load_record(X, next_c, next_g);
         const LaneDraw d = lane_draw(ctr, k, t, k0, k1);
-        const float scale = -2.0f * 1.44269504f * Q.bq;
         const uint32_t *tab[4], *tab2[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -329,7 +332,7 @@ __device__ __forceinline__ void rq_block(const RBInst &X, const RQInst &Q, uint3
                 float diff[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float y = __builtin_fmaf((float)(int32_t)e[i], scale, 32.0f);
+                    const float y = __builtin_fmaf((float)(int32_t)e[i], Q.scale, 32.0f);
                     diff[i] = y - __builtin_amdgcn_logf((float)word_of(u, i) + 1.0f);
                     push_positive(a[i], diff[i]);
                 }
@@ -521,6 +524,7 @@ __device__ __forceinline__ void rq_tile(const Inst &I, int k, uint32_t *table, i
     RQInst Q;
     Q.J = (GlobalInt)scalar_ptr(I.cmj);
     Q.bq = __uint_as_float(scalar(__float_as_uint(I.bq[k])));
+    Q.scale = __uint_as_float(scalar(__float_as_uint(__builtin_fmaxf(-2.0f * 1.44269504f * Q.bq, -3.0e38f))));
     const bool all = scalar(I.thr[k].w) != 0u;
     const int ns = scalar(I.NS), t0 = phase == 2 ? ns / 2 : 0, t1 = phase == 1 ? ns / 2 : ns;
     uint32_t *lds = table + 4 * X.plane * words;

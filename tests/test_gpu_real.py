@@ -242,3 +242,19 @@ def test_single_temperature_and_single_replica():
         assert st == sto == 0
         compare_state(p.get_state(), o.get_state(), f"real L={L} R={R}")
         compare_run(p.observables(), p.step_sums(), o, what=f"real L={L} R={R}")
+
+
+# decisions from thresholds, from bond sums and from couplings, on both lattices
+@pytest.mark.parametrize("dim,L,R", [(3, 4, 200), (3, 9, 60), (3, 13, 30), (2, 12, 200), (2, 46, 30)])
+def test_quench_at_betas_whose_exponents_overflow(dim, L, R):
+    """beta up to the largest whose binary32 scale is finite, and beyond: moves
+    with dE = 0 (common with couplings +-1) are accepted, dE > 0 never."""
+    from paper_1710_09025_amd import Pamc
+
+    J = np.where(np.random.default_rng(L).random((dim, L ** dim)) < 0.5, -(2 ** 20), 2 ** 20).astype(np.int32)
+    beta = np.array([0.0, 0.7, 1e43, 2e44, 3e44, 1e46])
+    p = Pamc(L, J, R, beta, 3, 900 + L)
+    o = oracle.Oracle(L, J, R, beta, 3, 900 + L, threads=THREADS)
+    assert p.anneal() == o.run() == 0
+    compare_state(p.get_state(), o.get_state(), f"{dim}D L={L}")
+    np.testing.assert_array_equal(p.observables()["sum_E"], o.records()["sumE"])
