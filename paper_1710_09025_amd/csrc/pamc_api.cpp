@@ -33,7 +33,7 @@ namespace pamc {
 int make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const double *beta, int nT, int NS,
               uint64_t seed, const pamc_options &opt, HostInst &h);
 bool shape_valid(const HostInst &h, const char **why);
-bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why);
+bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char **why);
 int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt);
 }
 
@@ -110,6 +110,7 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
     h.N = N;
     h.ncol = li.ncol;
     h.variant = li.variant;
+    h.gmax = li.gmax;
     h.row_bytes = li.row_bytes;
     h.packed = opt.spin_format == PAMC_SPINS_PACKED ? 1 : 0;
     h.srow_bytes = pamc::stored_row_bytes(li.row_bytes, h.packed != 0);
@@ -142,7 +143,7 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
         h.ovl_slot[nT - 1] = h.ovl_n++;
     }
     // sweep workgroup shape: explicit, tuned by measurement, or the default
-    pamc::default_shape(h, li.gmax, {R});
+    pamc::default_shape(h, {R});
     if (opt.tile_rows < 0 || opt.tile_rows > 4096) return invalid("tile_rows out of range");
     if (opt.group_replicas < 0 || opt.group_replicas > 1024) return invalid("group_replicas out of range");
     // lattices whose sweep takes replicas in fours honour group_replicas
@@ -150,7 +151,7 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
     if (opt.tile_rows > 0 || (quads && opt.group_replicas > 0)) {
         if (quads && opt.group_replicas % 4) return invalid("group_replicas must be a multiple of four for this lattice");
         const char *why = nullptr;
-        if (!pamc::explicit_shape(h, li.gmax, opt.tile_rows, opt.group_replicas, &why)) return invalid(why);
+        if (!pamc::explicit_shape(h, opt.tile_rows, opt.group_replicas, &why)) return invalid(why);
         h.own_shape = true;
     } else if (opt.autotune) {
         const int st = pamc::tune_shape(h, opt, nullptr);

@@ -733,11 +733,12 @@ int Runner::build_work(const std::vector<int> &active)
                 s.NS = h.NS;
                 s.ncol = h.ncol;
                 s.variant = h.variant;
+                s.gmax = h.gmax;
                 s.row_bytes = h.row_bytes;
                 s.real = h.real;
                 s.tpr = h.tpr;
                 s.Rcap = h.Rcap;
-                default_shape(s, h.dev.gmax, pops[lattice(h)], beside);
+                default_shape(s, pops[lattice(h)], beside);
             }
             h.tile_rows = s.tile_rows;
             h.rp = s.rp;

@@ -22,6 +22,7 @@ namespace pamc {
 struct HostInst {
     int dim = 3;                       // lattice dimension (2 or 3), N = L^dim
     int L = 0, N = 0, ncol = 0, variant = 0;
+    int gmax = 0;                      // Philox blocks of the largest colour
     int row_bytes = 0, tile_rows = 0;
     int packed = 0;                    // spins stored one bit per position
     int real = 0;                      // real couplings in fixed point (Jq)
@@ -66,7 +67,7 @@ inline void take_shape(HostInst &h, const HostInst &from)
 
 // Sweep workgroup shape for instances of h's lattice with these populations
 // swept as one launch, `beside` launches at once (tune.cpp).
-void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows, int beside = 1);
+void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside = 1);
 
 struct Allocator {
     void *(*alloc)(size_t, void *) = nullptr;

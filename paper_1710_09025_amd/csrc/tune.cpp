@@ -48,18 +48,14 @@ constexpr int kMaxWord = 32;        // replicas per word
 
 bool is_rb(const HostInst &h) { return h.variant == kSweepRB; }
 
-// Philox blocks of the largest colour.
-int max_blocks(const HostInst &h) { return layout_for(h.L, h.real != 0, h.dim).gmax; }
-
 // The word kernels' launch: threads and LDS of a workgroup of `sets` sets, the
 // waves a compute unit holds (80 to 188 registers a lane).
-bool words_uniform(const HostInst &h, int G) { return is_rb(h) ? rb_uniform(G) : rq_uniform(G); }
-int words_threads(const HostInst &h, int G, int sets) { return is_rb(h) ? rb_threads(G, sets) : rq_threads(G, sets); }
+int words_threads(const HostInst &h, int sets) { return is_rb(h) ? rb_threads(h.gmax, sets) : rq_threads(h.gmax, sets); }
 int64_t words_lds(const HostInst &h, int m, int sets)
 {
-    const int plane = rb_plane(h.row_bytes), G = max_blocks(h);
+    const int plane = rb_plane(h.row_bytes);
     if (!is_rb(h)) return rq_lds(h.variant, plane, m, sets);
-    return (int64_t)(rs_small(G, m, sets) ? rs_lds(plane, G, sets) : rb_lds(plane, sets));
+    return (int64_t)(rs_small(h.gmax, m, sets) ? rs_lds(plane, h.gmax, sets) : rb_lds(plane, sets));
 }
 int64_t words_max_lds(const HostInst &h) { return is_rb(h) ? kMaxLds : kMaxWordLds; }
 int words_cu_waves(const HostInst &h, bool small) { return !is_rb(h) ? 16 : !small ? 24 : h.ncol == 2 ? 12 : 8; }
@@ -185,9 +181,8 @@ bool shape_valid(const HostInst &h, const char **why)
     if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
     } else {
-        const int G = max_blocks(h);
-        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (is_rb(h) && rb_uniform(G) && h.sets != 1) ||
-            words_threads(h, G, h.sets) > 1024)
+        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (is_rb(h) && rb_uniform(h.gmax) && h.sets != 1) ||
+            words_threads(h, h.sets) > 1024)
             w = "no such grouping of replicas";
         else if (words_lds(h, h.mrep, h.sets) > words_max_lds(h))
             w = "the workgroup's tile does not fit in LDS";
@@ -220,14 +215,14 @@ int cm_replicas_per_block(int tpr)
 // Sets of a workgroup of about `threads` threads: with +-1 couplings one where
 // a set fills whole waves; else the count up to that size (at least one) with
 // the fewest idle lanes.
-static int words_sets(const HostInst &h, int G, int threads)
+static int words_sets(const HostInst &h, int threads)
 {
     int best = 1;
     double best_use = 0.0;
-    if (is_rb(h) && rb_uniform(G)) return 1;
-    for (int s = 1; words_threads(h, G, s) <= std::min(1024, std::max(threads, words_threads(h, G, 1))); ++s) {
+    if (is_rb(h) && rb_uniform(h.gmax)) return 1;
+    for (int s = 1; words_threads(h, s) <= std::min(1024, std::max(threads, words_threads(h, 1))); ++s) {
         if (words_lds(h, kMaxWord, s) > words_max_lds(h)) break;
-        const double use = (double)G * s / words_threads(h, G, s);
+        const double use = (double)h.gmax * s / words_threads(h, s);
         if (use >= best_use - 0.005) {
             best = s;
             best_use = std::max(use, best_use);
@@ -260,22 +255,22 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
 // measured; over 36 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
 // R = 5 10^4 and L = 32, R = 50 the shape chosen is within 10% of the best of
 // all that can be tried.
-void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows, int beside)
+void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
 {
     const int64_t most = *std::max_element(rows.begin(), rows.end());
     double best = INFINITY;
     int last = 0;
     for (int threads : {64, 256, 512, 1024}) {
         if (is_rb(h) && threads == 512) continue;
-        const int sets = words_sets(h, gmax, threads);
+        const int sets = words_sets(h, threads);
         if (sets == last) continue;
         last = sets;
-        const int nt = words_threads(h, gmax, sets), blocks = std::max(1, (gmax + nt - 1) / nt);
+        const int nt = words_threads(h, sets), blocks = std::max(1, (h.gmax + nt - 1) / nt);
         for (int m = 1; m <= kMaxWord; ++m) {
             if (m > 4 && m * sets > most) break;
             // (+-1 couplings: the table mode draws for four at a time)
             if (is_rb(h) && m > 2 && m % 4 != 0) continue;
-            const bool small = is_rb(h) && rs_small(gmax, m, sets);
+            const bool small = is_rb(h) && rs_small(h.gmax, m, sets);
             const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
             // instructions of a lane's colour step: fields, and draws
             // and decisions of four sites; tables, once a launch
@@ -319,7 +314,7 @@ void default_shape(HostInst &h, int gmax, const std::vector<int64_t> &rows, int 
 // group_replicas is ignored there and where a lattice has no quads).  The
 // words of M replicas then take as many of the group's replicas as they can.
 // h holds the default shape on entry.
-bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, const char **why)
+bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char **why)
 {
     const char *w = nullptr;
     int group = 0;
@@ -357,7 +352,7 @@ bool explicit_shape(HostInst &h, int gmax, int tile_rows, int group_replicas, co
     if (w) return false;
     const int rows = group > 0 ? std::min(group, tile_rows) : tile_rows;
     const int m = std::min(rows, kMaxWord);
-    set_rb(h, m, std::max(1, std::min(words_sets(h, gmax, is_rb(h) ? 256 : 1024), rows / m)), tile_rows);
+    set_rb(h, m, std::max(1, std::min(words_sets(h, is_rb(h) ? 256 : 1024), rows / m)), tile_rows);
     return shape_valid(h, why);
 }
 
@@ -373,13 +368,13 @@ static std::vector<HostInst> shape_candidates(const HostInst &h)
     t.L = h.L;
     t.N = h.N;
     t.variant = h.variant;
+    t.gmax = h.gmax;
     t.row_bytes = h.row_bytes;
     t.real = h.real;
     t.tpr = h.tpr;
-    const int G = max_blocks(h);
     int last = 0;
     for (int threads : {64, 128, 256, 512, 1024}) {
-        const int sets = words_sets(h, G, threads);
+        const int sets = words_sets(h, threads);
         if (sets == last) continue;
         last = sets;
         for (int m : kWords) {
@@ -404,6 +399,7 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
             t.dim = h.dim;
             t.L = h.L;
             t.variant = h.variant;
+            t.gmax = h.gmax;
             t.row_bytes = h.row_bytes;
             t.real = h.real;
             t.tpr = h.tpr;

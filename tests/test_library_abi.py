@@ -2,6 +2,7 @@
 include/pamc.h; host-side argument validation returns the documented status
 codes before any device work (no GPU needed)."""
 import ctypes
+import math
 import os
 import re
 import subprocess
@@ -410,3 +411,38 @@ def test_static_entry_refuses_oversize_runs_on_the_host(lib):
     # invalid arguments are refused the same way
     assert lib.pamc_anneal_static(L, None, R, beta.ctypes.data_as(ctypes.c_void_p), 11, 2, 1, None, obs,
                                   None) == _capi.ERR_INVALID
+
+
+@pytest.mark.parametrize("L,real", [(32, False), (20, True)])
+def test_choosing_a_sweep_shape_costs_little_beside_the_layout(lib, L, real):
+    """Host work of a creation up to the sweep shape (a refused tile_rows ends
+    it there): a few times that of laying the lattice out once, which
+    pamc_footprint does, and not that for every shape considered."""
+    import time
+
+    from paper_1710_09025_amd import _capi
+
+    J = np.ones((3, L ** 3), dtype=np.int32 if real else np.int8)
+    beta = np.array([0.0, 1.0])
+    opt = _capi.Options()
+    lib.pamc_default_options(ctypes.byref(opt))
+    opt.tile_rows, opt.real_couplings = -1, int(real)
+    h = ctypes.c_void_p()
+    create = lib.pamc_create_real if real else lib.pamc_create
+
+    def refused():
+        assert create(L, J.ctypes.data, 20_000, beta.ctypes.data, 2, 10, 1, ctypes.byref(opt),
+                      ctypes.byref(h)) == _capi.ERR_INVALID
+
+    def layout():
+        assert lib.pamc_footprint(L, 20_000, 2, ctypes.byref(opt)) > 0
+
+    def fastest(f):
+        best = math.inf
+        for _ in range(50):
+            t = time.perf_counter()
+            f()
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    assert fastest(refused) < 6 * fastest(layout)
