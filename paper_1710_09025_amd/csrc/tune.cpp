@@ -242,19 +242,68 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
     return std::max<int>(1, (int)std::min<int64_t>(n, 160 * 1024 / (lds + 512)));
 }
 
-// The shape used without tuning.
-// Launches beside others (a batch of several lattices) also count the issue
-// time they take of the chip, at 0.3 of it: nine instances of L = 4 ... 11 with
-// 3528 rows each ran 59 ms with every launch the shortest by itself, 51 so, 59
-// with all of it; real couplings gain nothing from it.
-// The sets and the replicas per word m that give the shortest launch by what a colour step of a lane issues, about a instructions for its fields
-// and b per draw of four sites, at 4.45 cycles an instruction for each of the
-// waves that share a SIMD (6 or 8 for one, 9.3 for two; the small words of
-// sweep_rs.hip 6.3, 8.2 and 3.6 each).  Large words save fields,
+// Predicted time (cycles of a SIMD a colour step) of a launch over populations
+// of these rows in workgroups of tile_rows rows, m replicas per word and `sets`
+// words side by side: what a colour step of a lane issues, about a instructions
+// for its fields and b per draw of four sites, at 4.45 cycles an instruction
+// for each of the waves that share a SIMD (6 or 8 for one, 9.3 for two; the
+// small words of sweep_rs.hip 6.3, 8.2 and 3.6 each).  Large words save fields,
 // small ones fill the chip and its last round of workgroups.  The figures are
 // measured; over 36 sizes with +-1 couplings from L = 4, R = 10^3 to L = 16,
 // R = 5 10^4 and L = 32, R = 50 the shape chosen is within 10% of the best of
 // all that can be tried.
+// Launches beside others (a batch of several lattices) also count the issue
+// time they take of the chip, at 0.3 of it: nine instances of L = 4 ... 11 with
+// 3528 rows each ran 59 ms with every launch the shortest by itself, 51 so, 59
+// with all of it; real couplings gain nothing from it.
+static double shape_time(const HostInst &h, int m, int sets, int tile_rows, const std::vector<int64_t> &rows, int beside)
+{
+    const int nt = words_threads(h, sets), blocks = std::max(1, (h.gmax + nt - 1) / nt);
+    const bool small = is_rb(h) && rs_small(h.gmax, m, sets);
+    const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
+    // instructions of a lane's colour step: fields, and draws and decisions of
+    // four sites; tables, once a launch
+    double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
+    if (!is_rb(h)) {
+        const int kind = rq_kind(h.variant, m * sets);
+        if (kind == kRQBonds) {
+            a = 180.0;
+            b = 130.0;
+        } else {
+            a = m <= 4 ? 120.0 : 320.0;
+            b = (kind == kRQThr ? 62.0 : 105.0) + (m <= 4 ? 48.0 : 0.0);
+        }
+        once = (double)h.N / nt * (kind == kRQThr ? h.dim == 3 ? 1400.0 : 400.0 : 150.0) / (h.NS * h.ncol);
+    }
+    const int64_t round = (int64_t)kCU * per_cu;
+    int64_t wgs = 0, most = 0;
+    for (int64_t r : rows) {
+        wgs += (r + tile_rows - 1) / tile_rows;
+        most = std::max(most, r);
+    }
+    // cycles per instruction of a lane's colour step with n workgroups on the
+    // chip, from the waves that share a SIMD
+    auto cycles = [&](int64_t n) {
+        const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
+        if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
+        return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
+    };
+    // (a further pass loads and stores rows of its own, about 6 us; tables of
+    // thresholds are made anew)
+    const int passes = std::max<int>(1, (int)((std::min<int64_t>(tile_rows, most) + m * sets - 1) / (m * sets)));
+    const double step = (a + b * m) * blocks + once;
+    double t = step * ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
+    // many waves in step with each other, words of few replicas: L = 5, 128 rows
+    // as two a word in 11 waves take 80 us (46 by the above), as four bytes a
+    // word in 6 waves 60 (53); L = 3, R = 10^5, two a word in 12 waves 110
+    if (is_rb(h) && !small && sets > 1 && nt > 256) t *= 1.0 + std::max(0.0, 1.5 / m - 0.1);
+    if (is_rb(h) && beside > 1)
+        t = t / beside + 0.3 * step * 4.45 * (double)(wgs * (nt / 64)) / (4.0 * kCU);
+    return t * passes + (passes - 1) * 14400.0 / (h.NS * h.ncol);
+}
+
+// The shape used without tuning: that of the shortest launch, one pass a
+// workgroup.
 void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
 {
     const int64_t most = *std::max_element(rows.begin(), rows.end());
@@ -265,47 +314,34 @@ void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
         const int sets = words_sets(h, threads);
         if (sets == last) continue;
         last = sets;
-        const int nt = words_threads(h, sets), blocks = std::max(1, (h.gmax + nt - 1) / nt);
         for (int m = 1; m <= kMaxWord; ++m) {
             if (m > 4 && m * sets > most) break;
             // (+-1 couplings: the table mode draws for four at a time)
             if (is_rb(h) && m > 2 && m % 4 != 0) continue;
-            const bool small = is_rb(h) && rs_small(h.gmax, m, sets);
-            const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
-            // instructions of a lane's colour step: fields, and draws
-            // and decisions of four sites; tables, once a launch
-            double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
-            if (!is_rb(h)) {
-                const int kind = rq_kind(h.variant, m * sets);
-                if (kind == kRQBonds) {
-                    a = 180.0;
-                    b = 130.0;
-                } else {
-                    a = m <= 4 ? 120.0 : 320.0;
-                    b = (kind == kRQThr ? 62.0 : 105.0) + (m <= 4 ? 48.0 : 0.0);
-                }
-                once = (double)h.N / nt * (kind == kRQThr ? h.dim == 3 ? 1400.0 : 400.0 : 150.0) / (h.NS * h.ncol);
-            }
-            const int64_t round = (int64_t)kCU * per_cu;
-            int64_t wgs = 0;
-            for (int64_t r : rows) wgs += (r + m * sets - 1) / (m * sets);
-            // cycles per instruction of a lane's colour step with n
-            // workgroups on the chip, from the waves that share a SIMD
-            auto cycles = [&](int64_t n) {
-                const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
-                if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
-                return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
-            };
-            const double step = (a + b * m) * blocks + once;
-            double t = step * ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
-            if (is_rb(h) && beside > 1)
-                t = t / beside + 0.3 * step * 4.45 * (double)(wgs * (nt / 64)) / (4.0 * kCU);
+            const double t = shape_time(h, m, sets, m * sets, rows, beside);
             if (t < 0.98 * best) {
                 best = t;
                 set_rb(h, m, sets, m * sets);
             }
         }
     }
+}
+
+// What the sweep kernels need to know of the instance to judge a shape.
+static HostInst shape_of(const HostInst &h)
+{
+    HostInst t;
+    t.dim = h.dim;
+    t.L = h.L;
+    t.N = h.N;
+    t.ncol = h.ncol;
+    t.NS = h.NS;
+    t.variant = h.variant;
+    t.gmax = h.gmax;
+    t.row_bytes = h.row_bytes;
+    t.real = h.real;
+    t.tpr = h.tpr;
+    return t;
 }
 
 // The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
@@ -361,17 +397,8 @@ constexpr int kWords[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
 
 static std::vector<HostInst> shape_candidates(const HostInst &h)
 {
-    // (only the shape fields of the returned descriptions are used)
     std::vector<HostInst> c;
-    HostInst t;
-    t.dim = h.dim;
-    t.L = h.L;
-    t.N = h.N;
-    t.variant = h.variant;
-    t.gmax = h.gmax;
-    t.row_bytes = h.row_bytes;
-    t.real = h.real;
-    t.tpr = h.tpr;
+    HostInst t = shape_of(h);
     int last = 0;
     for (int threads : {64, 128, 256, 512, 1024}) {
         const int sets = words_sets(h, threads);
@@ -395,14 +422,7 @@ int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
             const Choice &c = it->second;
-            HostInst t;
-            t.dim = h.dim;
-            t.L = h.L;
-            t.variant = h.variant;
-            t.gmax = h.gmax;
-            t.row_bytes = h.row_bytes;
-            t.real = h.real;
-            t.tpr = h.tpr;
+            HostInst t = shape_of(h);
             t.tile_rows = c.tile_rows;
             t.rp = c.rp;
             t.mrep = c.mrep;

@@ -1,0 +1,38 @@
+"""The sweep shapes that the library gives an instance (no GPU needed): a
+helper program linked with the library asks for them."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+COMPUTE_UNITS = 256
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    from paper_1710_09025_amd import build
+
+    exe = str(tmp_path_factory.mktemp("shape") / "sweep_shape")
+    lib = os.path.dirname(build.LIB)
+    cmd = [build.hipcc(), "-x", "c++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", build.ROCM_INC,
+           os.path.join(ROOT, "tests", "helpers", "sweep_shape.cpp"), "-o", exe, "-x", "none", build.LIB,
+           f"-Wl,-rpath,{lib}", "-L", os.path.join(os.path.dirname(build.ROCM_INC), "lib"), "-lamdhip64"]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+
+    def ask(*cases):
+        """(dim, real, L, R, sweeps, tile_rows, group_replicas) each: dicts"""
+        args = [str(int(v)) for c in cases for v in c]
+        r = subprocess.run([exe, *args], check=True, capture_output=True, text=True)
+        keys = ("status", "m", "sets", "tile_rows", "blocks")
+        return [dict(zip(keys, map(int, line.split()))) for line in r.stdout.splitlines()]
+
+    return ask
+
+
+def test_small_lattices_fill_the_chip(shapes):
+    """A large population of a lattice of a few blocks: workgroups for every
+    SIMD, not one of many waves in step for each compute unit."""
+    for L, R in ((2, 100_000), (3, 100_000), (3, 200_000), (4, 100_000), (5, 100_000)):
+        (s,) = shapes((3, 0, L, R, 10, 0, 0))
+        assert s["status"] == 0 and R / s["tile_rows"] >= 4 * COMPUTE_UNITS, (L, R, s)
