@@ -104,8 +104,9 @@ typedef struct pamc_options {
                                 together, rounded up to whole 64-lane waves,
                                 at most 1024 threads, and fours of at most
                                 64 threads must fill their waves.  The
-                                library sweeps the replicas in words of up
-                                to 32                                      */
+                                library sweeps the tile's replicas in words
+                                of up to 32, as many side by side as make
+                                the shortest launch                        */
     int autotune;            /* 1: when tile_rows and group_replicas are 0,
                                 pick them by timing the candidate shapes on
                                 a throw-away run first (see pamc_autotune);

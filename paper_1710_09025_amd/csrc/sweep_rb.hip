@@ -449,7 +449,7 @@ void launch_sweep_rb(const SweepShape &sh, const Inst *insts, const Work *work, 
     // launch of several rounds it would bring the loads of the later ones
     // together (L = 12, R = 10^5: 725 -> 766 us)
     const bool even = nwork <= 256 * (int)std::min<size_t>(24 / (nt / 64), 160 * 1024 / (lds + 512));
-    if (rb_uniform(sh.G))
+    if (rb_uniform(sh.G) && sh.sets == 1)
         k_sweep_rb<true><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase, even);
     else
         k_sweep_rb<false><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, phase, even);

@@ -322,7 +322,7 @@ void launch_sweep_rs(const SweepShape &sh, const Inst *insts, const Work *work, 
     const size_t lds = rs_lds(sh.plane, sh.G, sh.sets);
 #define PAMC_RS(UNI, NCOL) \
     k_sweep_rs<UNI, NCOL><<<nwork, nt, lds, st>>>(insts, work, sh.tile_rows, sh.M, sh.sets, stride, phase)
-    if (rb_uniform(sh.G)) {
+    if (rb_uniform(sh.G) && sh.sets == 1) {
         if (sh.ncol == 2)
             PAMC_RS(true, 2);
         else

@@ -181,8 +181,8 @@ bool shape_valid(const HostInst &h, const char **why)
     if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
     } else {
-        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || (is_rb(h) && rb_uniform(h.gmax) && h.sets != 1) ||
-            words_threads(h, h.sets) > 1024)
+        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || words_threads(h, h.sets) > 1024 ||
+            (is_rb(h) && h.sets > 1 && h.gmax * h.sets > 1024))
             w = "no such grouping of replicas";
         else if (words_lds(h, h.mrep, h.sets) > words_max_lds(h))
             w = "the workgroup's tile does not fit in LDS";
@@ -346,14 +346,18 @@ static HostInst shape_of(const HostInst &h)
 
 // The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
 // The options keep the ranges documented for them: quads of replicas in byte
-// planes, tiles that fit the workgroup's LDS at one byte per spin (and with +-1 couplings, L = 8 and 16, whole passes of 8 and 2 rows;
-// group_replicas is ignored there and where a lattice has no quads).  The
-// words of M replicas then take as many of the group's replicas as they can.
+// planes, tiles that fit the workgroup's LDS at one byte per spin (and with +-1
+// couplings, L = 8 and 16, whole passes of 8 and 2 rows; group_replicas is
+// ignored there and where a lattice has no quads).  The tile's rows are then
+// swept in the words and sets of the shortest launch.  (Words of 32 replicas in
+// the lanes that few sets have blocks for, eight at L = 4: tile 128, group 64,
+// R = 1000, 41 temperatures in 7.5 ms; now 1.9, quads of byte planes 2.8.  L = 8,
+// tile 64: 7.8, 3.3 and 3.5; real couplings, L = 8, tile 64, R = 20000: 27.6,
+// 8.2 and 12.9.)
 // h holds the default shape on entry.
 bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char **why)
 {
     const char *w = nullptr;
-    int group = 0;
     const int rb = h.row_bytes;
     if (is_rb(h) && (h.L == 8 || h.L == 16)) {
         const int p = h.L == 8 ? 8 : 2;
@@ -375,7 +379,6 @@ bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char *
             table = h.ncol == 3 ? 16 + 144 * h.tpr : h.tpr <= 128 ? 16 + 96 * h.tpr : 0;
             if (slot * rp0 + 32 + 4 * 64 + table > kMaxLds || 8 * (int64_t)cm_plane_bytes(rb) > 65536) table = 0;
         }
-        group = 4 * rp;
         if (tile_rows > 4096)
             w = "tile_rows must be in [1, 4096]";
         else if (rp < 1 || (h.tpr <= 64 && (h.tpr * rp) % 64 != 0) || cm_launch_threads(h.tpr, rp) > 1024)
@@ -386,9 +389,23 @@ bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char *
     }
     if (why) *why = w;
     if (w) return false;
-    const int rows = group > 0 ? std::min(group, tile_rows) : tile_rows;
-    const int m = std::min(rows, kMaxWord);
-    set_rb(h, m, std::max(1, std::min(words_sets(h, is_rb(h) ? 256 : 1024), rows / m)), tile_rows);
+    // m replicas per word, as many sets as n passes over the tile take
+    const int rows = (int)std::min<int64_t>(tile_rows, h.R);
+    HostInst t = shape_of(h);
+    double best = INFINITY;
+    for (int m = 1; m <= kMaxWord; ++m) {
+        if (is_rb(h) && m > 2 && m % 4 != 0) continue;
+        for (int n = 1, sets = 0; sets != 1; n += std::max(1, n / 4)) {
+            sets = (rows + m * n - 1) / (m * n);
+            set_rb(t, m, sets, tile_rows);
+            if (!shape_valid(t, nullptr)) continue;
+            const double time = shape_time(h, m, sets, tile_rows, {h.R}, 1);
+            if (time < 0.98 * best) {
+                best = time;
+                take_shape(h, t);
+            }
+        }
+    }
     return shape_valid(h, why);
 }
 

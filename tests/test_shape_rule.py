@@ -36,3 +36,25 @@ def test_small_lattices_fill_the_chip(shapes):
     for L, R in ((2, 100_000), (3, 100_000), (3, 200_000), (4, 100_000), (5, 100_000)):
         (s,) = shapes((3, 0, L, R, 10, 0, 0))
         assert s["status"] == 0 and R / s["tile_rows"] >= 4 * COMPUTE_UNITS, (L, R, s)
+
+
+# (dim, real couplings, L, R, sweeps, tile_rows, group_replicas), draws of a lane
+# in a colour step: 4 for each pass of the group's quads over the tile
+EXPLICIT = [
+    ((3, 0, 4, 1000, 10, 32, 32), 4), ((3, 0, 4, 1000, 10, 128, 64), 8), ((3, 0, 4, 20000, 10, 128, 64), 8),
+    ((3, 0, 4, 1000, 10, 1000, 256), 16), ((3, 0, 5, 1000, 10, 40, 16), 12), ((3, 0, 5, 1000, 10, 128, 128), 4),
+    ((3, 0, 6, 1000, 10, 64, 32), 8), ((3, 0, 7, 20000, 10, 64, 32), 8), ((3, 0, 8, 1000, 10, 64, 0), 16),
+    ((3, 1, 4, 1000, 10, 128, 128), 4), ((3, 1, 6, 1000, 10, 256, 64), 16), ((3, 1, 8, 20000, 10, 64, 32), 8),
+    ((2, 1, 16, 1000, 10, 64, 32), 8),
+]
+
+
+@pytest.mark.parametrize("case,draws", EXPLICIT)
+def test_tiles_that_are_asked_for_use_the_lanes_they_have_rows_for(shapes, case, draws):
+    """A workgroup sweeps its tile side by side, not a word of 32 replicas in a
+    few lanes: no lane draws for more replicas than with quads."""
+    (s,) = shapes(case)
+    rows = min(case[5], case[3])
+    passes = -(-rows // (s["m"] * s["sets"]))
+    assert s["status"] == 0 and s["tile_rows"] == case[5]
+    assert passes * s["m"] <= draws, (case, s)
