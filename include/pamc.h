@@ -164,7 +164,9 @@ void pamc_default_options(pamc_options *opt);
  * throw-away run needs the device memory of one run of this size.
  * Outputs (each may be NULL): *tile_rows, *group_replicas (0 where the
  * kernel has a fixed value), *ns_per_attempt (sweep time per spin-flip
- * attempt of the winner).
+ * attempt of the winner).  The pair is accepted as the options of those
+ * names, as is the one pamc_sweep_shape reports, also where other values of
+ * their size are not.
  * Errors: PAMC_ERR_INVALID, PAMC_ERR_NOMEM, PAMC_ERR_DEVICE. */
 int pamc_autotune(int L, int64_t R, int sweeps, const pamc_options *opt, int *tile_rows, int *group_replicas,
                   double *ns_per_attempt);

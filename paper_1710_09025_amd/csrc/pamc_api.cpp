@@ -33,6 +33,7 @@ namespace pamc {
 int make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const double *beta, int nT, int NS,
               uint64_t seed, const pamc_options &opt, HostInst &h);
 bool shape_valid(const HostInst &h, const char **why);
+bool reported_shape(const HostInst &h, int tile_rows, int group_replicas);
 bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char **why);
 int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt);
 }
@@ -145,7 +146,9 @@ int pamc::make_inst(int L, const int8_t *J, const int32_t *Jq, int64_t R, const 
     // sweep workgroup shape: explicit, tuned by measurement, or the default
     pamc::default_shape(h, {R});
     if (opt.tile_rows < 0 || opt.tile_rows > 4096) return invalid("tile_rows out of range");
-    if (opt.group_replicas < 0 || opt.group_replicas > 1024) return invalid("group_replicas out of range");
+    if (opt.group_replicas < 0 ||
+        (opt.group_replicas > 1024 && !pamc::reported_shape(h, opt.tile_rows, opt.group_replicas)))
+        return invalid("group_replicas out of range");
     // lattices whose sweep takes replicas in fours honour group_replicas
     const bool quads = real || !(L == 8 || L == 16 || L > 21 || (L > 20 && L % 2 == 0));
     if (opt.tile_rows > 0 || (quads && opt.group_replicas > 0)) {

@@ -242,6 +242,10 @@ static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
     return std::max<int>(1, (int)std::min<int64_t>(n, 160 * 1024 / (lds + 512)));
 }
 
+// Replicas per word worth considering (+-1 couplings: the table mode draws for
+// four at a time).
+static bool words_worth(const HostInst &h, int m) { return !is_rb(h) || m <= 2 || m % 4 == 0; }
+
 // Predicted time (cycles of a SIMD a colour step) of a launch over populations
 // of these rows in workgroups of tile_rows rows, m replicas per word and `sets`
 // words side by side: what a colour step of a lane issues, about a instructions
@@ -316,8 +320,7 @@ void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
         last = sets;
         for (int m = 1; m <= kMaxWord; ++m) {
             if (m > 4 && m * sets > most) break;
-            // (+-1 couplings: the table mode draws for four at a time)
-            if (is_rb(h) && m > 2 && m % 4 != 0) continue;
+            if (!words_worth(h, m)) continue;
             const double t = shape_time(h, m, sets, m * sets, rows, beside);
             if (t < 0.98 * best) {
                 best = t;
@@ -344,6 +347,38 @@ static HostInst shape_of(const HostInst &h)
     return t;
 }
 
+static Key cache_key(const HostInst &h) { return Key(h.variant, h.dim, h.L, h.NS, ceil_log2(h.Rcap), h.packed); }
+
+// The choice measured before for this key, as far as the kernel can run it.
+static bool cached_shape(const std::pair<std::string, Key> &key, HostInst &t, double *ns_per_attempt)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    load_persistent();
+    const auto it = g_cache.find(key);
+    if (it == g_cache.end()) return false;
+    const Choice &c = it->second;
+    t.tile_rows = c.tile_rows;
+    t.rp = c.rp;
+    t.mrep = c.mrep;
+    t.sets = c.sets;
+    if (!shape_valid(t, nullptr)) return false;
+    if (ns_per_attempt) *ns_per_attempt = c.ns_per_attempt;
+    return true;
+}
+
+// Whether the library reports this tile and group for a shape of its own
+// choice (the rule's or the tuner's: one pass a workgroup).
+bool reported_shape(const HostInst &h, int tile_rows, int group_replicas)
+{
+    if (!fixed_group(h) && group_replicas != (tile_rows + 3) / 4 * 4) return false;
+    for (int threads : {64, 128, 256, 512, 1024}) {
+        const int sets = words_sets(h, threads);
+        const int m = tile_rows / sets;
+        if (m >= 1 && m * sets == tile_rows && m <= kMaxWord && words_worth(h, m)) return true;
+    }
+    return false;
+}
+
 // The shape a caller asked for (tile_rows > 0, group_replicas > 0 or both).
 // The options keep the ranges documented for them: quads of replicas in byte
 // planes, tiles that fit the workgroup's LDS at one byte per spin (and with +-1
@@ -353,12 +388,15 @@ static HostInst shape_of(const HostInst &h)
 // the lanes that few sets have blocks for, eight at L = 4: tile 128, group 64,
 // R = 1000, 41 temperatures in 7.5 ms; now 1.9, quads of byte planes 2.8.  L = 8,
 // tile 64: 7.8, 3.3 and 3.5; real couplings, L = 8, tile 64, R = 20000: 27.6,
-// 8.2 and 12.9.)
+// 8.2 and 12.9.)  What the library itself reports for a shape of its choice is
+// taken back whatever those ranges are, and as that shape where it is the
+// default or the one measured for this instance.
 // h holds the default shape on entry.
 bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char **why)
 {
     const char *w = nullptr;
     const int rb = h.row_bytes;
+    const int asked = tile_rows;
     if (is_rb(h) && (h.L == 8 || h.L == 16)) {
         const int p = h.L == 8 ? 8 : 2;
         tile_rows = (tile_rows + p - 1) / p * p;
@@ -387,6 +425,16 @@ bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char *
         else if (slot * rp + 32 + (is_rb(h) ? 4 : 8) * (int64_t)tile_rows + table > kMaxLds)
             w = "the workgroup's tile does not fit in LDS";
     }
+    if (reported_shape(h, asked, group_replicas)) {
+        w = nullptr;
+        if (h.tile_rows == asked && 4 * h.rp == group_replicas) return true;
+        HostInst known = shape_of(h);
+        if (cached_shape({device_tag(), cache_key(h)}, known, nullptr) && known.tile_rows == asked &&
+            4 * known.rp == group_replicas) {
+            take_shape(h, known);
+            return true;
+        }
+    }
     if (why) *why = w;
     if (w) return false;
     // m replicas per word, as many sets as n passes over the tile take
@@ -394,7 +442,7 @@ bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char *
     HostInst t = shape_of(h);
     double best = INFINITY;
     for (int m = 1; m <= kMaxWord; ++m) {
-        if (is_rb(h) && m > 2 && m % 4 != 0) continue;
+        if (!words_worth(h, m)) continue;
         for (int n = 1, sets = 0; sets != 1; n += std::max(1, n / 4)) {
             sets = (rows + m * n - 1) / (m * n);
             set_rb(t, m, sets, tile_rows);
@@ -431,25 +479,12 @@ static std::vector<HostInst> shape_candidates(const HostInst &h)
 
 int tune_shape(HostInst &h, const pamc_options &opt, double *ns_per_attempt)
 {
-    const Key k0(h.variant, h.dim, h.L, h.NS, ceil_log2(h.Rcap), h.packed);
+    const Key k0 = cache_key(h);
     const auto key = std::make_pair(device_tag(), k0);
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        load_persistent();
-        auto it = g_cache.find(key);
-        if (it != g_cache.end()) {
-            const Choice &c = it->second;
-            HostInst t = shape_of(h);
-            t.tile_rows = c.tile_rows;
-            t.rp = c.rp;
-            t.mrep = c.mrep;
-            t.sets = c.sets;
-            if (shape_valid(t, nullptr)) {
-                take_shape(h, t);
-                if (ns_per_attempt) *ns_per_attempt = c.ns_per_attempt;
-                return PAMC_OK;
-            }
-        }
+    HostInst known = shape_of(h);
+    if (cached_shape(key, known, ns_per_attempt)) {
+        take_shape(h, known);
+        return PAMC_OK;
     }
     const auto cand = shape_candidates(h);
     if (cand.empty()) {

@@ -1,6 +1,6 @@
 // Prints the sweep shape that the library gives an instance, host only:
 //   sweep_shape DIM REAL L R SWEEPS TILE_ROWS GROUP_REPLICAS ...  (seven numbers a line of output)
-// as "status replicas_per_word sets tile_rows blocks_of_a_colour".
+// as "status replicas_per_word sets tile_rows group_replicas blocks_of_a_colour".
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -29,7 +29,7 @@ int main(int argc, char **argv)
         pamc::HostInst h;
         const int st = pamc::make_inst(L, J.data(), real ? Jq.data() : nullptr, atoll(argv[i + 3]), beta, 2,
                                        atoi(argv[i + 4]), 1, o, h);
-        printf("%d %d %d %d %d\n", st, h.mrep, h.sets, h.tile_rows, h.gmax);
+        printf("%d %d %d %d %d %d\n", st, h.mrep, h.sets, h.tile_rows, 4 * h.rp, h.gmax);
     }
     return 0;
 }

@@ -1,5 +1,6 @@
 """The sweep shapes that the library gives an instance (no GPU needed): a
 helper program linked with the library asks for them."""
+import json
 import os
 import subprocess
 
@@ -24,7 +25,7 @@ def shapes(tmp_path_factory):
         """(dim, real, L, R, sweeps, tile_rows, group_replicas) each: dicts"""
         args = [str(int(v)) for c in cases for v in c]
         r = subprocess.run([exe, *args], check=True, capture_output=True, text=True)
-        keys = ("status", "m", "sets", "tile_rows", "blocks")
+        keys = ("status", "m", "sets", "tile_rows", "group", "blocks")
         return [dict(zip(keys, map(int, line.split()))) for line in r.stdout.splitlines()]
 
     return ask
@@ -58,3 +59,26 @@ def test_tiles_that_are_asked_for_use_the_lanes_they_have_rows_for(shapes, case,
     passes = -(-rows // (s["m"] * s["sets"]))
     assert s["status"] == 0 and s["tile_rows"] == case[5]
     assert passes * s["m"] <= draws, (case, s)
+
+
+@pytest.mark.parametrize("dim,real,sizes", [(3, 0, range(2, 33)), (3, 1, range(2, 22)), (2, 1, range(2, 65, 3))])
+def test_reported_shapes_are_taken_back(shapes, dim, real, sizes):
+    """tile_rows and group_replicas as pamc_sweep_shape gives them for a default
+    shape, passed as options, are accepted and give that shape."""
+    cases = [(dim, real, L, R, 10) for L in sizes for R in (1, 30, 1000, 20_000, 500_000)]
+    first = shapes(*[c + (0, 0) for c in cases])
+    again = shapes(*[c + (s["tile_rows"], s["group"]) for c, s in zip(cases, first)])
+    for c, a, b in zip(cases, first, again):
+        assert a["status"] == 0 and a == b, (c, a, b)
+
+
+def test_measured_shapes_are_accepted(shapes):
+    """What pamc_autotune reports for the sizes of the shipped file."""
+    from paper_1710_09025_amd import build
+
+    with open(os.path.join(os.path.dirname(build.LIB), "tune_cache.jsonl")) as f:
+        lines = [json.loads(line) for line in f if line.strip()]
+    cases = [(d["dim"], int(d["variant"] >= 128), d["L"], 1000, d["sweeps"], d["tile_rows"], 4 * d["group_quads"])
+             for d in lines]
+    for c, s in zip(cases, shapes(*cases)):
+        assert s["status"] == 0 and s["tile_rows"] >= c[5], (c, s)
