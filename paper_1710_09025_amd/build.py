@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpamc.so")
-SOURCES = ["sweep.hip", "sweep_rb.hip", "sweep_rs.hip", "sweep_rq.hip", "gather.hip", "resample.hip", "icm.hip", "calib.hip", "static_run.hip", "runner.cpp",
+SOURCES = ["sweep.hip", "sweep_rb.hip", "sweep_rs.hip", "sweep_sw.hip", "sweep_rq.hip", "gather.hip", "resample.hip", "icm.hip", "calib.hip", "static_run.hip", "runner.cpp",
            "pamc_api.cpp", "server.cpp", "tune.cpp", "instances.cpp"]
 ARCH = os.environ.get("PAMC_OFFLOAD_ARCH", "gfx950")
 ROCM_INC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")

@@ -24,7 +24,7 @@ struct SweepShape {
     int variant = 0, tile_rows = 0, row_bytes = 0;
     int G = 0, plane = 0; // Philox blocks of the largest colour, words per site plane
     int ncol = 0;         // colours
-    int M = 0, sets = 0;  // replicas per word, sets (of M replicas) per pass of a workgroup
+    int M = 0, sets = 0;  // replicas per word (or kSiteWord + replicas per lane), sets of them per pass of a workgroup
 };
 
 // Dynamic LDS that every kernel may be launched with: gfx950 gives one
@@ -64,6 +64,12 @@ size_t rb_lds(int plane, int sets);
 constexpr int kSmallWord = 4;
 bool rs_small(int G, int m, int sets);
 size_t rs_lds(int plane, int G, int sets);
+// The form whose words are the four sites of a block of one replica (L = 8 and
+// 16): M = kSiteWord + replicas per lane, one thread per block and set.
+constexpr int kSiteWord = 32;
+bool sw_form(int L, int m);
+int sw_threads(int G, int sets);
+size_t sw_lds(int row_bytes, int m, int sets);
 // The same with real couplings, the tables included (thresholds or bond sums
 // by the rows of a pass).  These kernels have
 // little LDS of their own.
@@ -98,6 +104,8 @@ void launch_sweep_rb(const SweepShape &shape, const Inst *insts, const Work *wor
 hipError_t sweep_rb_init();
 void launch_sweep_rs(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 hipError_t sweep_rs_init();
+void launch_sweep_sw(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
+hipError_t sweep_sw_init();
 void launch_sweep_rq(const SweepShape &shape, const Inst *insts, const Work *work, int nwork, int phase, hipStream_t st);
 hipError_t sweep_rq_init();
 // resampling weights and their normaliser (instances with real couplings;

@@ -1,7 +1,7 @@
 // sweep.hip -- initial population and energies (paper Sec. II.B) for gfx950,
 // and the choice of the kernel that runs the checkerboard Metropolis sweeps
-// (Sec. III.A): +-1 couplings in sweep_rb.hip, sweep_rs.hip (few replicas a
-// lane), real couplings in sweep_rq.hip.
+// (Sec. III.A): +-1 couplings in sweep_rb.hip, sweep_rs.hip and sweep_sw.hip
+// (few replicas a lane), real couplings in sweep_rq.hip.
 //
 // A sweep workgroup loads replica rows into LDS, runs all N_S sweeps of the
 // current temperature on chip, recomputes each replica's energy (Eq. (1))
@@ -156,6 +156,7 @@ hipError_t sweep_kernels_init()
 {
     hipError_t r = sweep_rb_init();
     if (r == hipSuccess) r = sweep_rs_init();
+    if (r == hipSuccess) r = sweep_sw_init();
     if (r == hipSuccess) r = sweep_rq_init();
     return r;
 }
@@ -185,6 +186,8 @@ void launch_sweep(const SweepShape &sh, const Inst *insts, const Work *work, int
     if (!nwork) return;
     if (sh.variant != kSweepRB)
         launch_sweep_rq(sh, insts, work, nwork, phase, st);
+    else if (sh.M > kSiteWord)
+        launch_sweep_sw(sh, insts, work, nwork, phase, st);
     else if (rs_small(sh.G, sh.M, sh.sets))
         launch_sweep_rs(sh, insts, work, nwork, phase, st);
     else

@@ -16,8 +16,8 @@
 // What bounds it: the latency of one wave, about 190 instructions and two LDS
 // round trips a colour step for one replica a lane (0.55 us), and some 6 us to
 // read the tables and rows.  Launches of 10 sweeps at beta = 1.5 against words
-// of bits: L = 4, R = 1000: 29.5 -> 21.4 us; L = 8, R = 300: 31.7 -> 25.0;
-// L = 10, R = 500: 35.0 -> 28.6; L = 16, R = 200: 45.5 -> 30.7.  With four
+// of bits: L = 4, R = 1000: 29.5 -> 21.4 us; L = 10, R = 500: 35.0 -> 28.6
+// (L = 8 and 16 have sweep_sw.hip for such populations).  With four
 // replicas a lane the two are level (L = 8, R = 8000: 61.1 and 60.9); beyond,
 // words of bits win.
 #include "launch.h"
@@ -44,7 +44,6 @@ typedef __attribute__((address_space(3))) uint32_t *LdsWord;
 __device__ __forceinline__ uint32_t lds_address(uint32_t *p) { return (uint32_t)(uintptr_t)(LdsWord)p; }
 __device__ __forceinline__ uint32_t word_at(uint32_t a) { return *(LdsWord)(uintptr_t)a; }
 __device__ __forceinline__ void set_word(uint32_t a, uint32_t v) { *(LdsWord)(uintptr_t)a = v; }
-
 
 // acc += a ^ b, acc += [u < T] (T the same in all lanes)
 __device__ __forceinline__ void xor_add(uint32_t &acc, uint32_t a, uint32_t b)

@@ -26,6 +26,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -44,22 +45,31 @@ constexpr int kTimedSteps = 3;      // timed steps per candidate shape (after on
 constexpr int kBurnIn = 8;          // steps before the first candidate
 constexpr double kTuneBeta = 2.0;   // inside the low-temperature part where an anneal spends most steps
 
-constexpr int kMaxWord = 32;        // replicas per word
+constexpr int kMaxWord = kSiteWord;  // replicas per word (more: words of sites, see sw_form)
 
 bool is_rb(const HostInst &h) { return h.variant == kSweepRB; }
 
 // The word kernels' launch: threads and LDS of a workgroup of `sets` sets, the
 // waves a compute unit holds (80 to 188 registers a lane).
-int words_threads(const HostInst &h, int sets) { return is_rb(h) ? rb_threads(h.gmax, sets) : rq_threads(h.gmax, sets); }
+int words_threads(const HostInst &h, int m, int sets)
+{
+    return m > kMaxWord ? sw_threads(h.gmax, sets) : is_rb(h) ? rb_threads(h.gmax, sets) : rq_threads(h.gmax, sets);
+}
 int64_t words_lds(const HostInst &h, int m, int sets)
 {
     const int plane = rb_plane(h.row_bytes);
     if (!is_rb(h)) return rq_lds(h.variant, plane, m, sets);
+    if (m > kMaxWord) return (int64_t)sw_lds(h.row_bytes, m, sets);
     return (int64_t)(rs_small(h.gmax, m, sets) ? rs_lds(plane, h.gmax, sets) : rb_lds(plane, sets));
 }
 int64_t words_max_lds(const HostInst &h) { return is_rb(h) ? kMaxLds : kMaxWordLds; }
-int words_cu_waves(const HostInst &h, bool small) { return !is_rb(h) ? 16 : !small ? 24 : h.ncol == 2 ? 12 : 8; }
+int words_cu_waves(const HostInst &h, int m, bool small)
+{
+    return !is_rb(h) ? 16 : m > kMaxWord ? 28 : !small ? 24 : h.ncol == 2 ? 12 : 8;
+}
 
+// Rows of a pass.
+int words_rows(int m, int sets) { return (m > kMaxWord ? m - kMaxWord : m) * sets; }
 // A shape of words: m replicas per word, `sets` sets per pass, tile_rows rows
 // per workgroup.  rp, reported as group_replicas = 4 rp, is 0 where the caller
 // cannot choose it.
@@ -69,7 +79,7 @@ void set_rb(HostInst &h, int m, int sets, int tile_rows)
     h.mrep = m;
     h.sets = sets;
     h.tile_rows = tile_rows;
-    h.rp = fixed_group(h) ? 0 : (m * sets + 3) / 4;
+    h.rp = fixed_group(h) ? 0 : (words_rows(m, sets) + 3) / 4;
 }
 
 struct Choice {
@@ -80,8 +90,8 @@ struct Choice {
 using Key = std::tuple<int, int, int, int, int, int>;  // variant, dim, L, sweeps, log2 capacity, packed
 
 // The variant a choice of words is stored under tells the replicas per word
-// (kSweepRB + m, m <= kMaxWord; the variants are 64 apart); its workgroups
-// sweep tile_rows = m sets rows in one pass.
+// (kSweepRB + m; the variants are 64 apart); its workgroups sweep tile_rows =
+// words_rows(m, sets) rows in one pass.
 
 std::mutex g_mu;
 std::map<std::pair<std::string, Key>, Choice> g_cache;  // by device and key
@@ -124,7 +134,7 @@ void load_file(const std::string &path)
         if (v >= kSweepRB) {
             c.mrep = v % 64;
             if (c.mrep < 1) continue;
-            c.sets = tr / c.mrep;
+            c.sets = tr / words_rows(c.mrep, 1);
             v -= c.mrep;
         }
         g_cache[{dev, Key(v, d, L, ns, cl, pk)}] = c;
@@ -181,8 +191,8 @@ bool shape_valid(const HostInst &h, const char **why)
     if (h.tile_rows < 1 || h.tile_rows > 4096) {
         w = "tile_rows must be in [1, 4096]";
     } else {
-        if (h.mrep < 1 || h.mrep > kMaxWord || h.sets < 1 || words_threads(h, h.sets) > 1024 ||
-            (is_rb(h) && h.sets > 1 && h.gmax * h.sets > 1024))
+        if (h.mrep < 1 || (h.mrep > kMaxWord && !(is_rb(h) && sw_form(h.L, h.mrep))) || h.sets < 1 ||
+            words_threads(h, h.mrep, h.sets) > 1024 || (is_rb(h) && h.sets > 1 && h.gmax * h.sets > 1024))
             w = "no such grouping of replicas";
         else if (words_lds(h, h.mrep, h.sets) > words_max_lds(h))
             w = "the workgroup's tile does not fit in LDS";
@@ -220,9 +230,9 @@ static int words_sets(const HostInst &h, int threads)
     int best = 1;
     double best_use = 0.0;
     if (is_rb(h) && rb_uniform(h.gmax)) return 1;
-    for (int s = 1; words_threads(h, s) <= std::min(1024, std::max(threads, words_threads(h, 1))); ++s) {
+    for (int s = 1; words_threads(h, 1, s) <= std::min(1024, std::max(threads, words_threads(h, 1, 1))); ++s) {
         if (words_lds(h, kMaxWord, s) > words_max_lds(h)) break;
-        const double use = (double)h.gmax * s / words_threads(h, s);
+        const double use = (double)h.gmax * s / words_threads(h, 1, s);
         if (use >= best_use - 0.005) {
             best = s;
             best_use = std::max(use, best_use);
@@ -235,16 +245,19 @@ static int words_sets(const HostInst &h, int threads)
 // or three waves a SIMD, a workgroup whose waves do not divide among the four
 // SIMDs leaves room that the next one cannot take.)
 constexpr int kCU = 256;
-static int words_per_cu(const HostInst &h, int nt, int64_t lds, bool small)
+static int words_per_cu(const HostInst &h, int m, int nt, int64_t lds, bool small)
 {
-    const int waves = nt / 64, most = words_cu_waves(h, small);
+    const int waves = nt / 64, most = words_cu_waves(h, m, small);
     const int n = small && waves > 4 ? most / 4 / ((waves + 3) / 4) : most / waves;
     return std::max<int>(1, (int)std::min<int64_t>(n, 160 * 1024 / (lds + 512)));
 }
 
 // Replicas per word worth considering (+-1 couplings: the table mode draws for
 // four at a time).
-static bool words_worth(const HostInst &h, int m) { return !is_rb(h) || m <= 2 || m % 4 == 0; }
+static bool words_worth(const HostInst &h, int m)
+{
+    return m > kMaxWord ? is_rb(h) && sw_form(h.L, m) : !is_rb(h) || m <= 2 || m % 4 == 0;
+}
 
 // Predicted time (cycles of a SIMD a colour step) of a launch over populations
 // of these rows in workgroups of tile_rows rows, m replicas per word and `sets`
@@ -262,12 +275,12 @@ static bool words_worth(const HostInst &h, int m) { return !is_rb(h) || m <= 2 |
 // with all of it; real couplings gain nothing from it.
 static double shape_time(const HostInst &h, int m, int sets, int tile_rows, const std::vector<int64_t> &rows, int beside)
 {
-    const int nt = words_threads(h, sets), blocks = std::max(1, (h.gmax + nt - 1) / nt);
-    const bool small = is_rb(h) && rs_small(h.gmax, m, sets);
-    const int per_cu = words_per_cu(h, nt, words_lds(h, m, sets), small);
+    const int nt = words_threads(h, m, sets), blocks = std::max(1, (h.gmax + nt - 1) / nt), pass = words_rows(m, sets);
+    const bool site = m > kMaxWord, small = is_rb(h) && !site && rs_small(h.gmax, m, sets);
+    const int per_cu = words_per_cu(h, m, nt, words_lds(h, m, sets), small);
     // instructions of a lane's colour step: fields, and draws and decisions of
     // four sites; tables, once a launch
-    double a = small ? 155.0 : 190.0, b = small ? 90.0 : 42.0, once = 0.0;
+    double a = site ? 36.0 : small ? 155.0 : 190.0, b = site ? 45.0 : small ? 90.0 : 42.0, once = 0.0;
     if (!is_rb(h)) {
         const int kind = rq_kind(h.variant, m * sets);
         if (kind == kRQBonds) {
@@ -289,28 +302,47 @@ static double shape_time(const HostInst &h, int m, int sets, int tile_rows, cons
     // chip, from the waves that share a SIMD
     auto cycles = [&](int64_t n) {
         const int64_t w = ((n + kCU - 1) / kCU * (nt / 64) + 3) / 4;
+        if (site) return w == 0 ? 0.0 : w == 1 ? 6.3 : 4.3 * (double)w + 1.0;
         if (small) return w == 0 ? 0.0 : w == 1 ? 6.3 : w == 2 ? 8.2 : 3.6 * (double)w;
         return w == 0 ? 0.0 : w == 1 ? (is_rb(h) ? 8.0 : 6.0) : w == 2 ? 9.3 : 4.45 * (double)w;
     };
     // (a further pass loads and stores rows of its own, about 6 us; tables of
     // thresholds are made anew)
-    const int passes = std::max<int>(1, (int)((std::min<int64_t>(tile_rows, most) + m * sets - 1) / (m * sets)));
-    const double step = (a + b * m) * blocks + once;
+    const int passes = std::max<int>(1, (int)((std::min<int64_t>(tile_rows, most) + pass - 1) / pass));
+    const double step = (a + b * words_rows(m, 1)) * blocks + once;
     double t = step * ((double)(wgs / round) * cycles(round) + cycles(wgs % round));
     // many waves in step with each other, words of few replicas: L = 5, 128 rows
     // as two a word in 11 waves take 80 us (46 by the above), as four bytes a
     // word in 6 waves 60 (53); L = 3, R = 10^5, two a word in 12 waves 110
-    if (is_rb(h) && !small && sets > 1 && nt > 256) t *= 1.0 + std::max(0.0, 1.5 / m - 0.1);
+    if (is_rb(h) && !small && !site && sets > 1 && nt > 256) t *= 1.0 + std::max(0.0, 1.5 / m - 0.1);
     if (is_rb(h) && beside > 1)
         t = t / beside + 0.3 * step * 4.45 * (double)(wgs * (nt / 64)) / (4.0 * kCU);
     return t * passes + (passes - 1) * 14400.0 / (h.NS * h.ncol);
 }
 
+// Sets of words of sites side by side: one, or where a set is a wave four (a
+// workgroup's rows and tables in fewer, larger transfers; L = 8, R = 20000:
+// 63 us with one replica a lane in four sets, 60 with two).
+static int site_sets(const HostInst &h, bool many) { return many && h.gmax == 64 ? 4 : 1; }
+
 // The shape used without tuning: that of the shortest launch, one pass a
 // workgroup.
+// Words of sites take populations up to 2 10^7 spins (among the launches side
+// by side), with two replicas a lane where one would give each SIMD more than
+// four waves.  Launches of 10 sweeps, words of sites against the best of
+// replicas: L = 8, R = 1000: 13 and 24 us; 10^4: 35 and 56; 2 10^4: 60 and 78;
+// 5 10^4: 134 and 133; 10^5: 243 and 214; L = 16, R = 300: 21 and 33; 1000: 32
+// and 54; 3000: 74 and 89; 6000: 133 and 129.
 void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
 {
     const int64_t most = *std::max_element(rows.begin(), rows.end());
+    const int64_t total = std::accumulate(rows.begin(), rows.end(), (int64_t)0);
+    if (words_worth(h, kSiteWord + 1) && total * h.N * beside <= 20'000'000) {
+        const bool many = total * (h.gmax / 64) > 16 * kCU;
+        const int m = kSiteWord + (many ? 2 : 1), sets = site_sets(h, many);
+        set_rb(h, m, sets, words_rows(m, sets));
+        return;
+    }
     double best = INFINITY;
     int last = 0;
     for (int threads : {64, 256, 512, 1024}) {
@@ -376,6 +408,8 @@ bool reported_shape(const HostInst &h, int tile_rows, int group_replicas)
         const int m = tile_rows / sets;
         if (m >= 1 && m * sets == tile_rows && m <= kMaxWord && words_worth(h, m)) return true;
     }
+    for (int m = kSiteWord + 1; words_worth(h, m); ++m)
+        if (tile_rows == words_rows(m, 1) || tile_rows == words_rows(m, site_sets(h, true))) return true;
     return false;
 }
 
@@ -441,10 +475,10 @@ bool explicit_shape(HostInst &h, int tile_rows, int group_replicas, const char *
     const int rows = (int)std::min<int64_t>(tile_rows, h.R);
     HostInst t = shape_of(h);
     double best = INFINITY;
-    for (int m = 1; m <= kMaxWord; ++m) {
+    for (int m = 1; m <= kSiteWord + 2; ++m) {
         if (!words_worth(h, m)) continue;
         for (int n = 1, sets = 0; sets != 1; n += std::max(1, n / 4)) {
-            sets = (rows + m * n - 1) / (m * n);
+            sets = (rows + words_rows(m, n) - 1) / words_rows(m, n);
             set_rb(t, m, sets, tile_rows);
             if (!shape_valid(t, nullptr)) continue;
             const double time = shape_time(h, m, sets, tile_rows, {h.R}, 1);
@@ -474,6 +508,11 @@ static std::vector<HostInst> shape_candidates(const HostInst &h)
             if ((m == 1 || m * sets <= 2 * h.Rcap) && shape_valid(t, nullptr)) c.push_back(t);
         }
     }
+    for (int m = kSiteWord + 1; words_worth(h, m); ++m)
+        for (int sets : {1, 4}) {
+            set_rb(t, m, sets, words_rows(m, sets));
+            if (shape_valid(t, nullptr)) c.push_back(t);
+        }
     return c;
 }
 
