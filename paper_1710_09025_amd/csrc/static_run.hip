@@ -9,8 +9,8 @@
 // once per device with hipGetSymbolAddress and hands the kernels pointers
 // into it exactly as it hands them pointers into hipMalloc'ed memory in
 // pamc_create.  The run is the one pamc_create + pamc_anneal would do, with
-// the fixed sweep shape rule, direct kernel launches (no graph) and the
-// caller's stream.
+// the fixed sweep shape rule (longer tiles where its work list would not fit),
+// direct kernel launches (no graph) and the caller's stream.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -103,7 +103,13 @@ extern "C" int pamc_anneal_static(int L, const int8_t *couplings, int64_t R, con
     HostInst h;
     int st = make_inst(L, couplings, nullptr, R, beta, n_temps, sweeps, seed, o, h);
     if (st != PAMC_OK) return st;
-    const size_t need = static_need(h);
+    size_t need = static_need(h);
+    // at the array's end: more passes a sweep workgroup, a shorter work list
+    while (need > kStaticBytes && 2 * h.tile_rows <= 4096) {
+        h.tile_rows *= 2;
+        h.own_shape = true;
+        need = static_need(h);
+    }
     if (need > kStaticBytes)
         return fail(PAMC_ERR_INVALID, "the run needs " + std::to_string(need) + " bytes of device memory, more than the " +
                                           std::to_string(kStaticBytes) + " bytes of the allocation-free path");

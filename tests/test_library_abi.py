@@ -446,3 +446,16 @@ def test_choosing_a_sweep_shape_costs_little_beside_the_layout(lib, L, real):
         return best
 
     assert fastest(refused) < 6 * fastest(layout)
+
+
+@pytest.mark.parametrize("L,R", [(2, 977_052), (3, 502_043), (4, 403_549), (7, 88_125), (8, 61_159), (12, 18_019), (32, 708)])
+def test_static_array_holds_the_largest_populations_it_held(lib, L, R):
+    """Populations at the end of the static array are accepted whatever sweep
+    shape, and so whatever length of work list, the rule gives them (without a
+    device the call ends at looking for one)."""
+    from paper_1710_09025_amd import _capi
+
+    J, beta = np.ones((3, L ** 3), dtype=np.int8), np.array([0.0, 1.0])
+    obs = (_capi.StepObs * 2)()
+    st = lib.pamc_anneal_static(L, J.ctypes.data, R, beta.ctypes.data, 2, 2, 1, None, obs, None)
+    assert st in (_capi.OK, _capi.ERR_DEVICE), lib.pamc_last_error()
