@@ -262,7 +262,9 @@ __device__ __forceinline__ void rb_store(const RBInst &X, const uint32_t *lds, i
     }
     // (every word of a stored row, zeros past the blocks: the overlap reads
     // whole rows, and a buffer that staged a stored state holds its bytes)
-    const int nd = X.srow >> 2;
+    // (opaque: the reciprocal to divide by it would be held through the sweeps)
+    int nd = X.srow >> 2;
+    asm volatile("" : "+s"(nd));
     for (int it = tid; it < sets * nd; it += blockDim.x) {
         const int s = UNI ? 0 : it / nd, d = UNI ? it : it - s * nd;
         const uint32_t *sp = lds + s * 4 * plane;
