@@ -84,7 +84,7 @@ struct Inst {
                         //    keep those in the idle energy buffer); +-1 couplings: parts of the energy histogram
     uint32_t *bsum;     // [nblk]
     uint32_t *boff;     // [nblk]
-    uint32_t *sync;     // [4] workgroups finished in the current sweep / post / weights launch
+    uint32_t *sync;     // [4] workgroups finished: 0 in the first sweep launch of a step with cluster moves, 1 in the post launch
     int32_t post_blocks;  // workgroups of this instance in a post launch
     uint32_t *hist;     // [nlev] energy histogram, (E + 3N)/2
     int32_t hist_copies;  // parts the sweep's workgroups count into: hist, and more in loff (cleared by k_expand);
@@ -97,21 +97,17 @@ struct Inst {
     const double *rho;  // [nT] exp(-2 (beta_{k+1} - beta_k)), host libm
     const double *Rt;   // [nT] nominal population R(beta_k) the resampling targets
     const double *nlnn; // [>= Rcap + 1] n ln n, host libm (shared)
-    // +-1 couplings: per colour and Philox block 64 bytes, the LDS word
-    // indices (16 bits) within a set of the six neighbours of its four sites
-    // ([direction][site]), the sign bits (J = -1: bit 4 d + i) and the mask
-    // of real sites
+    // per colour and Philox block 64 bytes: the LDS word indices (16 bits)
+    // within a set of the six neighbours of its four sites
+    // ([direction][site]), the sign bits (+-1 couplings, J = -1: bit 4 d + i)
+    // and the mask of real sites
     const uint4 *rbtab; // [ncol][gmax][4]
     int32_t rb_plane;   // LDS words per site plane (rb_plane())
     const uint16_t *pos;// [N] storage position of each lexicographic site
     const uint16_t *lexof; // [row_bytes] lexicographic site at each storage position (0xFFFF: padding)
-    // real couplings: per colour and Philox block, the 24 storage positions
-    // of the 6 neighbours of its 4 sites; word 24 is the mask of real
-    // (non-padding) sites, one 0x01 per byte.
     int32_t cbase[3];   // first storage position of each colour
-    int32_t ncs[3];     // sites per colour
-    int32_t gcs[3];     // Philox blocks per colour, ceil(ncs / 4)
-    int32_t gmax;
+    int32_t gcs[3];     // Philox blocks of each colour
+    int32_t gmax;       // ... of the largest
     // real couplings
     int64_t *Eq[2];     // energies, units of 2^-20
     double *wrep;       // [Rcap] resampling weight of each row

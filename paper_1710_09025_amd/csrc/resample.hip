@@ -711,8 +711,8 @@ __global__ __launch_bounds__(1024) void k_post(const Inst *insts, const Work *wo
     if (last_workgroup(count, expected)) post_finish(I, end, k, buf, Rk, sh, a);
 }
 
-// Copy map of the resampling of step k - 1 (more than kMapRows rows) (the step index has advanced):
-// source row r owns destination rows [off_r, off_r + n_r).  A few rows can
+// Copy map of the resampling of step k - 1 (the step index has advanced), more
+// than kMapRows rows: source row r owns destination rows [off_r, off_r + n_r).  A few rows can
 // own thousands of copies when the temperature step is large, so the
 // workgroup of a row block walks the block's destinations instead of its
 // rows: destination j belongs to the last row whose local offset is <= j.

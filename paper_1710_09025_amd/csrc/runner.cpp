@@ -545,10 +545,7 @@ int Runner::upload_inst(int i)
                 col[s] = colour_of(L, x, y, z);
                 rank[s] = ncs[col[s]]++;
             }
-    for (int c = 0; c < 3; ++c) {
-        d.ncs[c] = ncs[c];
-        d.gcs[c] = (ncs[c] + 3) / 4;
-    }
+    for (int c = 0; c < 3; ++c) d.gcs[c] = (ncs[c] + 3) / 4;
     d.gmax = std::max(d.gcs[0], std::max(d.gcs[1], d.gcs[2]));
     // coupling of bond (dir, s): +-1, or j (units of 2^-20) for real couplings
     auto J = [&](int dir, int s) { return h.real ? (int)h.Jq[(size_t)dir * N + s] : (int)h.J[(size_t)dir * N + s]; };
@@ -558,16 +555,16 @@ int Runner::upload_inst(int i)
     const LayoutInfo li = layout_for(L, h.real != 0, h.dim);
     for (int c = 0; c < 3; ++c) d.cbase[c] = li.cbase[c];
     // storage position of each site
-    h.lex_pos.resize(N);
+    std::vector<int> lex_pos((size_t)N);
     std::vector<uint16_t> pos16((size_t)N);
     for (int s = 0; s < N; ++s) {
-        h.lex_pos[s] = li.cbase[col[s]] + rank[s];
-        pos16[s] = (uint16_t)h.lex_pos[s];
+        lex_pos[s] = li.cbase[col[s]] + rank[s];
+        pos16[s] = (uint16_t)lex_pos[s];
     }
     // its inverse over the storage positions of a row (cluster moves read
     // rows in storage order)
     std::vector<uint16_t> lexof16((size_t)h.row_bytes, (uint16_t)0xFFFF);
-    for (int s = 0; s < N; ++s) lexof16[(size_t)h.lex_pos[s]] = (uint16_t)s;
+    for (int s = 0; s < N; ++s) lexof16[(size_t)lex_pos[s]] = (uint16_t)s;
     // per colour, Philox block and site: its six neighbours and couplings.
     // On the square lattice the two z entries of a site point at the site
     // itself with coupling 0 and are not read.  Padding sites point at
@@ -597,7 +594,7 @@ int Runner::upload_inst(int i)
                                        site_of(x, y - 1, z), sq ? s : site_of(x, y, z + 1),
                                        sq ? s : site_of(x, y, z - 1)};
                     for (int dd = 0; dd < 6; ++dd) {
-                        nbp[dd] = h.lex_pos[nb[dd]];
+                        nbp[dd] = lex_pos[nb[dd]];
                         jv[dd] = sq && dd >= 4 ? 0 : J(dd >> 1, dd & 1 ? nb[dd] : s);
                     }
                 }

@@ -45,7 +45,6 @@ struct HostInst {
     int k_enq = 0;                     // steps enqueued so far
     double lnZ_base = 0.0;             // ln Z at step k_base
     int k_base = 0;
-    std::vector<int> lex_pos;          // lexicographic site -> storage position
     // device memory
     void *block = nullptr;             // everything of this instance
     size_t bytes = 0;
@@ -258,7 +257,7 @@ private:
 
 void set_error(const std::string &msg);
 // Work items of the stand-alone gather of instance slot i: blocks of about
-// 32 KB of spin rows, the row count in Work::pad.
+// 32 KB of spin rows, the row count in Work::n.
 std::vector<Work> gather_items(uint32_t slot, int64_t Rcap, int row_bytes);
 
 }  // namespace pamc

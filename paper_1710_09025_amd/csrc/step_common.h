@@ -243,26 +243,20 @@ __device__ __forceinline__ int late_thread()
     return t;
 }
 
-// Adds one count per valid lane to arr[idx]: at low temperature most replicas
-// share a few energies, and per-lane atomics on one address would serialise,
-// so the first kShared distinct indices found in the wave get one atomic
-// each; at high temperature, where nearly every lane has its own, the rest
-// go out in one instruction, a count per lane (a pass per distinct index
-// took a third of the whole launch at L = 8, beta = 0).  Every lane of the
-// wave must call it.
+// Adds one count per valid lane to arr[idx], one atomic per distinct index of
+// the wave: at low temperature most replicas share a few energies, and per-lane
+// atomics on one address would serialise.  Every lane of the wave must call it.
 __device__ __forceinline__ void count_wave(uint32_t *arr, uint32_t idx, bool valid)
 {
-    constexpr int kShared = 64;
     const int lane = late_thread() & 63;
     uint64_t pending = __ballot(valid);
-    for (int i = 0; i < kShared && pending; ++i) {
+    while (pending) {
         const int leader = __builtin_ctzll(pending);
         const uint32_t li = __builtin_amdgcn_readlane(idx, leader);
         const uint64_t same = __ballot(valid && idx == li) & pending;
         if (lane == leader) atomicAdd(&arr[li], (uint32_t)__builtin_popcountll(same));
         pending &= ~same;
     }
-    if ((pending >> lane) & 1u) atomicAdd(&arr[idx], 1u);
 }
 
 // The same where equal indices come in runs of consecutive lanes: one count

@@ -571,7 +571,7 @@ __device__ __forceinline__ void rq_tile(const Inst &I, int k, uint32_t *table, i
                 eacc[q] = (unsigned long long)(X.ncol == 2 ? -h : -(h / 2));
             }
             __syncthreads();
-            tile_energies_real(I, io, eacc, row0, nr, 0);
+            tile_energies_real(I, io, eacc, row0, nr);
             tile_family_count(I, fam, nr);
             __syncthreads();
         }
@@ -596,7 +596,7 @@ __global__ __launch_bounds__(1024) void k_sweep_rq(const Inst *insts, const Work
     if (phase == 1) phase1_done(I, w.n);
 }
 
-// Thresholds cost their making once a workgroup (31 evaluations of the recipe
+// Thresholds cost their making once a workgroup (32 evaluations of the recipe
 // a site on the cubic lattice, 8 on the square one, some 40 instructions
 // each) and save 12 instructions an attempt: from 16 and 4 rows on at 10
 // sweeps a step.

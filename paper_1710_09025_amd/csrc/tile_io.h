@@ -95,19 +95,18 @@ __device__ __forceinline__ void tile_family_count(const Inst &I, const uint32_t 
     }
 }
 
-// Energies of the tile's rows (real couplings; E = the accumulated sums -
-// base), and the lowest of them; the other moments are taken with the weights.
+// Energies of the tile's rows (real couplings), and the lowest of them; the other moments are taken with the weights.
 // (All of them here, with 128-bit sums through LDS and five atomics a
 // workgroup, took 7 us of a workgroup's 170 at L = 8, R = 10^5.)
 __device__ __forceinline__ void tile_energies_real(const Inst &I, const TileIO &io, const unsigned long long *eacc,
-                                                   int r0, int nrows, long long base)
+                                                   int r0, int nrows)
 {
     const int t = late_thread();
     for (int q0 = scalar(t & ~63); q0 < nrows; q0 += blockDim.x) {
         const int q = q0 + (t & 63);
         long long e = kNoEnergy;
         if (q < nrows) {
-            e = (long long)eacc[q] - base;
+            e = (long long)eacc[q];
             io.Eqdst[r0 + q] = e;
         }
         for (int off = 32; off > 0; off >>= 1) {
