@@ -76,7 +76,7 @@ ALU_OPS_PER_ATTEMPT_REAL = 47.5
 
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "sweep_counters.json")
 SWEEP_SOURCES = [os.path.join(ROOT, "paper_1710_09025_amd", "csrc", f)
-                 for f in ("sweep_rb.hip", "sweep_rs.hip", "sweep_rq.hip", "rb_common.h", "tile_io.h",
+                 for f in ("sweep_rb.hip", "sweep_rs.hip", "sweep_sw.hip", "sweep_rq.hip", "rb_common.h", "tile_io.h",
                            "step_common.h", "pamc_dev.h")]
 
 

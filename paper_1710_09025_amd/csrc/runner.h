@@ -31,7 +31,7 @@ struct HostInst {
     int srow_bytes = 0;                // bytes per stored spin row
     int tpr = 0;                       // threads of a replica quad (what the shape options may ask for)
     int rp = 0;                        // quads of replicas a sweep workgroup holds at once
-    int mrep = 0, sets = 0;            // replicas per word, sets of them per pass of a workgroup
+    int mrep = 0, sets = 0;            // replicas per word (SweepShape::M), sets of them per pass of a workgroup
     bool own_shape = false;            // the shape was asked for or measured: launches keep it
     int64_t R = 0, Rcap = 0;
     int nT = 0, NS = 0;

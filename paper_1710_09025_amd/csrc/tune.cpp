@@ -328,13 +328,13 @@ static int site_sets(const HostInst &h, bool many) { return many && h.gmax == 64
 // The shape used without tuning: that of the shortest launch, one pass a
 // workgroup.
 // Words of sites take populations up to 2 10^7 spins, 10^7 where three launches
-// run side by side (they issue more for an attempt: batches of L = 4 ... 8,
-// 12 x 9023 rows: 42.5 ms with words of replicas, 40.7 so;
-// 15 x 12911: 13.1 and 13.5), with two replicas a lane where one would give
-// each SIMD more than four waves.  Launches of 10 sweeps, words of sites against the best of
-// replicas: L = 8, R = 1000: 13 and 24 us; 10^4: 35 and 56; 2 10^4: 60 and 78;
-// 5 10^4: 134 and 133; 10^5: 243 and 214; L = 16, R = 300: 21 and 33; 1000: 32
-// and 54; 3000: 74 and 89; 6000: 133 and 129.
+// run side by side (they issue more for an attempt; batches of L = 4 ... 8 in
+// words of replicas and of sites: 12 x 9023 rows 42.5 and 40.7 ms, 15 x 12911
+// rows 13.1 and 13.5), with two replicas a lane where one would give each SIMD
+// more than four waves.  Launches of 10 sweeps, words of sites against the best
+// of replicas: L = 8, R = 1000: 13 and 24 us; 10^4: 35 and 56; 2 10^4: 60 and
+// 78; 5 10^4: 134 and 133; 10^5: 243 and 214; L = 16, R = 300: 21 and 33; 1000:
+// 32 and 54; 3000: 74 and 89; 6000: 133 and 129.
 void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
 {
     const int64_t most = *std::max_element(rows.begin(), rows.end());
