@@ -68,8 +68,8 @@ typedef struct pamc_options {
     int spin_format;         /* spin buffers in HBM: PAMC_SPINS_INT8 (default),
                                 one byte per site, or PAMC_SPINS_PACKED, one
                                 bit per site (rows 8x smaller; the sweeps
-                                expand a tile to bytes on chip and pack it
-                                when they write it back).  Results are
+                                turn a tile's rows into words on chip and
+                                back when they write them).  Results are
                                 identical for both                          */
     int64_t capacity;        /* rows reserved per buffer; 0 = R + ceil(8 sqrt R) + 64 */
     void *stream;            /* hipStream_t to run on; NULL = a library stream  */
@@ -86,9 +86,8 @@ typedef struct pamc_options {
     int device;              /* HIP device ordinal; -1 = current device       */
     int tile_rows;           /* replica rows per sweep workgroup; 0 = the
                                 library's choice for the lattice size; for
-                                L = 8 and 16 rounded up to a multiple of the
-                                replicas one pass sweeps (any value gives
-                                identical results)                           */
+                                L = 8 and 16 rounded up to a multiple of 8
+                                and 2 (any value gives identical results)    */
     int graphs;              /* 1 (default): capture one temperature step in
                                 a hipGraph and replay it for every step (not
                                 with timing = 1); 0: launch kernels directly */
@@ -297,9 +296,9 @@ int pamc_thresholds(const pamc_ctx *ctx, uint32_t *out, uint8_t *accept_all);
 /* Device time of the steps run since the previous call (options.timing =
  * 1), measured with HIP events on the run's stream:
  *   sweep_ms     the sweep kernels (sweeps of all replicas, energies,
- *                energy histogram, measurement and the resampling table);
- *   resample_ms  copy counts, family and overlap statistics, prefix sum and
- *                copy map;
+ *                energy histogram and, with icm_rounds, the cluster moves);
+ *   resample_ms  measurement, weights, copy counts, family and overlap
+ *                statistics, prefix sum and copy map;
  *   gather_ms    the stand-alone gather of surviving replicas (zero when the
  *                gather is fused into the next sweep, fuse_gather = 1);
  *   n_steps      the number of steps.
