@@ -404,7 +404,7 @@ static bool cached_shape(const std::pair<std::string, Key> &key, HostInst &t, do
 // choice (the rule's or the tuner's: one pass a workgroup).
 bool reported_shape(const HostInst &h, int tile_rows, int group_replicas)
 {
-    if (!fixed_group(h) && group_replicas != (tile_rows + 3) / 4 * 4) return false;
+    if (group_replicas != (fixed_group(h) ? 0 : (tile_rows + 3) / 4 * 4)) return false;
     for (int threads : {64, 128, 256, 512, 1024}) {
         const int sets = words_sets(h, threads);
         const int m = tile_rows / sets;

@@ -82,3 +82,11 @@ def test_measured_shapes_are_accepted(shapes):
              for d in lines]
     for c, s in zip(cases, shapes(*cases)):
         assert s["status"] == 0 and s["tile_rows"] >= c[5], (c, s)
+
+
+@pytest.mark.parametrize("case", [(3, 0, 8, 1000, 10, 16, 2000), (3, 0, 24, 100, 10, 4, 1028), (3, 0, 4, 1000, 10, 8, 1028),
+                                  (3, 0, 10, 1000, 10, 0, 64), (3, 0, 4, 1000, 10, 7, 8), (3, 1, 16, 100, 10, 5, 12)])
+def test_other_pairs_stay_refused(shapes, case):
+    """A group beyond its range, and pairs that nothing reports."""
+    (s,) = shapes(case)
+    assert s["status"] != 0, (case, s)
