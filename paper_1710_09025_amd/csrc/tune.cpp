@@ -364,7 +364,7 @@ void default_shape(HostInst &h, const std::vector<int64_t> &rows, int beside)
     }
 }
 
-// What the sweep kernels need to know of the instance to judge a shape.
+// What the sweep kernels need to know of the instance to weigh a shape.
 static HostInst shape_of(const HostInst &h)
 {
     HostInst t;
